@@ -303,11 +303,17 @@ int sketch_merge(sketch_t *dst, const sketch_t *src, void *hip_stream);
 
 /* ---- tuning ---- */
 
-/* Options of sketch_set_option. The update has two kernels computing the
+/* Options of sketch_set_option. The update has two ways of computing the
  * same sketch: "direct" (each pair sets its r bits with a check-then-
  * atomicOr in the sketch, Alg. 1 as written) and "binned" (the bit sets are
- * grouped by 160 KiB tile of the sketch and applied in LDS, one workgroup
- * per tile or part of a tile; sketches of up to 3276 tiles, 511.9 MiB). */
+ * grouped by tile of the sketch, 160 KiB or less, and applied in LDS, one
+ * workgroup per tile or part of a tile; sketches of up to 3276 tiles of
+ * 160 KiB, 511.9 MiB). Chosen by size, a small update of a sketch that was
+ * just reset builds the tiles from all its pairs instead. Sketches of up to
+ * 40 MiB write the grouped bit sets batch by batch, larger ones (and every
+ * binned job of a call that has such a sketch) in regions per tile, which a
+ * count pass sizes: SAMPLE, REGIONS and the per-block minimum below concern
+ * those. */
 enum {
   SKETCH_OPT_UPDATE_PATH = 1,       /* 0 = choose by size (default),
                                        1 = direct, 2 = binned */
@@ -318,13 +324,16 @@ enum {
                                        the atomicOr (default), 0 = always OR */
   SKETCH_OPT_BINNED_ROUND = 5,      /* binned: pairs per round, 1024 to 2^28
                                        (default 2^28); the round's
-                                       codes (three per 8 bytes, in regions
-                                       and a spill area of that size each)
-                                       take about 5.4*r bytes per pair of
-                                       device memory, allocated on first use */
+                                       codes (three per 8 bytes; in regions
+                                       and a spill area of that size each
+                                       for sketches over 40 MiB) take about
+                                       5.4*r bytes per pair of device memory
+                                       (2.7*r below), allocated on first use */
   SKETCH_OPT_SCATTER_PPT = 6,       /* binned: pairs per thread in one LDS
-                                       sorting batch: 2, 4 or 6 (default);
-                                       capped by LDS at 4 for r in 6..7 and
+                                       sorting batch: 2, 4 or 6 (default;
+                                       sketches of up to 40 MiB take 1 to
+                                       this many, so that every compute unit
+                                       has a batch); capped by LDS at 4 for r in 6..7 and
                                        at 2 for r = 8. Sketches of more than
                                        2048 tiles (of 160 KiB) take 5 for
                                        r <= 5 up to 3072 tiles and 4 above

@@ -447,8 +447,8 @@ int ctx_acquire(int dev, int n_cu, DevCtx **out) {
       rc = fail(SKETCH_E_HIP, "device context: hipEventCreate failed");
     }
     if (!rc) rc = lane_init(c->noalloc_lane);
-    if (!rc && prepare_restore_kernels() != hipSuccess)
-      rc = fail(SKETCH_E_HIP, "device context: restore kernel attributes");
+    if (!rc && (prepare_restore_kernels() != hipSuccess || prepare_update_kernels() != hipSuccess))
+      rc = fail(SKETCH_E_HIP, "device context: kernel attributes");
     // the caller made dev current: this is dev's copy of the array
     if (!rc && hipGetSymbolAddress((void **)&c->noalloc, HIP_SYMBOL(scratch)) != hipSuccess) {
       c->noalloc = nullptr;
@@ -475,17 +475,21 @@ void ctx_release(DevCtx *c) {
   ctx_free(c);
 }
 
-// Copy n jobs into the next ring slot and launch them on st (caller holds
-// c->mu and has entered the pools).
-int launch_jobs(DevCtx *c, const UpdJob *jobs, uint32_t n, bool binned, uint32_t r,
+// Launch n jobs on st: through the next ring slot's table, or by value when
+// the launch needs none (caller holds c->mu and has entered the pools).
+int launch_jobs(DevCtx *c, const UpdJob *jobs, uint32_t n, UpdPath path, uint32_t r,
                 uint32_t ppt, uint32_t apply_grid, hipStream_t st) {
+  if (!launch_reads_table(path, n)) {
+    HIP_OK(launch_update_jobs(jobs, nullptr, n, nullptr, path, r, ppt, apply_grid, st));
+    return SKETCH_OK;
+  }
   const int slot = c->next;
   c->next = (c->next + 1) % DevCtx::SLOTS;
   if (c->armed[slot]) HIP_OK(hipEventSynchronize(c->ev[slot]));
   memcpy(c->h_jobs[slot], jobs, sizeof(UpdJob) * n);
   HIP_OK(hipMemcpyAsync(c->d_jobs[slot], c->h_jobs[slot], sizeof(UpdJob) * n,
                         hipMemcpyHostToDevice, st));
-  HIP_OK(launch_update_jobs(c->h_jobs[slot], c->d_jobs[slot], n, c->d_total + slot, binned, r,
+  HIP_OK(launch_update_jobs(c->h_jobs[slot], c->d_jobs[slot], n, c->d_total + slot, path, r,
                             ppt, apply_grid, st));
   HIP_OK(hipEventRecord(c->ev[slot], st));
   c->armed[slot] = true;
@@ -632,7 +636,9 @@ struct sketch {
   int update_path = 0;          // 0 by size, 1 direct, 2 binned
   size_t binned_min_pairs = 0;
   size_t binned_round = ARENA_MAX_PAIRS;
-  uint32_t nbins = 0;
+  uint32_t nbins = 0;           // tiles of 160 KiB
+  bool lin = false;             // binned rounds take the linear kernels
+  uint32_t tshift = 0, ltiles = 0;   // their tiles: 160 KiB >> tshift
   uint32_t bin_nblk = 0;        // count/scatter blocks per job (hist width)
   uint32_t scatter_ppt = 6;
   uint32_t bin_sample = 0;      // count every n-th batch (0: by the block's batches)
@@ -1015,127 +1021,217 @@ UpdJob job_base(const sketch *s) {
   return J;
 }
 
+// The job's tiles as the linear and fresh kernels cut them.
+void set_tiles(const sketch *s, UpdJob &J) {
+  J.tshift = s->lin ? s->tshift : 0;
+  J.nbins = s->lin ? s->ltiles : s->nbins;
+}
+
 bool wants_binned(const sketch *s, size_t n) {
   if (s->nbins > BIN_MAX) return false;
   return s->update_path == 2 || (s->update_path == 0 && n >= s->binned_min_pairs);
+}
+
+// Pairs times tiles up to which an update of an all-zero sketch that is too
+// small to be binned builds every tile from all the pairs (k_update_fresh).
+// k = 18 (1024 tiles): 16,000 pairs take 58 us, a zero fill and the direct
+// kernel 49 us and the scan of the sketch that the restore then needs 32 us
+// more (8 us from the zero counts); at 64,000 pairs the visits cost more
+// than that.
+constexpr uint64_t FRESH_VISITS = (uint64_t)1 << 25;
+
+// How an update of n pairs runs: by the sketch's options and n; fresh: the
+// sketch is all zero and not yet written.
+UpdPath update_path(const sketch *s, size_t n, bool fresh) {
+  if (wants_binned(s, n)) return s->lin ? UPD_LINEAR : UPD_REGIONS;
+  const uint64_t tiles = s->lin ? s->ltiles : s->nbins;
+  if (fresh && s->update_path == 0 && s->nbins <= BIN_MAX && n <= FRESH_VISITS / tiles)
+    return UPD_FRESH;
+  return UPD_DIRECT;
+}
+
+// The path of each job of an update; fresh(j): job j's sketch is all zero and
+// not yet written. In a call where a job takes the region kernels, the other
+// binned jobs join its launch (a second set of launches, one after the
+// other, was slower: 12 links of 0.3M to 50M pairs, two of them in regions,
+// 2.79 against 2.65 ms a cycle), unless their pairs are not 16-byte aligned.
+template <class Fresh>
+std::vector<UpdPath> update_paths(const sketch_update_job_t *jobs, size_t n_jobs, Fresh fresh) {
+  std::vector<UpdPath> path(n_jobs, UPD_DIRECT);
+  bool regions = false;
+  for (size_t j = 0; j < n_jobs; j++) {
+    if (jobs[j].n_pairs) path[j] = update_path(jobs[j].sketch, jobs[j].n_pairs, fresh(j));
+    regions = regions || path[j] == UPD_REGIONS;
+  }
+  for (size_t j = 0; j < n_jobs && regions; j++)
+    if (path[j] == UPD_LINEAR && !(((uintptr_t)jobs[j].d_pairs) & 15u)) path[j] = UPD_REGIONS;
+  return path;
+}
+
+// Whether a job on this path writes every tile of a fresh sketch (no pair
+// goes through the direct kernel first), with its zero counts.
+bool writes_all(const sketch_update_job_t &job, UpdPath path) {
+  if (!job.n_pairs) return false;
+  return path == UPD_REGIONS ? !(((uintptr_t)job.d_pairs) & 15u) : path != UPD_DIRECT;
 }
 
 // A launch group: jobs that share the kernels (same r, path, check flag,
 // scatter batch).
 struct Group {
   uint32_t r;
-  bool binned;
+  UpdPath path;
   uint32_t check;
   uint32_t ppt;
   uint32_t apply_grid;
-  bool wide;                    // binned: more than 2048 tiles per sketch
+  bool wide;                    // regions: more than 2048 tiles per sketch
   std::vector<UpdJob> jobs;
-  size_t pairs = 0;             // binned: pairs of the jobs (the arena's share)
+  size_t pairs = 0;             // arena paths: pairs of the jobs (the arena's share)
 };
 
-// The scatter batch (pairs per thread) of a binned launch of n jobs with
-// the requested setting ppt.
-uint32_t launch_ppt(const UpdJob *J, uint32_t n, uint32_t r, uint32_t ppt) {
+// Whether a path's launches use the shared update arena.
+bool uses_arena(UpdPath path) { return path == UPD_REGIONS || path == UPD_LINEAR; }
+
+// The scatter batch (pairs per thread) of a launch of n jobs with the
+// requested setting ppt. A linear launch takes as large a batch as leaves
+// every compute unit one (its blocks hold one batch each at a time): fewer
+// pairs than that spread over smaller batches.
+uint32_t launch_ppt(const UpdJob *J, uint32_t n, UpdPath path, uint32_t r, uint32_t ppt) {
   uint32_t max_tiles = 0;
-  for (uint32_t j = 0; j < n; j++) max_tiles = std::max(max_tiles, J[j].nbins);
-  return scatter_ppt(r, max_tiles, ppt);
+  uint64_t pairs = 0;
+  for (uint32_t j = 0; j < n; j++) {
+    max_tiles = std::max(max_tiles, J[j].nbins);
+    pairs += J[j].n;
+  }
+  const uint32_t p = scatter_ppt(r, max_tiles, ppt);
+  if (path != UPD_LINEAR) return p;
+  const uint64_t per = pairs / (1024 * (uint64_t)J[0].hstride);
+  return per >= p ? p : per >= 4 && p > 4 ? 4 : per >= 2 ? 2 : 1;
 }
 
-// 32-bit words a binned job takes from the arena's code buffer: its code
+// 32-bit words a job takes from the arena's code buffer. Regions: its code
 // regions and spill area (job_code_words 64-bit words) and its tiles'
-// spill-run lists (nbins * dmax uint2), 16-byte aligned.
-size_t job_arena_words(const UpdJob &J, uint32_t r, uint32_t ppt) {
+// spill-run lists (nbins * dmax uint2). Linear: its batches' words and the
+// directory. 16-byte aligned.
+size_t job_arena_words(const UpdJob &J, UpdPath path, uint32_t r, uint32_t ppt) {
+  if (path == UPD_LINEAR)
+    return 2 * (size_t)J.nbatch * J.wcap + (((size_t)J.nbatch * LIN_DIR / 2 + 7) & ~(size_t)3);
   const uint64_t w = code_words_bound(J.n, r, J.nbins, J.nblk, J.chunk);
   const uint64_t dmax = job_batches(J.nblk, J.chunk, ppt);
   return (size_t)(2 * job_code_words(w, J.nbins) + ((2 * J.nbins * dmax + 3) & ~3ull));
 }
 
-// Block and tile prefixes of one launch's jobs; for a binned launch, the
-// code words and scratch tiles its jobs take from an arena.
-void layout_launch(UpdJob *J, uint32_t n, bool binned, uint32_t r, uint32_t ppt, size_t *words,
+// Batches of a linear launch's jobs and their blocks: about one block per
+// compute unit for a job alone, about four for several jobs (whose blocks
+// the dispatcher then evens out).
+void shape_linear(UpdJob *J, uint32_t n, uint32_t r, uint32_t ppt) {
+  uint64_t total = 0;
+  for (uint32_t j = 0; j < n; j++) {
+    J[j].nbatch = (uint32_t)((J[j].n + 1024 * ppt - 1) / (1024 * ppt));
+    J[j].wcap = lin_batch_words(r, ppt, J[j].nbins);
+    total += J[j].nbatch;
+  }
+  const uint64_t blocks = (uint64_t)J[0].hstride * (n > 1 ? 4 : 1);
+  const uint64_t per = std::max<uint64_t>(1, (total + blocks - 1) / blocks);
+  for (uint32_t j = 0; j < n; j++) {
+    J[j].chunk = per;
+    J[j].nblk = (uint32_t)((J[j].nbatch + per - 1) / per);
+  }
+}
+
+// Block and tile prefixes of one launch's jobs; for a launch that uses the
+// arena, the code words and scratch tiles its jobs take from it.
+void layout_launch(UpdJob *J, uint32_t n, UpdPath path, uint32_t r, uint32_t ppt, size_t *words,
                    size_t *tiles) {
   uint32_t blk = 0, tile = 0;
   *words = 0;
   *tiles = 0;
-  const uint32_t pe = binned ? launch_ppt(J, n, r, ppt) : 0;
+  const uint32_t pe = uses_arena(path) ? launch_ppt(J, n, path, r, ppt) : 0;
+  if (path == UPD_LINEAR) shape_linear(J, n, r, pe);
   for (uint32_t j = 0; j < n; j++) {
     J[j].blk0 = blk;
     J[j].tile0 = tile;
     blk += J[j].nblk;
-    tile += J[j].nbins;
-    if (binned) {
+    tile += path == UPD_LINEAR || path == UPD_FRESH ? tile_groups(J[j].nbins) : J[j].nbins;
+    if (uses_arena(path)) *words += job_arena_words(J[j], path, r, pe);
+    if (path == UPD_REGIONS) {
       const size_t w = code_words_bound(J[j].n, r, J[j].nbins, J[j].nblk, J[j].chunk);
-      *words += job_arena_words(J[j], r, pe);
       *tiles += w / APPLY_ITEM + 1;
     }
   }
 }
 
-// Binned jobs' code buffers (regions, spill area, spill-run lists) and
-// scratch tiles, packed one after another.
-void place_arena(UpdJob *J, uint32_t n, uint32_t r, uint32_t ppt, uint32_t *codes,
+// The jobs' code buffers (regions, spill area, spill-run lists; or batches
+// and directory) and scratch tiles, packed one after another.
+void place_arena(UpdJob *J, uint32_t n, UpdPath path, uint32_t r, uint32_t ppt, uint32_t *codes,
                  uint32_t *scratch) {
-  const uint32_t pe = launch_ppt(J, n, r, ppt);
+  const uint32_t pe = launch_ppt(J, n, path, r, ppt);
   size_t wo = 0, to = 0;
   for (uint32_t j = 0; j < n; j++) {
-    const uint64_t w = code_words_bound(J[j].n, r, J[j].nbins, J[j].nblk, J[j].chunk);
     J[j].codes = codes + wo;
-    J[j].rcap = job_region_words(w, J[j].nbins);
-    J[j].dmax = job_batches(J[j].nblk, J[j].chunk, pe);
-    J[j].desc = reinterpret_cast<uint2 *>(codes + wo + 2 * job_code_words(w, J[j].nbins));
-    J[j].scratch = scratch + to * (size_t)BIN_TILE_WORDS;
-    wo += job_arena_words(J[j], r, pe);
-    to += w / APPLY_ITEM + 1;
+    if (path == UPD_LINEAR) {
+      J[j].dir = reinterpret_cast<uint16_t *>(codes + wo + 2 * (size_t)J[j].nbatch * J[j].wcap);
+    } else {
+      const uint64_t w = code_words_bound(J[j].n, r, J[j].nbins, J[j].nblk, J[j].chunk);
+      J[j].rcap = job_region_words(w, J[j].nbins);
+      J[j].dmax = job_batches(J[j].nblk, J[j].chunk, pe);
+      J[j].desc = reinterpret_cast<uint2 *>(codes + wo + 2 * job_code_words(w, J[j].nbins));
+      J[j].scratch = scratch + to * (size_t)BIN_TILE_WORDS;
+      to += w / APPLY_ITEM + 1;
+    }
+    wo += job_arena_words(J[j], path, r, pe);
   }
 }
 
 // Launch a group's jobs now (caller holds c->mu), at most MAX_JOBS per
 // launch; binned jobs take the device's shared arena.
 int flush_group(DevCtx *c, Group &g, hipStream_t st) {
+  const bool arena = uses_arena(g.path);
   for (size_t at = 0; at < g.jobs.size(); at += MAX_JOBS) {
     const uint32_t n = (uint32_t)std::min<size_t>(MAX_JOBS, g.jobs.size() - at);
     UpdJob *J = g.jobs.data() + at;
     size_t words, tiles;
-    layout_launch(J, n, g.binned, g.r, g.ppt, &words, &tiles);
-    if (g.binned) {
+    layout_launch(J, n, g.path, g.r, g.ppt, &words, &tiles);
+    uint32_t ppt = g.ppt;
+    if (arena) {
       int rc = ensure_arena(c, words, tiles);
       if (rc) return rc;
-      place_arena(J, n, g.r, g.ppt, c->codes, c->scratch);
+      place_arena(J, n, g.path, g.r, g.ppt, c->codes, c->scratch);
+      if (g.path == UPD_LINEAR) ppt = launch_ppt(J, n, g.path, g.r, g.ppt);
     }
-    // only binned launches use the shared arena
-    int rc = g.binned ? lane_enter(c->arena_lane, st) : SKETCH_OK;
+    // only these launches use the shared arena
+    int rc = arena ? lane_enter(c->arena_lane, st) : SKETCH_OK;
     if (rc) return rc;
-    rc = launch_jobs(c, J, n, g.binned, g.r, g.ppt, g.apply_grid, st);
+    rc = launch_jobs(c, J, n, g.path, g.r, ppt, g.apply_grid, st);
     if (rc) return rc;
-    rc = g.binned ? lane_leave(c->arena_lane, st) : SKETCH_OK;
+    rc = arena ? lane_leave(c->arena_lane, st) : SKETCH_OK;
     if (rc) return rc;
   }
   g.jobs.clear();
   return SKETCH_OK;
 }
 
-// Binned jobs share a launch only with sketches of the same tile class: the
+// Region jobs share a launch only with sketches of the same tile class: the
 // launch's largest sketch picks the scatter variant, and one of more than
 // 2048 tiles would hold every job of the launch to its smaller batches.
-size_t group_of(std::vector<Group> &groups, const sketch *s, const UpdJob &J, bool binned) {
-  const bool wide = binned && s->nbins > 2048;
+size_t group_of(std::vector<Group> &groups, const sketch *s, const UpdJob &J, UpdPath path) {
+  const bool wide = path == UPD_REGIONS && s->nbins > 2048;
   for (size_t i = 0; i < groups.size(); i++) {
     const Group &g = groups[i];
-    if (g.r == s->p.r && g.binned == binned && g.wide == wide &&
-        (binned ? g.ppt == s->scatter_ppt : g.check == J.check))
+    if (g.r == s->p.r && g.path == path && g.wide == wide &&
+        (uses_arena(path) ? g.ppt == s->scatter_ppt : path == UPD_FRESH || g.check == J.check))
       return i;
   }
-  groups.push_back(Group{s->p.r, binned, J.check, s->scatter_ppt, s->apply_grid, wide, {}});
+  groups.push_back(Group{s->p.r, path, J.check, s->scatter_ppt, s->apply_grid, wide, {}});
   return groups.size() - 1;
 }
 
-void add_job(std::vector<Group> &groups, const sketch *s, const UpdJob &J, bool binned) {
-  Group &g = groups[group_of(groups, s, J, binned)];
+void add_job(std::vector<Group> &groups, const sketch *s, const UpdJob &J, UpdPath path) {
+  Group &g = groups[group_of(groups, s, J, path)];
   g.apply_grid = g.jobs.empty() ? s->apply_grid
                  : (g.apply_grid == 0 || s->apply_grid == 0) ? 0u
                                                              : std::max(g.apply_grid, s->apply_grid);
   g.jobs.push_back(J);
-  if (binned) g.pairs += J.n;
+  if (uses_arena(path)) g.pairs += J.n;
 }
 
 // Pairs, blocks and pairs per block of a binned round of m pairs: about
@@ -1185,44 +1281,36 @@ int check_update_jobs(const sketch_update_job_t *jobs, size_t n_jobs, const char
 // holds at most ARENA_MAX_PAIRS pairs, and one that is full is flushed
 // during the pass, the rest at its end, so a job's rounds run in order.
 // Job j's per-sketch arrays come from base(j).
-// Whether an update of n pairs at p takes binned rounds from its first pair
-// on (no pair goes through the direct kernel first).
-bool binned_from_start(const sketch *s, const uint32_t *p, size_t n) {
-  return n && wants_binned(s, n) && !(((uintptr_t)p) & 15u);
-}
-
-// fresh (may be null): per job, 1 if the job's first binned round starts
-// from a fresh sketch (binned_from_start must hold); consumed by that round.
+// path: update_paths' choice. fresh: per job, 1 if its sketch is all zero and
+// the job's update writes every tile (writes_all must hold); the first round
+// of the job consumes it.
 template <class Base, class Flush>
-int schedule_update(const sketch_update_job_t *jobs, size_t n_jobs, Base base, Flush flush,
-                    char *fresh = nullptr) {
+int schedule_update(const sketch_update_job_t *jobs, size_t n_jobs,
+                    const std::vector<UpdPath> &path, Base base, Flush flush, char *fresh) {
   std::vector<const uint32_t *> ptr(n_jobs);
   std::vector<size_t> left(n_jobs);
-  std::vector<char> binned(n_jobs);
   std::vector<Group> groups;
   for (size_t j = 0; j < n_jobs; j++) {
     sketch *s = jobs[j].sketch;
     ptr[j] = jobs[j].d_pairs;
     left[j] = jobs[j].n_pairs;
-    binned[j] = left[j] && wants_binned(s, left[j]);
-    if (binned[j] && (((uintptr_t)ptr[j]) & 15u)) {
+    if (path[j] == UPD_REGIONS && (((uintptr_t)ptr[j]) & 15u)) {
       // the count pass reads pairs 16 bytes at a time: the first pair goes
       // through the direct kernel so the rest starts 16-byte aligned
       UpdJob J = base(j);
       J.pairs = reinterpret_cast<const uint2 *>(ptr[j]);
       J.n = 1;
       J.nblk = 1;
-      add_job(groups, s, J, false);
+      add_job(groups, s, J, UPD_DIRECT);
       ptr[j] += 2;
       left[j]--;
     }
   }
-  // pairs per block at least: 4096 per binned job of the call, up to 32768.
-  // A window alone spreads over many compute units (a 1M-pair window takes
-  // 245 blocks, against 31 at 32k pairs per block); the jobs of a batch
-  // share them, and more blocks per job would only add per-block work
+  // regions: pairs per block at least: 4096 per binned job of the call, up
+  // to 32768. A window alone spreads over many compute units; the jobs of a
+  // batch share them, and more blocks per job would only add per-block work
   size_t n_binned = 0;
-  for (size_t j = 0; j < n_jobs; j++) n_binned += binned[j] ? 1 : 0;
+  for (size_t j = 0; j < n_jobs; j++) n_binned += path[j] == UPD_REGIONS ? 1 : 0;
   const size_t min_chunk = std::min<size_t>(32768, 4096 * std::max<size_t>(1, n_binned));
   for (;;) {
     bool any = false;
@@ -1231,30 +1319,34 @@ int schedule_update(const sketch_update_job_t *jobs, size_t n_jobs, Base base, F
       sketch *s = jobs[j].sketch;
       UpdJob J = base(j);
       J.pairs = reinterpret_cast<const uint2 *>(ptr[j]);
-      if (binned[j]) {
-        Group &g = groups[group_of(groups, s, J, true)];
+      size_t m = left[j];
+      if (uses_arena(path[j])) {
+        Group &g = groups[group_of(groups, s, J, path[j])];
         if (g.pairs >= ARENA_MAX_PAIRS) {
           int rc = flush(g);
           if (rc) return rc;
           g.jobs.clear();
           g.pairs = 0;
         }
-        const size_t m = std::min({left[j], s->binned_round, ARENA_MAX_PAIRS - g.pairs});
-        bin_shape(s, m, min_chunk, J);
-        if (fresh) {
-          J.fresh = (uint32_t)fresh[j];
-          fresh[j] = 0;
-        }
-        add_job(groups, s, J, true);
-        ptr[j] += 2 * m;
-        left[j] -= m;
-      } else {
-        J.n = left[j];
-        J.nblk = (uint32_t)std::max<size_t>(
-            1, std::min<size_t>((size_t)s->update_grid, (left[j] + 255) / 256));
-        add_job(groups, s, J, false);
-        left[j] = 0;
+        m = std::min({left[j], s->binned_round, ARENA_MAX_PAIRS - g.pairs});
       }
+      if (path[j] == UPD_REGIONS) {
+        bin_shape(s, m, min_chunk, J);
+      } else {
+        J.n = m;
+        if (path[j] == UPD_DIRECT)
+          J.nblk = (uint32_t)std::max<size_t>(
+              1, std::min<size_t>((size_t)s->update_grid, (m + 255) / 256));
+        else
+          set_tiles(s, J);
+      }
+      if (path[j] != UPD_DIRECT) {
+        J.fresh = (uint32_t)fresh[j];
+        fresh[j] = 0;
+      }
+      add_job(groups, s, J, path[j]);
+      ptr[j] += 2 * m;
+      left[j] -= m;
       any = true;
     }
     for (Group &g : groups) {
@@ -1298,27 +1390,31 @@ int update_jobs(const sketch_update_job_t *jobs, size_t n_jobs, hipStream_t st) 
   DEVICE_GUARD(jobs[0].sketch->p.device);
   DevCtx *c = jobs[0].sketch->ctx;
   std::lock_guard<std::mutex> lk(c->mu);
-  // a fresh sketch whose update is binned from its first pair skips its
-  // zero fill; any other fresh sketch with pairs gets its zeros first
+  // a fresh sketch whose update writes every tile skips its zero fill; any
+  // other fresh sketch with pairs gets its zeros first. A linear update
+  // always writes every tile, with the zero counts
   std::vector<char> fresh(n_jobs, 0);
+  const std::vector<UpdPath> path =
+      update_paths(jobs, n_jobs, [&](size_t j) { return jobs[j].sketch->fresh; });
   for (size_t j = 0; j < n_jobs; j++) {
     sketch *s = jobs[j].sketch;
     if (jobs[j].n_pairs == 0) continue;
     rc = lane_enter(s->lane, st);
     if (rc) return rc;
-    const bool binned = binned_from_start(s, jobs[j].d_pairs, jobs[j].n_pairs);
-    if (s->fresh && binned) {
+    if (s->fresh && writes_all(jobs[j], path[j])) {
       fresh[j] = 1;
       s->fresh = false;
       s->lez_valid = s->lez != nullptr;     // every tile is written
     } else {
       rc = materialize(s, st);
       if (rc) return rc;
-      if (!binned) s->lez_valid = false;    // the direct kernel sets bits
+      if (path[j] == UPD_LINEAR) s->lez_valid = s->lez != nullptr;
+      else if (path[j] == UPD_DIRECT || (((uintptr_t)jobs[j].d_pairs) & 15u))
+        s->lez_valid = false;               // the direct kernel sets bits
     }
   }
   rc = schedule_update(
-      jobs, n_jobs, [&](size_t j) { return job_base(jobs[j].sketch); },
+      jobs, n_jobs, path, [&](size_t j) { return job_base(jobs[j].sketch); },
       [&](Group &g) { return flush_group(c, g, st); }, fresh.data());
   for (size_t j = 0; j < n_jobs && !rc; j++)
     if (jobs[j].n_pairs) rc = lane_leave(jobs[j].sketch->lane, st);
@@ -1365,7 +1461,7 @@ struct PlanLaunch {
   std::vector<UpdJob> h;
   UpdJob *d = nullptr;
   uint32_t *d_total = nullptr;
-  bool binned = false;
+  UpdPath path = UPD_DIRECT;
   uint32_t r = 0, ppt = 0, apply_grid = 0;
 };
 
@@ -1450,9 +1546,12 @@ int plan_enqueue(sketch_plan *P, hipStream_t st) {
   if (P->flags & SKETCH_PLAN_RESET)
     for (PlanJob &j : P->jobs)
       if (!j.fresh) HIP_OK(launch_fill_u32(j.s->d_sketch, j.s->words, 0u, j.s->grid * 4, st));
-  for (PlanLaunch &L : P->launches)
-    HIP_OK(launch_update_jobs(L.h.data(), L.d, (uint32_t)L.h.size(), L.d_total, L.binned, L.r,
-                              L.ppt, L.apply_grid, st));
+  for (PlanLaunch &L : P->launches) {
+    const uint32_t n = (uint32_t)L.h.size();
+    const uint32_t ppt =
+        L.path == UPD_LINEAR ? launch_ppt(L.h.data(), n, L.path, L.r, L.ppt) : L.ppt;
+    HIP_OK(launch_update_jobs(L.h.data(), L.d, n, L.d_total, L.path, L.r, ppt, L.apply_grid, st));
+  }
   if (P->flags & SKETCH_PLAN_RESTORE) {
     std::vector<uint8_t> used(RESTORE_POOLS, 0);
     for (const PlanJob &j : P->jobs) used[j.pool] = 1;
@@ -1483,8 +1582,9 @@ int plan_build_graph(sketch_plan *P) {
     for (size_t i = 0; i < P->jobs.size(); i++) P->jobs[i].pool = pools[i];
   }
   for (PlanLaunch &L : P->launches) {
-    if (!L.binned) continue;
-    place_arena(L.h.data(), (uint32_t)L.h.size(), L.r, L.ppt, c->codes, c->scratch);
+    if (!uses_arena(L.path)) continue;
+    const uint32_t n = (uint32_t)L.h.size();
+    place_arena(L.h.data(), n, L.path, L.r, L.ppt, c->codes, c->scratch);
     HIP_OK(hipMemcpy(L.d, L.h.data(), sizeof(UpdJob) * L.h.size(), hipMemcpyHostToDevice));
   }
   HIP_OK(hipStreamBeginCapture(P->cap, hipStreamCaptureModeThreadLocal));
@@ -1560,13 +1660,20 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   s->grid = s->n_cu * 8;
   s->update_grid = s->n_cu * 8;
   s->nbins = (uint32_t)((s->words + BIN_TILE_WORDS - 1) / BIN_TILE_WORDS);
+  s->tshift = lin_shift(s->words);
+  s->ltiles = lin_tiles(s->words, s->tshift);
+  s->lin = s->ltiles <= LIN_TILES;
   s->bin_nblk = (uint32_t)std::min<int>((int)BIN_BLOCKS_MAX, s->n_cu);
   // one apply workgroup per item: the dispatcher balances uneven tiles
   // (measured 60 us faster than one per compute unit on the 100M window)
   s->apply_grid = 0;
-  // measured crossover on MI355X (100M-pair Zipf window): the binned update
-  // wins from ~1e5 pairs at k = 14 and ~2e5 at k = 18
-  s->binned_min_pairs = std::max<size_t>(s->words / 256, 1 << 14);
+  // measured crossovers on MI355X (Zipf(1.1) windows). Linear sketches, k =
+  // 14 to 16: the linear update takes 23-29 us at 16,000 pairs and 23-30 at
+  // 32,000; a reset sketch built from all its pairs 17-24 and 23-29; the
+  // direct kernel on a written sketch about 22 and 40. Larger sketches: the
+  // regions take 91 us at k = 17 and 125 at k = 18 for any small window; the
+  // direct kernel 92 and 105 at 128,000 pairs, 235 and 280 at 256,000
+  s->binned_min_pairs = s->lin ? 24576 : std::max<size_t>(s->words / 256, 1 << 14);
 
   const size_t n_le = (size_t)params->r << params->k;
   const size_t nb = (size_t)1 << (params->k - params->alpha);
@@ -2086,16 +2193,19 @@ int sketch_plan_create(const sketch_plan_job_t *jobs, size_t n_jobs, int flags,
     rc = fail(SKETCH_E_HIP, "plan: hipStreamCreate failed");
   }
   std::vector<char> fresh(n_jobs, 0);
-  if (flags & SKETCH_PLAN_RESET)
+  const bool reset = flags & SKETCH_PLAN_RESET;
+  const std::vector<UpdPath> path =
+      update_paths(uj.data(), n_jobs, [&](size_t) { return reset; });
+  if (reset)
     for (size_t j = 0; j < n_jobs; j++) {
-      P->jobs[j].fresh = binned_from_start(uj[j].sketch, uj[j].d_pairs, uj[j].n_pairs);
+      P->jobs[j].fresh = writes_all(uj[j], path[j]);
       fresh[j] = P->jobs[j].fresh;
     }
   if (!rc) {
     std::lock_guard<std::mutex> lk(c->mu);
     // the update launches, with this plan's per-job arrays
     rc = schedule_update(
-        uj.data(), n_jobs,
+        uj.data(), n_jobs, path,
         [&](size_t j) {
           UpdJob J = job_base(uj[j].sketch);
           const PlanJob &pj = P->jobs[j];
@@ -2116,10 +2226,10 @@ int sketch_plan_create(const sketch_plan_job_t *jobs, size_t n_jobs, int flags,
             PlanLaunch L;
             L.h.assign(g.jobs.begin() + at, g.jobs.begin() + at + n);
             size_t words, tiles;
-            layout_launch(L.h.data(), n, g.binned, g.r, g.ppt, &words, &tiles);
+            layout_launch(L.h.data(), n, g.path, g.r, g.ppt, &words, &tiles);
             P->arena_words = std::max(P->arena_words, words);
             P->arena_tiles = std::max(P->arena_tiles, tiles);
-            L.binned = g.binned;
+            L.path = g.path;
             L.r = g.r;
             L.ppt = g.ppt;
             L.apply_grid = g.apply_grid;

@@ -32,10 +32,13 @@ __device__ __forceinline__ uint32_t hash_h1(const Geom &G, uint32_t y) {
   return (uint32_t)((G.a1 * (uint64_t)y + G.b1) >> (64 - G.log2g));
 }
 
-// BL(i): k bits of x starting at bit (i-1)*alpha (0 past bit 31).
+// BL(i): k bits of x starting at bit (i-1)*alpha (0 past bit 31): one bit
+// field extract, of width 0 for a block that starts past bit 31 (the shift
+// and the width are the same in every lane).
 __device__ __forceinline__ uint32_t bit_block(const Geom &G, uint32_t i,
                                               uint32_t x) {
-  return (uint32_t)(((uint64_t)x >> G.shift[i]) & ((1u << G.k) - 1));
+  const uint32_t sh = G.shift[i];
+  return __builtin_amdgcn_ubfe(x, sh, sh < 32 ? G.k : 0u);
 }
 
 // Device-resident state of one restore. Zeroed at the start of each restore
@@ -219,7 +222,54 @@ struct UpdJob {
   uint32_t sample;       // count every sample-th batch of a block (1: all)
   uint32_t rscale;       // region = estimate * rscale / 64 + pad (0: the default
                          // 9/8 of a sampled estimate, or the exact count)
+  // linear and fresh launches (linear.hip): tiles of 160 KiB >> tshift, and
+  // for a linear one its batches, the words reserved per batch and the
+  // directory of run starts ([nbatch][LIN_DIR]); chunk is then in batches
+  uint32_t tshift, nbatch, wcap;
+  uint16_t *dir;
 };
+
+// How an update launch sets its jobs' bits (see update.hip, linear.hip).
+enum UpdPath : uint32_t { UPD_DIRECT, UPD_REGIONS, UPD_LINEAR, UPD_FRESH };
+
+// Job argument of the kernels in linear.hip: a single job by value, or a
+// table of nj in device memory.
+struct JobArg {
+  UpdJob one;
+  const UpdJob *tab;
+  uint32_t nj;
+};
+
+// The linear update keeps at most LIN_TILES tiles per sketch: sketches of up
+// to 40 MiB (LIN_TILES tiles of 160 KiB), smaller ones in smaller tiles, cut
+// in half up to LIN_SHIFT_MAX times. With 256 tiles a batch of 6144 pairs
+// leaves runs of about 40 words (320 bytes), with 1024 it would leave 80
+// bytes, less than a cache line.
+constexpr uint32_t LIN_TILES = 256;
+constexpr uint32_t LIN_SHIFT_MAX = 4;
+constexpr uint32_t LIN_DIR = LIN_TILES + 4;           // directory entries per batch
+
+// Tile cuts of a sketch of `words`: the most that keep it within LIN_TILES.
+inline uint32_t lin_shift(uint64_t words) {
+  uint32_t s = 0;
+  while (s < LIN_SHIFT_MAX && (words << (s + 1)) <= (uint64_t)LIN_TILES * BIN_TILE_WORDS) s++;
+  return s;
+}
+inline uint32_t lin_tiles(uint64_t words, uint32_t shift) {
+  const uint64_t tw = BIN_TILE_WORDS >> shift;
+  return (uint32_t)((words + tw - 1) / tw);
+}
+
+// Workgroups of a linear or fresh tile pass for a job of `tiles` tiles.
+inline uint32_t tile_groups(uint32_t tiles) {
+  return (tiles + BIN_GROUPS - 1) / BIN_GROUPS * BIN_GROUPS;
+}
+
+// Words reserved for one linear batch: its codes, three to a word, and two
+// pad slots per tile; even.
+inline uint32_t lin_batch_words(uint32_t r, uint32_t ppt, uint32_t tiles) {
+  return ((1024 * ppt * r + 2 * tiles + 2) / 3 + 1) & ~1u;
+}
 
 constexpr uint32_t MAX_JOBS = 256;     // jobs per launch group
 
@@ -274,10 +324,22 @@ inline uint32_t job_batches(uint32_t nblk, uint64_t chunk, uint32_t ppt) {
 // host copy (blk0 / tile0 / nblk filled in), `d_jobs` its device copy
 // (already transferred), `d_total` one device word for the item count.
 hipError_t launch_update_jobs(const UpdJob *h_jobs, UpdJob *d_jobs, uint32_t n_jobs,
-                              uint32_t *d_total, bool binned, uint32_t r, uint32_t ppt,
+                              uint32_t *d_total, UpdPath path, uint32_t r, uint32_t ppt,
                               uint32_t apply_grid, hipStream_t st);
+// Whether a launch reads its jobs from the device table.
+inline bool launch_reads_table(UpdPath path, uint32_t n_jobs) {
+  return path == UPD_REGIONS || n_jobs > 1;
+}
 
-// ---- launchers (update.hip) ----
+// ---- launchers (linear.hip) ----
+hipError_t launch_small_update(const UpdJob *h_jobs, const UpdJob *d_jobs, uint32_t n_jobs,
+                               UpdPath path, uint32_t r, uint32_t ppt, uint32_t apply_grid,
+                               hipStream_t st);
+// Once per device (and outside graph capture): lets tiles take more than
+// 64 KiB of LDS.
+hipError_t prepare_update_kernels();
+
+// ---- launchers (ops.hip) ----
 hipError_t launch_fill_u32(uint32_t *p, size_t n_words, uint32_t value,
                            int grid, hipStream_t st);
 hipError_t launch_or_u32(uint32_t *dst, const uint32_t *src, size_t n_words, int grid,

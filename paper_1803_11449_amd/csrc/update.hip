@@ -5,19 +5,11 @@
 // sketch's update is a batch of one. Blocks, tiles and work items are mapped
 // to their job by binary search over the jobs' prefix fields.
 //
-// Two kernels compute the same sketch:
+// Four ways compute the same sketch; update_path (api.hip) chooses. The
+// direct, linear and fresh kernels are in linear.hip; here are the passes of
+// the region update, for sketches of more than LIN_TILES tiles.
 //
-// direct   Alg. 1 as written. Each lane loads one 8-byte pair, hashes it in
-//          registers (two multiply-add-shifts, r-1 shift/xor) and sets one
-//          bit in one LE of each row with a non-returning atomicOr, after a
-//          plain load shows the bit unset (Alg. 1 skips a bit already 1;
-//          that turns the heavy hitters' updates, whose LEs fill early, into
-//          cache reads). Bound by random accesses into the sketch: on MI355X
-//          a random 4-byte access to a 160 MiB buffer runs at ~60 G/s and a
-//          global atomicOr at ~27 G/s, whatever the buffer size. Used for
-//          small updates.
-//
-// binned   The bit sets are moved into LDS. Every (pair, row) gives the bit
+// regions  The bit sets are moved into LDS. Every (pair, row) gives the bit
 //          index B = ((row * 2^k + cell) * g) + bit of the sketch seen as
 //          one bit string; tile = B / 1310720 names the 160 KiB slice it
 //          falls in and code = B mod 1310720 the bit inside it (21 bits).
@@ -52,109 +44,11 @@
 //          tiles move through HBM.
 #include <type_traits>
 
-#include "ddhf_internal.h"
+#include "update_dev.h"
 
 namespace ddhf {
 
-// Pointers read from a job table are generic to the compiler, which then
-// emits flat loads and stores; those count against the LDS wait counter too,
-// so every wait for an LDS result would also wait for all memory traffic in
-// flight. Every job buffer is device global memory: say so.
-#define GMEM __attribute__((address_space(1)))
-template <typename T>
-__device__ __forceinline__ GMEM T *gmem(T *p) {
-  return (GMEM T *)p;
-}
-// HIP's vector structs cannot be copied out of a qualified pointer: 8- and
-// 16-byte accesses go through the compiler's own vector types.
-typedef uint32_t v2u __attribute__((ext_vector_type(2)));
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint2 ld2(const GMEM uint2 *p) {
-  const v2u v = *reinterpret_cast<const GMEM v2u *>(p);
-  return make_uint2(v.x, v.y);
-}
-__device__ __forceinline__ uint4 ld4(const GMEM uint4 *p) {
-  const v4u v = *reinterpret_cast<const GMEM v4u *>(p);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void st4(GMEM uint4 *p, uint4 x) {
-  v4u v;
-  v.x = x.x; v.y = x.y; v.z = x.z; v.w = x.w;
-  *reinterpret_cast<GMEM v4u *>(p) = v;
-}
-
-// ------------------------------------------------------------ job lookup
-
-__device__ __forceinline__ uint32_t job_of_block(const UpdJob *jobs, uint32_t nj, uint32_t b) {
-  uint32_t lo = 0, hi = nj;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (jobs[mid].blk0 <= b) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-__device__ __forceinline__ uint32_t job_of_tile(const UpdJob *jobs, uint32_t nj, uint32_t t) {
-  uint32_t lo = 0, hi = nj;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (jobs[mid].tile0 <= t) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-__device__ __forceinline__ uint32_t job_of_item(const UpdJob *jobs, uint32_t nj, uint32_t it) {
-  uint32_t lo = 0, hi = nj;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (jobs[mid].item0 <= it) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-// ---------------------------------------------------------------- direct
-
-template <int R, bool CHECK>
-__global__ __launch_bounds__(256) void k_update(const UpdJob *__restrict__ jobs, uint32_t nj) {
-  const uint32_t j = job_of_block(jobs, nj, blockIdx.x);
-  const UpdJob &J = jobs[j];
-  const Geom G = J.G;
-  GMEM uint32_t *__restrict__ sk = gmem(J.sk);
-  const GMEM uint2 *__restrict__ pairs = gmem(J.pairs);
-  const size_t n = J.n;
-  const size_t stride = (size_t)J.nblk * blockDim.x;
-  for (size_t i = (size_t)(blockIdx.x - J.blk0) * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const uint2 p = ld2(pairs + i);
-    const uint32_t bit = hash_h1(G, p.y);
-    const uint32_t c0 = hash_dh0(G, p.x);
-    const uint32_t mask = 1u << (bit & 31);
-    const uint32_t wofs = bit >> 5;
-#pragma unroll
-    for (int row = 0; row < R; row++) {
-      const uint32_t cell = row == 0 ? c0 : (bit_block(G, row, p.x) ^ c0);
-      GMEM uint32_t *w = sk + ((size_t)(((uint32_t)row << G.k) | cell) * G.wpl + wofs);
-      if (CHECK && (*w & mask)) continue;
-      atomicOr((uint32_t *)w, mask);    // stays a global atomic after inlining
-    }
-  }
-}
-
 // ---------------------------------------------------------------- binned
-
-constexpr uint32_t CODE_BITS = 21;
-constexpr uint32_t CODE_MASK = (1u << CODE_BITS) - 1;
-
-template <int R>
-__device__ __forceinline__ void pair_codes(const Geom &G, uint2 p, uint32_t *B) {
-  const uint32_t bit = hash_h1(G, p.y);
-  const uint32_t c0 = hash_dh0(G, p.x);
-#pragma unroll
-  for (int row = 0; row < R; row++) {
-    const uint32_t cell = row == 0 ? c0 : (bit_block(G, row, p.x) ^ c0);
-    // sketch bit index; < 2^32 since a binned sketch has at most BIN_MAX tiles
-    B[row] = ((((uint32_t)row << G.k) | cell) << G.log2g) | bit;
-  }
-}
 
 template <int R>
 __device__ __forceinline__ void count_pair(const Geom &G, uint2 p, uint32_t *h) {
@@ -508,15 +402,6 @@ __global__ __launch_bounds__(1024) void k_item_offsets(UpdJob *__restrict__ jobs
 
 constexpr int SCATTER_UNROLL = 4;
 
-// Two 16-bit ranks per register (q is a compile-time index after unrolling).
-__device__ __forceinline__ void put_rank(uint32_t *rk2, int q, uint32_t r) {
-  if (q & 1) rk2[q >> 1] |= r << 16;
-  else rk2[q >> 1] = r;
-}
-__device__ __forceinline__ uint32_t get_rank(const uint32_t *rk2, int q) {
-  return (q & 1) ? rk2[q >> 1] >> 16 : rk2[q >> 1] & 0xFFFFu;
-}
-
 // The value the scatter keeps per bit set. Up to 2048 tiles it is the tile
 // (11 bits) over the code (21 bits), split once per bit set; above, the
 // sketch bit index, whose tile takes a division wherever it is needed
@@ -563,7 +448,6 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
   const UpdJob &J = jobs[job_of_block(jobs, nj, blockIdx.x)];
   const Geom G = J.G;
   const uint32_t lb = blockIdx.x - J.blk0;
-  const GMEM uint2 *__restrict__ pairs = gmem(J.pairs);
   GMEM uint64_t *__restrict__ words = gmem(reinterpret_cast<uint64_t *>(J.codes));
   // this block's group's regions, one per tile: claim cursors and ends (in
   // words from the job's codes)
@@ -576,7 +460,10 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
   const size_t p0 = (size_t)lb * J.chunk;
   const size_t p1 = p0 + J.chunk < J.n ? p0 + J.chunk : J.n;
   if (p0 >= p1) return;                                // uniform over the block
-  const size_t step = (size_t)blockDim.x * PPT;
+  // the chunk's pairs, indexed in 32 bits from its start
+  const GMEM uint2 *__restrict__ pairs = gmem(J.pairs) + p0;
+  const uint32_t n = (uint32_t)(p1 - p0);
+  constexpr uint32_t step = 1024 * PPT;
   // A batch's pairs are held in pr. The next batch's pairs are loaded into
   // pr as soon as this batch's codes are made (step 1), so they are in
   // flight through the claims and the scan (and, with one tile per thread,
@@ -585,18 +472,18 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
   // the chunk re-read its last pair (their lanes are masked later): with no
   // branch around them the compiler need not wait for every load in flight.
   uint2 pr[PPT];
-  auto load = [&](size_t b0, uint32_t tid) {
+  auto load = [&](uint32_t b0, uint32_t tid) {
 #pragma unroll
     for (int k = 0; k < PPT; k++) {
-      const size_t i = b0 + (size_t)k * blockDim.x + tid;
-      pr[k] = ld2(pairs + (i < p1 ? i : p1 - 1));
+      const uint32_t i = b0 + (uint32_t)k * 1024 + tid;
+      pr[k] = ld2(pairs + (i < n ? i : n - 1));
     }
   };
   // One batch: the pairs [i0, i0 + step) of the chunk, held in pr. A full
   // batch (FULL) has all its pairs and takes no per-pair bounds test; only
   // a chunk's last batch can be partial, and its missing pairs get the
   // code ~0.
-  auto batch = [&](auto full_c, size_t i0) {
+  auto batch = [&](auto full_c, uint32_t i0) {
     constexpr bool FULL = decltype(full_c)::value;
     // The thread index is taken afresh per batch, so that addresses derived
     // from it are recomputed here rather than held in registers (or spilled)
@@ -612,8 +499,8 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
     // for the 100M-pair window)
 #pragma unroll
     for (int k = 0; k < PPT; k++) {
-      const size_t i = i0 + (size_t)k * blockDim.x + tid;
-      if (FULL || i < p1) {
+      const uint32_t i = i0 + (uint32_t)k * 1024 + tid;
+      if (FULL || i < n) {
         uint32_t B[R];
         pair_codes<R>(G, pr[k], B);
 #pragma unroll
@@ -659,14 +546,21 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
     __syncthreads();
     // 3: group by tile in LDS; dst maps a batch word to its word slot
 #pragma unroll
-    for (int q = 0; q < PPT * R; q++)
+    for (int q = 0; q < PPT * R; q++) {
       if (FULL || v[q] != ~0u) sorted[lofs[SV::tile(v[q])] + get_rank(rk2, q)] = v[q];
+      // with more tiles per thread the registers do not hold every code's
+      // run start at once
+      if constexpr (TPT > 1)
+        if (q % 10 == 9) __builtin_amdgcn_sched_barrier(0);
+    }
+    tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     // a run that fits its region goes there; one that does not goes whole
     // to the spill area (the run that crosses the region's end marks where
     // the region's written part ends) and joins its tile's spill runs
 #pragma unroll
     for (uint32_t u = 0; u < TPT; u++) {
-      const uint32_t t = t0 + u;
+      const uint32_t t = tid * TPT + u;
       const uint32_t w = (cnt[t] + 2) / 3;
       cnt[t] = 0;                                       // for the next batch
       if (!w) continue;
@@ -703,34 +597,13 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
     for (; j < nw; j += 1024) put(j);
     __syncthreads();
   };
-  load(p0, threadIdx.x);
-  size_t i0 = p0;
-  for (; i0 + step <= p1; i0 += step) batch(std::true_type{}, i0);
-  if (i0 < p1) batch(std::false_type{}, i0);
+  load(0, threadIdx.x);
+  uint32_t i0 = 0;
+  for (; i0 + step <= n; i0 += step) batch(std::true_type{}, i0);
+  if (i0 < n) batch(std::false_type{}, i0);
 }
 
 constexpr int APPLY_UNROLL = 4;
-
-// Zero count of the LE that holds sketch words [w, w+4) (v), when the LE's
-// W = wpl words are spread over W/4 consecutive lanes, each with one 16-byte
-// vector (4 <= W <= 256): the lanes' one-counts are summed across the group
-// and its first lane writes g - ones. Every lane of a group must call it.
-__device__ __forceinline__ void le_zeros(const Geom &G, GMEM uint32_t *lez, size_t w, uint4 v) {
-  const uint32_t L = G.wpl / 4;                         // lanes per LE, 1..64
-  uint32_t ones = __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
-  for (uint32_t m = L >> 1; m >= 1; m >>= 1) ones += __shfl_xor(ones, (int)m, 64);
-  if ((w / 4) % L == 0) lez[w / G.wpl] = G.g - ones;
-}
-
-// The three codes of a word (low half lo, high half hi) into the LDS tile.
-__device__ __forceinline__ void or_word(uint32_t *tile, uint2 w) {
-  const uint32_t a = w.x & CODE_MASK;
-  const uint32_t b = __builtin_amdgcn_alignbit(w.y, w.x, CODE_BITS) & CODE_MASK;
-  const uint32_t c = (w.y >> (2 * CODE_BITS - 32)) & CODE_MASK;
-  atomicOr(&tile[a >> 5], 1u << (a & 31));
-  atomicOr(&tile[b >> 5], 1u << (b & 31));
-  atomicOr(&tile[c >> 5], 1u << (c & 31));
-}
 
 // The code words [c0, c1) of one region or spill run into the LDS tile: a
 // single word up to an even index, uint4 bodies (two words each; whole
@@ -920,17 +793,11 @@ static void launch_front(UpdJob *d, uint32_t nj, uint32_t blocks, uint32_t tiles
 
 template <int R>
 static hipError_t launch_r(const UpdJob *h, UpdJob *d, uint32_t nj, uint32_t *d_total,
-                           bool binned, uint32_t ppt, uint32_t apply_grid, hipStream_t st) {
+                           uint32_t ppt, uint32_t apply_grid, hipStream_t st) {
   uint32_t blocks = 0, tiles = 0;
   for (uint32_t j = 0; j < nj; j++) {
     blocks += h[j].nblk;
     tiles += h[j].nbins;
-  }
-  if (!binned) {
-    bool check = h[0].check != 0;
-    if (check) k_update<R, true><<<blocks, 256, 0, st>>>(d, nj);
-    else k_update<R, false><<<blocks, 256, 0, st>>>(d, nj);
-    return hipGetLastError();
   }
   // LDS of the scatter: 4*(1024*PPT*r + 2*TMAX) bytes of sorted codes +
   // 12*TMAX bytes of tile arrays <= 160 KiB. Up to 2048 tiles: 6 pairs per
@@ -972,16 +839,18 @@ static hipError_t launch_r(const UpdJob *h, UpdJob *d, uint32_t nj, uint32_t *d_
 }
 
 hipError_t launch_update_jobs(const UpdJob *h_jobs, UpdJob *d_jobs, uint32_t n_jobs,
-                              uint32_t *d_total, bool binned, uint32_t r, uint32_t ppt,
+                              uint32_t *d_total, UpdPath path, uint32_t r, uint32_t ppt,
                               uint32_t apply_grid, hipStream_t st) {
   if (n_jobs == 0) return hipSuccess;
+  if (path != UPD_REGIONS)
+    return launch_small_update(h_jobs, d_jobs, n_jobs, path, r, ppt, apply_grid, st);
   switch (r) {
-    case 3: return launch_r<3>(h_jobs, d_jobs, n_jobs, d_total, binned, ppt, apply_grid, st);
-    case 4: return launch_r<4>(h_jobs, d_jobs, n_jobs, d_total, binned, ppt, apply_grid, st);
-    case 5: return launch_r<5>(h_jobs, d_jobs, n_jobs, d_total, binned, ppt, apply_grid, st);
-    case 6: return launch_r<6>(h_jobs, d_jobs, n_jobs, d_total, binned, ppt, apply_grid, st);
-    case 7: return launch_r<7>(h_jobs, d_jobs, n_jobs, d_total, binned, ppt, apply_grid, st);
-    case 8: return launch_r<8>(h_jobs, d_jobs, n_jobs, d_total, binned, ppt, apply_grid, st);
+    case 3: return launch_r<3>(h_jobs, d_jobs, n_jobs, d_total, ppt, apply_grid, st);
+    case 4: return launch_r<4>(h_jobs, d_jobs, n_jobs, d_total, ppt, apply_grid, st);
+    case 5: return launch_r<5>(h_jobs, d_jobs, n_jobs, d_total, ppt, apply_grid, st);
+    case 6: return launch_r<6>(h_jobs, d_jobs, n_jobs, d_total, ppt, apply_grid, st);
+    case 7: return launch_r<7>(h_jobs, d_jobs, n_jobs, d_total, ppt, apply_grid, st);
+    case 8: return launch_r<8>(h_jobs, d_jobs, n_jobs, d_total, ppt, apply_grid, st);
     default: return hipErrorInvalidValue;
   }
 }
