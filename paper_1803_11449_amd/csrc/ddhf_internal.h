@@ -260,6 +260,11 @@ inline uint32_t lin_tiles(uint64_t words, uint32_t shift) {
   return (uint32_t)((words + tw - 1) / tw);
 }
 
+// Linear batches of one or two pairs per thread (up to 4096 pairs per
+// compute unit) take no repeat filter: there is little to repeat in a block.
+constexpr bool lin_filters(uint32_t ppt) { return ppt >= 4; }
+constexpr uint32_t LIN_FILT_WORDS = 8192;
+
 // Workgroups of a linear or fresh tile pass for a job of `tiles` tiles.
 inline uint32_t tile_groups(uint32_t tiles) {
   return (tiles + BIN_GROUPS - 1) / BIN_GROUPS * BIN_GROUPS;

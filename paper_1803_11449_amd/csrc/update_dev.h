@@ -86,6 +86,81 @@ __device__ __forceinline__ void pair_codes(const Geom &G, uint2 p, uint32_t *B) 
   codes_of<R>(G, p.x, pair_code0(G, p), B);
 }
 
+// ------------------------------------------------------------ repeat filter
+
+// A (source, bit) pair that a block has seen before sets only bits that the
+// block's words set already, and under skewed traffic a few sources send
+// most pairs. Each scatter block keeps, in LDS, a bitmap of the bits seen for
+// as many sources as fit in WORDS words: a slot belongs for the whole launch
+// to the first source that comes to it twice in a row (which leaves most
+// slots to the sources with the most pairs), and a pair of a slot's owner
+// whose bit is already set is dropped. Dropping repeats takes out most of
+// the words that pile up on the busiest source's tiles, whose workgroups
+// the apply pass otherwise waits for: 4M pairs at g = 512, r = 4 (Zipf 1.1),
+// apply 73 -> 27 us for 4 us more in the scatter; 15M pairs at k = 16 (Zipf
+// 1.0), 139 -> 79 us for 15 us. A table shared by the blocks of an XCD drops
+// more (15M pairs: apply 66 us) but its busiest lines are read by every
+// wave: the scatter went from 85 to 650 us and more.
+//
+// Slots are claimed in a block's first FILT_CLAIM batches only (in every
+// batch it cost twice as much). The next batch's drops are counted, and a
+// block where fewer than one pair in 32 repeats goes on without the filter.
+constexpr uint32_t FILT_FREE = 0xFFFFFFFFu;             // no source: passes unfiltered
+constexpr uint32_t FILT_CLAIM = 1;
+
+template <uint32_t WORDS>
+struct Filter {
+  static constexpr uint32_t SLOTS = WORDS / 32;         // at most, for LEs of 32 words and less
+  uint32_t bits[WORDS + 64], own[SLOTS], last[SLOTS], drops;
+
+  __device__ __forceinline__ void clear() {
+    for (uint32_t i = threadIdx.x; i < WORDS + 64; i += blockDim.x) bits[i] = 0;
+    for (uint32_t i = threadIdx.x; i < SLOTS; i += blockDim.x) own[i] = last[i] = FILT_FREE;
+    if (threadIdx.x == 0) drops = 0;
+  }
+  // Which of N pairs (sources x, row-0 bit indexes B0) repeat an earlier one:
+  // bit k of the result. live: the pairs that exist. The lookups, and the
+  // test-and-sets, of all N go out together: a lane without an owned slot
+  // sets nothing in a word of its own.
+  template <int N>
+  __device__ __forceinline__ uint32_t repeats(const Geom &G, const uint32_t *x,
+                                              const uint32_t *B0, uint32_t live,
+                                              uint32_t batch) {
+    const uint32_t mask = (G.wpl <= 32 ? SLOTS : WORDS / G.wpl) - 1;   // WORDS >= 2048, the largest LE
+    uint32_t o[N], seen = 0;
+#pragma unroll
+    for (int k = 0; k < N; k++) o[k] = own[(B0[k] >> G.log2g) & mask];
+    if (batch < FILT_CLAIM) {                           // uniform over the block
+#pragma unroll
+      for (int k = 0; k < N; k++) {
+        const uint32_t slot = (B0[k] >> G.log2g) & mask;
+        if (((live >> k) & 1u) && x[k] != FILT_FREE && o[k] == FILT_FREE) {
+          if (last[slot] == x[k]) {
+            const uint32_t old = atomicCAS(&own[slot], FILT_FREE, x[k]);
+            o[k] = old == FILT_FREE ? x[k] : old;
+          } else {
+            last[slot] = x[k];
+          }
+        }
+      }
+    }
+    uint32_t old[N], m[N];
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+      const uint32_t slot = (B0[k] >> G.log2g) & mask, bit = B0[k] & (G.g - 1);
+      const bool mine = o[k] == x[k] && x[k] != FILT_FREE && ((live >> k) & 1u);
+      m[k] = mine ? 1u << (bit & 31) : 0u;
+      old[k] = atomicOr(&bits[mine ? slot * G.wpl + (bit >> 5) : WORDS + (threadIdx.x & 63)], m[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < N; k++) seen |= (old[k] & m[k]) ? 1u << k : 0u;
+    if (batch == FILT_CLAIM) atomicAdd(&drops, (uint32_t)__popc(seen));
+    return seen;
+  }
+  // After a barrier that follows batch FILT_CLAIM: whether to go on.
+  __device__ __forceinline__ bool useful(uint32_t pairs) const { return drops * 32 >= pairs; }
+};
+
 // Two 16-bit ranks per register (q is a compile-time index after unrolling).
 __device__ __forceinline__ void put_rank(uint32_t *rk2, int q, uint32_t r) {
   if (q & 1) rk2[q >> 1] |= r << 16;
