@@ -660,6 +660,14 @@ struct sketch {
   // between its launch and its check when restores are batched)
   size_t ran_seg_cap = 0, ran_cand_cap = 0, ran_spl_cap = 0, ran_h_recs_cap = 0;
   int ran_pool = 0;             // the pool that restore ran on
+  // what the last restore found, for what the next one at that threshold
+  // launches (RestoreBufs::expect, sort_one): the search that ran, the
+  // records, and the thresholds' exp(-theta / g) they belong to
+  uint32_t hint_search = 0;
+  uint64_t hint_n = ~0ull;
+  double hint_e = -1.0, ran_e = -1.0;
+  bool ran_sort_one = false;
+  uint2 *chunks = nullptr;      // hot scan chunks (scan_chunks)
   uint64_t cost_hint = 0;       // the last restore's row-0 cells times their addresses
   uint64_t join_hint = 0;       // the last restore's join wave items of stage 1 (0: none yet)
 };
@@ -687,6 +695,7 @@ void free_sketch(sketch *s) {
   dev_free(s->lez);
   dev_free(s->st);
   dev_free(s->hotmask);
+  dev_free(s->chunks);
   dev_free(s->he);
   dev_free(s->bk_off);
   dev_free(s->bk_cur);
@@ -708,10 +717,31 @@ int grow_sorted(sketch *s, size_t need) {
   return rc;
 }
 
-RestoreBufs restore_bufs(const sketch *s, const RPool &p) {
-  const DevCtx *c = s->ctx;
+// Lists that fit the one-launch sort with room to grow from window to window.
+constexpr uint64_t SORT_ONE_HINT = RESTORE_SORT_ONE - RESTORE_SORT_ONE / 4;
+
+// Blocks of the join kernels; fewer than the device's jblk use the first of
+// the pool's segments. Unset, the join takes four blocks per compute unit (a
+// walk two, the most that its LDS leaves), or one when the sketch's last
+// restore had fewer stage-1 wave items than compute units: short hot lists
+// leave most of a larger grid idle, and each block still loads its bucket
+// tables.
+uint32_t join_grid(const sketch *s, bool walk) {
+  const uint32_t most = s->ctx->jblk, n_cu = most / 4;
+  if (s->join_blocks) return std::min(s->join_blocks, most);
+  if (s->join_hint && s->join_hint < n_cu) return n_cu;
+  return walk ? 2 * n_cu : most;
+}
+
+RestoreBufs restore_bufs(const sketch *s, const RPool &p, const Thresholds &t) {
   RestoreBufs B{};
-  B.lez = s->lez_valid ? s->lez : nullptr;
+  B.lez = s->lez;
+  B.lez_stale = !s->lez_valid;
+  B.chunks = s->chunks;
+  if (s->hint_e == t.e_theta) {
+    B.expect = s->cand_path == 0 ? s->hint_search : 0;
+    B.sort_one = s->hint_n <= SORT_ONE_HINT;
+  }
   B.st = s->st;
   B.hotmask = s->hotmask;
   B.he = s->he;
@@ -723,15 +753,8 @@ RestoreBufs restore_bufs(const sketch *s, const RPool &p) {
   B.segc[0] = p.segc[0];
   B.segc[1] = p.segc[1];
   B.seg_cap = p.seg_cap;
-  // fewer join blocks use the first of the pool's segments. Unset, the
-  // join takes four blocks per compute unit, or one when the sketch's last
-  // restore had fewer stage-1 wave items than compute units: short hot
-  // lists leave most of a larger grid idle, and each block still loads its
-  // bucket table
-  const uint32_t n_cu = c->jblk / 4;
-  B.jblk = s->join_blocks ? std::min(s->join_blocks, c->jblk)
-           : (s->join_hint && s->join_hint < n_cu) ? n_cu
-                                                    : c->jblk;
+  B.walk = join_walks(s->G);
+  B.jblk = join_grid(s, B.walk);
   B.cand = p.cand;
   B.cand_sorted = p.cand_sorted;
   B.cand_cap = p.cand_cap;
@@ -808,9 +831,6 @@ int materialize(sketch *s, hipStream_t st) {
 
 // Enqueue the restore kernels on buffers B, whose shared part is ordered by
 // `pool`, and the copy of the device state (no wait). Caller holds ctx->mu.
-
-// Enqueue the restore kernels on buffers B, whose shared part is ordered by
-// `pool`, and the copy of the device state (no wait). Caller holds ctx->mu.
 int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresholds &t,
                       int estimate, hipStream_t st) {
   int rc = lane_enter(s->lane, st);
@@ -819,9 +839,11 @@ int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresho
   if (rc) return rc;
   HIP_OK(launch_restore(s->G, s->d_sketch, B, t.zhot, t.e_theta, estimate, s->grid, st,
                         s->timing ? s->tev : nullptr));
+  s->ran_e = t.e_theta;
+  s->ran_sort_one = B.sort_one;
   if (s->timing) {
     s->timed = true;
-    s->timed_lez = B.lez != nullptr;
+    s->timed_lez = B.lez && !B.lez_stale;
   }
   rc = lane_leave(pool, st);
   if (!rc) rc = lane_leave(s->lane, st);
@@ -831,7 +853,7 @@ int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresho
 // The restore on restore pool i, enqueued on st.
 int restore_launch_pool(sketch *s, const Thresholds &t, int estimate, int i, hipStream_t st) {
   RPool &p = s->ctx->pool[i];
-  const RestoreBufs B = restore_bufs(s, p);
+  const RestoreBufs B = restore_bufs(s, p, t);
   s->ran_seg_cap = B.seg_cap;
   s->ran_cand_cap = B.cand_cap;
   s->ran_spl_cap = B.spl_cap;
@@ -851,8 +873,12 @@ double restore_cost(const sketch *s) {
   return (double)((size_t)s->p.r << s->p.k) / 4.0 + (double)s->cost_hint;
 }
 
-void note_cost(sketch *s, const DevState &h) {
-  if (h.saturated) return;
+// What a finished restore found (e: its threshold's exp(-theta / g)).
+void note_cost(sketch *s, const DevState &h, double e) {
+  if (h.saturated || h.search == 0) return;
+  s->hint_search = h.search;
+  s->hint_n = h.n_spl;
+  s->hint_e = e;
   s->cost_hint = (uint64_t)h.he_count[0] << (32 - s->p.k);
   s->join_hint = std::max<uint64_t>(1, (uint64_t)h.he_count[0] * ((h.he_count[1] + 63) / 64));
 }
@@ -917,8 +943,14 @@ hipError_t batch_join(DevCtx *c, const uint8_t *used, hipStream_t st) {
 // The restore's shared buffers carved from the no-alloc array at `base`:
 // sort ranks, segment counts, candidates and records (each with its sorted
 // copy) at fixed sizes, the rest split into the join's partial segments.
-RestoreBufs noalloc_bufs(const sketch *s, uint8_t *base) {
-  RestoreBufs B = restore_bufs(s, s->ctx->pool[0]);   // every pool buffer replaced below
+RestoreBufs noalloc_bufs(const sketch *s, uint8_t *base, const Thresholds &t) {
+  RestoreBufs B = restore_bufs(s, s->ctx->pool[0], t);   // every pool buffer replaced below
+  // a sketch set to the join keeps its stages here, which refuse partial
+  // addresses beyond the array
+  if (s->cand_path == 1) {
+    B.walk = 0;
+    B.jblk = join_grid(s, false);
+  }
   const uint32_t jb = s->ctx->jblk;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -950,7 +982,13 @@ int restore_check(sketch *s, int estimate, bool *again) {
   RPool &p = c->pool[s->ran_pool];
   *again = false;
   if (h.saturated) return SKETCH_E_SATURATED;
-  note_cost(s, h);
+  if (h.search == 0) {                  // the other search's turn
+    s->hint_e = -1.0;
+    *again = true;
+    return SKETCH_OK;
+  }
+  note_cost(s, h, s->ran_e);
+  if (estimate && s->ran_sort_one && h.n_spl > RESTORE_SORT_ONE) *again = true;
   // a stage overflowed if its count passed the capacity the run had; the
   // buffer grows only if it has not grown enough since
   size_t need_part = 0;
@@ -1453,6 +1491,8 @@ struct PlanJob {
   size_t ran_seg_cap = 0, ran_cand_cap = 0;   // pool capacities of the capture
   int pool = 0;                 // restore pool of the captured restore
   bool eager = false;           // this result comes from an eager rerun
+  bool ran_sort_one = false;    // what the captured restore launches
+  uint32_t ran_expect = 0;
   bool fresh = false;           // RESET plan: the first binned round writes every
                                 // tile from zeros, so no zero fill
 };
@@ -1478,6 +1518,7 @@ struct sketch_plan {
   bool dirty = true;            // a plan-owned buffer changed since the capture
   uint64_t gen = ~0ull;         // device context generation at the capture
   bool ran = false;             // the graph has run at least once
+  bool trimmed = false;         // captured (or about to be) for what the first run showed
   hipStream_t run_stream = nullptr;
 };
 
@@ -1527,10 +1568,10 @@ int plan_alloc_sorted(PlanJob &j, size_t cap) {
 
 RestoreBufs plan_restore_bufs(const sketch_plan *P, const PlanJob &j) {
   const RPool &pool = P->ctx->pool[j.pool];
-  RestoreBufs B = restore_bufs(j.s, pool);    // the sketch's rows, the job's pool
+  RestoreBufs B = restore_bufs(j.s, pool, j.t);    // the sketch's rows, the job's pool
   // the zero counts are known valid at capture only when each run starts
   // the window and its update writes every tile
-  B.lez = (P->flags & SKETCH_PLAN_RESET) && j.fresh ? j.s->lez : nullptr;
+  B.lez_stale = !((P->flags & SKETCH_PLAN_RESET) && j.fresh);
   B.st = j.st;
   B.spl_sorted = j.sorted;
   B.spl_cap = std::min(pool.spl_cap, j.sorted_cap);
@@ -1605,6 +1646,9 @@ int plan_build_graph(sketch_plan *P) {
     j.ran_cand_cap = pool.cand_cap;
     j.ran_spl_cap = std::min(pool.spl_cap, j.sorted_cap);
     j.ran_h_recs_cap = j.h_recs_cap;
+    const RestoreBufs B = plan_restore_bufs(P, j);
+    j.ran_sort_one = B.sort_one;
+    j.ran_expect = B.expect;
   }
   P->gen = c->gen;
   P->dirty = false;
@@ -1686,6 +1730,7 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   if (!rc) rc = dev_alloc(&s->d_sketch, s->words, "sketch");
   if (!rc) rc = dev_alloc(&s->st, 1, "state");
   if (!rc) rc = dev_alloc(&s->hotmask, n_le / 32, "hot bitmap");
+  if (!rc) rc = dev_alloc(&s->chunks, scan_chunks(params->r, params->k), "hot scan chunks");
   if (!rc) rc = dev_alloc(&s->he, n_le, "hot lists");
   if (!rc) rc = dev_alloc(&s->bk_off, (size_t)params->r * (nb + 1), "bucket offsets");
   if (!rc) rc = dev_alloc(&s->bk_cur, (size_t)params->r * nb, "bucket cursors");
@@ -1809,20 +1854,32 @@ int sketch_restore_noalloc(sketch_t *s, double theta, sketch_sp_t *out, size_t c
   std::lock_guard<std::mutex> lk(c->mu);
   if (!c->noalloc) return fail(SKETCH_E_HIP, "sketch_restore_noalloc: no work array on device");
   const Thresholds t = thresholds(s, theta);
-  RestoreBufs B = noalloc_bufs(s, c->noalloc);
+  RestoreBufs B = noalloc_bufs(s, c->noalloc, t);
   // a join whose partial addresses outgrow the array gives way to the
-  // lattice search, which makes none (both give the same candidates)
-  for (int attempt = 0; attempt < 2; attempt++) {
+  // lattice search, which makes none (both give the same candidates). A
+  // search or a sort that was expected and not the right one: again with
+  // every kernel
+  for (;;) {
     int rc = restore_launch_on(s, B, c->noalloc_lane, t, 1, st);
     if (rc) return rc;
     HIP_OK(hipStreamSynchronize(st));
     const DevState &h = *s->h_state;
     if (h.saturated) break;
+    if (B.expect && h.search == 0) {
+      B.expect = 0;
+      continue;
+    }
+    note_cost(s, h, t.e_theta);
+    if (B.sort_one && h.n_spl > RESTORE_SORT_ONE) {
+      B.sort_one = 0;
+      continue;
+    }
     uint32_t seg = 0;
     for (uint32_t i = 2; i + 1 < s->p.r; i++) seg = std::max(seg, h.seg_max[i]);
     if (seg <= B.seg_cap) break;
-    if (attempt == 0 && s->lat.ok && B.cand_path != 1) {
+    if (B.cand_path == 0 && s->lat.ok) {
       B.cand_path = 2;
+      B.expect = 0;
       continue;
     }
     return fail(SKETCH_E_CAPACITY, "sketch_restore_noalloc: a join block's %u partial "
@@ -2337,7 +2394,10 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
     const uint4 *src = pj.sorted;
     int rc = SKETCH_OK;
     pj.eager = false;
-    note_cost(s, *h);
+    note_cost(s, *h, pj.t.e_theta);
+    // the captured restore left out what this window needs (see restore_check)
+    const bool other = !h->saturated && h->search == 0;
+    const bool partial = other || (pj.ran_sort_one && h->n_spl > RESTORE_SORT_ONE);
     if (h->saturated) {
       rc = SKETCH_E_SATURATED;
     } else {
@@ -2347,8 +2407,15 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
       // a stage overflowed if its count passed the capacity the graph ran
       // with; the shared buffers grow as for an eager restore (which moves
       // them, so the next run captures again) and this job runs again alone
-      if (need_part > pj.ran_seg_cap || h->n_cand > pj.ran_cand_cap ||
-          h->n_spl > pj.ran_spl_cap) {
+      if (partial) {
+        if (other) s->hint_e = -1.0;
+        P->dirty = true;                // captured again with what it needs
+        rc = run_restore(s, pj.t, 1, st);
+        h = s->h_state;
+        src = s->spl_sorted;
+        pj.eager = true;
+      } else if (need_part > pj.ran_seg_cap || h->n_cand > pj.ran_cand_cap ||
+                 h->n_spl > pj.ran_spl_cap) {
         if (h->n_spl > pj.sorted_cap) {
           rc = plan_alloc_sorted(pj, grown(h->n_spl, pj.sorted_cap));
           P->dirty = true;
@@ -2393,6 +2460,15 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
     if (rc && !first_err) first_err = rc;
   }
   HIP_OK(hipStreamSynchronize(st));
+  // captured once more now that the first run has shown each job's search and
+  // list size, so that the graph holds only the kernels they need
+  if (!P->trimmed) {
+    P->trimmed = true;
+    for (const PlanJob &pj : P->jobs) {
+      const RestoreBufs B = plan_restore_bufs(P, pj);
+      if (B.expect != pj.ran_expect || (bool)B.sort_one != pj.ran_sort_one) P->dirty = true;
+    }
+  }
   if (first_err)
     return fail(first_err, "sketch_plan_results: a job failed (see each job's status)");
   return SKETCH_OK;

@@ -75,8 +75,10 @@ struct Lattice {
 
 // Restore work buffers (device pointers) and capacities.
 struct RestoreBufs {
-  const uint32_t *lez;    // zeros per LE as the update left them, or null
-                          // (the hot scan counts them in the sketch)
+  uint32_t *lez;          // zeros per LE, or null (LEs whose counts are not
+                          // kept: the hot scan counts them in the sketch)
+  uint32_t lez_stale;     // the counts are not the sketch's: count them first
+  uint2 *chunks;          // hot LEs and zeros of each chunk of the hot scan
   DevState *st;
   uint32_t *hotmask;      // r * 2^k bits
   uint32_t *he;           // r * 2^k entries, row i at i*2^k, ascending
@@ -107,7 +109,20 @@ struct RestoreBufs {
   // (0 = by estimated work, 1 = the join of Algs. 3-4, 2 = the lattice)
   Lattice lat;
   uint32_t cand_path;
+  // what to launch, by the sketch's last restore: only the search that ran
+  // then (0 = both, 1 = the join, 2 = the lattice), and the one-launch sort.
+  // A restore whose counts then call for the other search, or whose list is
+  // longer, leaves that to see in the state (search 0, n_spl) and is run again
+  uint32_t expect;
+  uint32_t sort_one;
+  uint32_t walk;          // the join as one walk (join_walks)
 };
+constexpr uint32_t RESTORE_SORT_ONE = 2048;           // records of the one-launch sort, at most
+// Whether the join of a sketch can run as one walk (r >= 4).
+constexpr uint32_t JOIN_WALK_BITS = 10;               // log2 of the buckets per row, at most
+inline bool join_walks(const Geom &G) { return G.r >= 4 && G.k - G.alpha <= JOIN_WALK_BITS; }
+// Chunks of the hot scan of larger sketches (RestoreBufs::chunks).
+inline size_t scan_chunks(uint32_t r, uint32_t k) { return ((size_t)r << k) / 4096 + 1; }
 
 // Inclusive prefix sum over the 64 lanes of a wave, in registers: four
 // row shifts inside each 16-lane row, then the row broadcasts of lanes 15

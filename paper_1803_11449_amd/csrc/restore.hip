@@ -1,18 +1,23 @@
 // Window-end restore (Alg. 2, Sec. 3.3, laid out as in Sec. 4.2).
 //
-//  1 hot scan      one read of the whole sketch: z0 = g - popcount of every
-//                  LE, ZR(i) per row, and a bitmap of hot LEs (z0 <= zhot,
-//                  i.e. z0 < Zmin = g*exp(-theta/g)). HBM-bound.
-//  2 HE compaction one workgroup per row turns the hot bitmap into HE(i),
-//                  ascending, by a block prefix sum.
+//  1 hot scan      z0 of every LE, from the zero counts the update kept or
+//                  counted here in one read of the sketch; ZR(i) per row,
+//                  and a bitmap of hot LEs (z0 <= zhot, i.e. z0 < Zmin =
+//                  g*exp(-theta/g)).
+//  2 HE compaction the hot bitmap into HE(i), ascending, by a block prefix
+//                  sum.
 //  3 buckets       rows >= 2: HE(i) grouped by its low k-alpha bits, so a
 //                  join probe finds exactly the entries whose overlap bits
 //                  match instead of testing all of HE(i) (Algs. 3-4 test
 //                  every tuple; the bucketed probe enumerates the same
 //                  accepted tuples and skips only failing ones).
+//                  Small sketches take 1-3 in one launch, one block per row
+//                  (k_scan_rows); larger ones in chunks spread over the chip
+//                  (k_hot_scan_lez, k_compact, and k_buckets for the join).
 //  4 scalars       psi (Lemma 1 with the flow-count estimate of Sec. 3.3),
 //                  D = g(1 - psi^r) (eq. (4)), T_rep = D*exp(-theta/g) and
-//                  the integer report bound floor(T_rep), in float64.
+//                  the integer report bound floor(T_rep), in float64, by one
+//                  thread of the search's first block.
 //  5 candidates   the addresses whose r LEs are all hot, by one of two
 //                  searches, chosen on the device from the hot-list sizes
 //                  by their estimated work:
@@ -31,7 +36,17 @@
 //  6 estimate      per candidate, AND of its r LEs (ULE), SZ = g - popcount,
 //                  report iff SZ <= floor(T_rep) (<=> C >= theta),
 //                  C = -g*ln(SZ/D) (eq. (4)), +inf when SZ = 0.
-//  7 sort          reported records ascending by address.
+//  7 sort          reported records ascending by address, and the state and
+//                  the records to pinned host memory: one launch for a short
+//                  list.
+//
+// A restore is a chain of short kernels, and for a small sketch their number
+// sets its time. Where the sketch's last restore at the same threshold says
+// what this one needs, only that is launched (RestoreBufs::expect, sort_one).
+// With the walk, the one-launch scan and sort, the 1M-pair window's restore
+// went from 11 launches (47 us of kernels) to 4, and the whole window from
+// 125 to 103 us; a 60,000-pair window with a few hundred hot LEs per row
+// from 137 to 77 us.
 #include <math.h>
 
 #include "ddhf_internal.h"
@@ -98,10 +113,9 @@ __device__ __forceinline__ LDSP T *lds_ptr(T *p) {
 
 // ----------------------------------------------------------- 0: state init
 
-// The device state, the sort ranks and the hot bitmap back to zero, in one
-// launch.
-__global__ __launch_bounds__(256) void k_restore_init(DevState *st, uint32_t *rank,
-                                                      uint32_t n_rank, uint32_t *hotmask,
+// The device state and the hot bitmap back to zero, in one launch (before
+// k_hot_scan, which adds to both).
+__global__ __launch_bounds__(256) void k_restore_init(DevState *st, uint32_t *hotmask,
                                                       size_t n_hm) {
   const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -109,7 +123,6 @@ __global__ __launch_bounds__(256) void k_restore_init(DevState *st, uint32_t *ra
     uint32_t *p = reinterpret_cast<uint32_t *>(st);
     for (uint32_t i = threadIdx.x; i < sizeof(DevState) / 4; i += blockDim.x) p[i] = 0;
   }
-  for (size_t i = i0; i < n_rank; i += stride) rank[i] = 0;
   for (size_t i = i0; i < n_hm; i += stride) hotmask[i] = 0;
 }
 
@@ -186,68 +199,149 @@ __global__ __launch_bounds__(256) void k_hot_scan(Geom G, const uint32_t *__rest
     atomicAdd(&st->zr[threadIdx.x], zr_sh[threadIdx.x]);
 }
 
-// The same from the zero counts the binned update kept (one word per LE, 4
-// bytes instead of g/8 per LE read). A lane takes 4 consecutive LEs with
-// one 16-byte load; 8 lanes make one word of the hot bitmap (their nibbles
-// ORed across the group), so every word is written once, with no atomics.
-// Rows start at multiples of 2^k >= 32 LEs, so a lane's 4 LEs share a row.
-constexpr int HS_LEZ_UNROLL = 4;
+// Zero counts of every LE from the sketch, where the update left none: the
+// scans below then read them (4 <= WPL <= 256; other LEs take k_hot_scan).
+// One read of the sketch at the HBM's rate; no atomics.
+template <int WPL>
+__global__ __launch_bounds__(256) void k_zero_counts(Geom G, const uint4 *__restrict__ sk4,
+                                                     uint32_t *__restrict__ lez) {
+  constexpr int L = WPL / 4;                            // lanes per LE
+  constexpr int U = 4;
+  const uint64_t n4 = ((uint64_t)G.r << G.k) * L;       // a multiple of 32
+  const uint64_t stride = (uint64_t)gridDim.x * 256;
+  for (uint64_t q0 = (uint64_t)blockIdx.x * 256 + threadIdx.x; q0 < n4; q0 += stride * U) {
+    uint32_t ones[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const uint64_t q = q0 + u * stride;
+      const uint4 v = sk4[q < n4 ? q : q0];
+      ones[u] = __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const uint64_t q = q0 + u * stride;
+#pragma unroll
+      for (int m = L / 2; m >= 1; m >>= 1) ones[u] += __shfl_xor(ones[u], m, 64);
+      if (q < n4 && q % L == 0) lez[q / L] = G.g - ones[u];
+    }
+  }
+}
+
+// The restore's state as every restore starts it, but for the ZR(i) and
+// |HE(i)| of the sketch's rows, which other blocks of the same launch write.
+__device__ __forceinline__ void state_begin(const Geom &G, DevState *st) {
+  const uint32_t i = threadIdx.x;
+  if (i < 8) {
+    st->n_out[i] = 0;
+    st->seg_max[i] = 0;
+    if (i >= G.r) {
+      st->zr[i] = 0;
+      st->he_count[i] = 0;
+    }
+  }
+  if (i == 0) {
+    st->n_cand = st->n_spl = 0;
+    st->psi = st->d = st->trep = 0.0;
+    st->szmax = st->saturated = st->search = st->pad = 0;
+  }
+}
+
+// A lane's four LEs (zero counts z) as hot bits in bits 4 (lane mod 8) of the
+// word that 8 lanes share: every lane of the 8 gets the word.
+__device__ __forceinline__ uint32_t hot_word(uint4 z, uint32_t zhot, uint32_t lane) {
+  uint32_t nib = (z.x <= zhot ? 1u : 0u) | (z.y <= zhot ? 2u : 0u) | (z.z <= zhot ? 4u : 0u) |
+                 (z.w <= zhot ? 8u : 0u);
+  nib <<= 4 * (lane & 7);
+  nib |= __shfl_xor(nib, 1, 64);
+  nib |= __shfl_xor(nib, 2, 64);
+  nib |= __shfl_xor(nib, 4, 64);
+  return nib;
+}
+
+// Hot scan of larger sketches, from the zero counts (4 bytes per LE). One
+// block per SCAN_CHUNK LEs of a row: its words of the hot bitmap, its hot
+// LEs' count and its zeros (k_compact adds them up: no atomics, so nothing
+// has to be cleared first).
+constexpr uint32_t SCAN_CHUNK = 4096;
 
 __global__ __launch_bounds__(256) void k_hot_scan_lez(Geom G, const uint4 *__restrict__ lez4,
-                                                      uint32_t zhot,
-                                                      uint32_t *__restrict__ hotmask,
-                                                      DevState *__restrict__ st) {
-  __shared__ unsigned long long zr_sh[8];
-  if (threadIdx.x < 8) zr_sh[threadIdx.x] = 0;
-  __syncthreads();
-  const uint64_t n_q = ((uint64_t)G.r << G.k) / 4;      // n_le is a multiple of 32
-  const uint32_t lane = threadIdx.x & 63;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  uint32_t cur_row = 0;
-  unsigned long long acc = 0;
-  // HS_LEZ_UNROLL loads per lane are issued before any is used; n_q is a
-  // multiple of 8, so a group of 8 lanes is whole or absent
-  for (uint64_t q0 = (uint64_t)blockIdx.x * blockDim.x * HS_LEZ_UNROLL + threadIdx.x; q0 < n_q;
-       q0 += stride * HS_LEZ_UNROLL) {
-    uint4 z[HS_LEZ_UNROLL];
+                                              uint32_t zhot, uint32_t *__restrict__ hotmask,
+                                              uint2 *__restrict__ chunks) {
+  __shared__ uint32_t sh_hot[4], sh_z[4];
+  constexpr int U = SCAN_CHUNK / 4 / 256;
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const size_t q0 = (size_t)blockIdx.x * (SCAN_CHUNK / 4) + threadIdx.x;
+  uint4 z[U];
 #pragma unroll
-    for (int u = 0; u < HS_LEZ_UNROLL; u++) {
-      const uint64_t q = q0 + (uint64_t)u * blockDim.x;
-      z[u] = q < n_q ? lez4[q] : make_uint4(0, 0, 0, 0);
-    }
+  for (int u = 0; u < U; u++) z[u] = lez4[q0 + u * 256];
+  uint32_t hot = 0, zeros = 0;                          // zeros of a chunk: at most 2^25
 #pragma unroll
-    for (int u = 0; u < HS_LEZ_UNROLL; u++) {
-      const uint64_t q = q0 + (uint64_t)u * blockDim.x;
-      if (q >= n_q) break;
-      uint32_t nib = (z[u].x <= zhot ? 1u : 0u) | (z[u].y <= zhot ? 2u : 0u) |
-                     (z[u].z <= zhot ? 4u : 0u) | (z[u].w <= zhot ? 8u : 0u);
-      nib <<= 4 * (lane & 7);
-      nib |= __shfl_xor(nib, 1, 64);
-      nib |= __shfl_xor(nib, 2, 64);
-      nib |= __shfl_xor(nib, 4, 64);
-      if ((lane & 7) == 0) hotmask[q >> 3] = nib;
-      const uint32_t row = (uint32_t)((q * 4) >> G.k);
-      if (row != cur_row) {
-        if (acc) atomicAdd(&zr_sh[cur_row], acc);
-        acc = 0;
-        cur_row = row;
-      }
-      acc += (unsigned long long)z[u].x + z[u].y + z[u].z + z[u].w;
+  for (int u = 0; u < U; u++) {
+    const uint32_t w = hot_word(z[u], zhot, lane);
+    if ((lane & 7) == 0) {
+      hotmask[(q0 + u * 256) >> 3] = w;
+      hot += __popc(w);
     }
+    zeros += z[u].x + z[u].y + z[u].z + z[u].w;
   }
-  // a lane's sum is below 2^22 (at most 2 passes of HS_LEZ_UNROLL x 4 LEs of
-  // <= 2^16 zeros), a wave's below 2^28: a wave whose lanes share a row
-  // folds its sum in registers and adds it once
-  const uint32_t row0 = __builtin_amdgcn_readfirstlane(cur_row);
-  if (__all(cur_row == row0)) {
-    const uint32_t tot = wave_scan_incl((uint32_t)acc);
-    if (lane == 63 && tot) atomicAdd(&zr_sh[row0], (unsigned long long)tot);
-  } else if (acc) {
-    atomicAdd(&zr_sh[cur_row], acc);
+  hot = wave_incl_scan(hot);
+  zeros = wave_incl_scan(zeros);
+  if (lane == 63) {
+    sh_hot[wid] = hot;
+    sh_z[wid] = zeros;
   }
   __syncthreads();
-  if (threadIdx.x < G.r && zr_sh[threadIdx.x])
-    atomicAdd(&st->zr[threadIdx.x], zr_sh[threadIdx.x]);
+  if (threadIdx.x == 0)
+    chunks[blockIdx.x] = make_uint2(sh_hot[0] + sh_hot[1] + sh_hot[2] + sh_hot[3],
+                                    sh_z[0] + sh_z[1] + sh_z[2] + sh_z[3]);
+}
+
+// HE(i) of larger sketches, one block per chunk: it starts where the row's
+// chunks before it end. One block per row did this in 18 us at k = 18 and 85
+// at k = 19, with the rest of the chip idle. A row's first block sums ZR(i).
+__global__ __launch_bounds__(256) void k_compact(Geom G, const uint32_t *__restrict__ hotmask,
+                                                 const uint2 *__restrict__ chunks,
+                                                 uint32_t *__restrict__ he,
+                                                 DevState *__restrict__ st) {
+  __shared__ unsigned long long sh_z[4];
+  __shared__ uint32_t sh_before[4], sh[4];
+  const uint32_t per_row = (1u << G.k) / SCAN_CHUNK;
+  const uint32_t row = blockIdx.x / per_row, c = blockIdx.x % per_row;
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (blockIdx.x == 0) state_begin(G, st);
+  uint32_t before = 0;
+  unsigned long long z = 0;
+  const uint32_t upto = c == 0 ? per_row : c;
+  for (uint32_t i = threadIdx.x; i < upto; i += 256) {
+    const uint2 v = chunks[row * per_row + i];
+    if (i < c) before += v.x;
+    z += v.y;
+  }
+  before = wave_incl_scan(before);
+  if (c == 0) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) z += __shfl_xor(z, m, 64);
+  }
+  if (lane == 63) {
+    sh_before[wid] = before;
+    sh_z[wid] = z;
+  }
+  constexpr uint32_t NW = SCAN_CHUNK / 32;              // words of the chunk: 128
+  const uint32_t w0 = blockIdx.x * NW;
+  uint32_t m = threadIdx.x < NW ? hotmask[w0 + threadIdx.x] : 0u;
+  uint32_t total;
+  const uint32_t ex = block_excl_scan<256>(__popc(m), &total, sh);   // holds barriers
+  const uint32_t off = sh_before[0] + sh_before[1] + sh_before[2] + sh_before[3];
+  uint32_t *out = he + ((size_t)row << G.k) + off + ex;
+  while (m) {
+    const uint32_t b = __ffs(m) - 1;
+    *out++ = ((c * NW + threadIdx.x) << 5) | b;
+    m &= m - 1;
+  }
+  if (threadIdx.x == 0) {
+    if (c + 1 == per_row) st->he_count[row] = off + total;
+    if (c == 0) st->zr[row] = sh_z[0] + sh_z[1] + sh_z[2] + sh_z[3];
+  }
 }
 
 // ---------------------------------------------------------- 2: HE compaction
@@ -393,30 +487,116 @@ __device__ __forceinline__ void scalars(const Geom &G, DevState *st, double e_th
   st->szmax = (uint32_t)floor(trep);
 }
 
-// One block per row i: HE(i) from the hot bitmap (step 2), its bucket table
-// when i >= 2 and the join may run (step 3), and in row 0's block the
-// scalars (step 4), which need only the ZR(i) of the hot scan.
+// The bucket table of one row from its hot list (step 3).
+__device__ __forceinline__ void row_buckets(const Geom &G, uint32_t row, const uint32_t *he,
+                                            uint32_t n, uint32_t *bk_off, uint32_t *bk_cur,
+                                            uint32_t *bk_val, uint32_t *lcur, uint32_t *sh) {
+  const uint32_t nb = 1u << (G.k - G.alpha);
+  uint32_t *off = bk_off + (size_t)row * (nb + 1);
+  const uint32_t *h = he + ((size_t)row << G.k);
+  uint32_t *val = bk_val + ((size_t)row << G.k);
+  if (nb <= BK_LDS) bucket_rows(G, row, h, n, off, lds_ptr(lcur), val, sh);
+  else bucket_rows(G, row, h, n, off, bk_cur + (size_t)row * nb, val, sh);
+}
+
+// One block per row i: HE(i) from the hot bitmap of k_hot_scan (step 2) and
+// its bucket table when i >= 2 and the join may run (step 3).
 __global__ __launch_bounds__(1024) void k_rows(Geom G, const uint32_t *__restrict__ hotmask,
                                                uint32_t *__restrict__ he,
                                                uint32_t *__restrict__ bk_off,
                                                uint32_t *__restrict__ bk_cur,
                                                uint32_t *__restrict__ bk_val,
-                                               DevState *__restrict__ st, double e_theta,
-                                               uint32_t buckets) {
+                                               DevState *__restrict__ st, uint32_t buckets) {
   __shared__ uint32_t sh[17];
   __shared__ uint32_t lcur[BK_LDS];
   const uint32_t row = blockIdx.x;
   compact_row(G, row, hotmask, he, st, sh);
-  if (row == 0 && threadIdx.x == 0) scalars(G, st, e_theta);
   if (row < 2 || !buckets) return;                     // uniform over the block
   __syncthreads();                                     // this row's HE and count
-  const uint32_t nb = 1u << (G.k - G.alpha);
-  uint32_t *off = bk_off + (size_t)row * (nb + 1);
-  const uint32_t *h = he + ((size_t)row << G.k);
-  uint32_t *val = bk_val + ((size_t)row << G.k);
-  const uint32_t n = st->he_count[row];
-  if (nb <= BK_LDS) bucket_rows(G, row, h, n, off, lds_ptr(lcur), val, sh);
-  else bucket_rows(G, row, h, n, off, bk_cur + (size_t)row * nb, val, sh);
+  row_buckets(G, row, he, st->he_count[row], bk_off, bk_cur, bk_val, lcur, sh);
+}
+
+// The bucket tables of rows 2..r-1 alone (larger sketches, after k_compact).
+__global__ __launch_bounds__(1024) void k_buckets(Geom G, const uint32_t *__restrict__ he,
+                                                  uint32_t *__restrict__ bk_off,
+                                                  uint32_t *__restrict__ bk_cur,
+                                                  uint32_t *__restrict__ bk_val,
+                                                  const DevState *__restrict__ st) {
+  __shared__ uint32_t sh[17];
+  __shared__ uint32_t lcur[BK_LDS];
+  const uint32_t row = blockIdx.x + 2;
+  row_buckets(G, row, he, st->he_count[row], bk_off, bk_cur, bk_val, lcur, sh);
+}
+
+// Steps 1-3 of a small sketch (k <= SCAN_ROWS_K) in one launch, one block
+// per row: the row's zero counts (at most 256 KiB) to its hot bitmap, ZR(i),
+// HE(i) and bucket table, and the state's start. A small sketch's restore is
+// a chain of launches of a few microseconds each: clearing, scan and rows
+// took 12.5 us of kernels in three launches for the default sketch.
+constexpr uint32_t SCAN_ROWS_K = 16;
+
+__global__ __launch_bounds__(1024) void k_scan_rows(
+    Geom G, const uint4 *__restrict__ lez4, uint32_t zhot, uint32_t *__restrict__ hotmask,
+    uint32_t *__restrict__ he, uint32_t *__restrict__ bk_off, uint32_t *__restrict__ bk_cur,
+    uint32_t *__restrict__ bk_val, DevState *__restrict__ st, uint32_t buckets) {
+  __shared__ uint32_t hw[(1u << SCAN_ROWS_K) / 32];
+  __shared__ uint32_t lcur[BK_LDS];
+  __shared__ uint32_t sh[17];
+  __shared__ unsigned long long zr;
+  const uint32_t row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const uint32_t nq = (1u << G.k) / 4, nw = (1u << G.k) / 32;   // k >= 5: whole groups of 8 lanes
+  const uint4 *z4 = lez4 + (size_t)row * nq;
+  if (row == 0) state_begin(G, st);
+  if (tid == 0) zr = 0;
+  __syncthreads();
+  uint32_t zeros = 0;                                   // a lane's: at most 64 LEs of 2^13
+  constexpr uint32_t U = 4;
+  for (uint32_t q0 = tid; q0 < nq; q0 += 1024 * U) {
+    uint4 z[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; u++) z[u] = z4[q0 + u * 1024 < nq ? q0 + u * 1024 : q0];
+#pragma unroll
+    for (uint32_t u = 0; u < U; u++) {
+      const uint32_t q = q0 + u * 1024;
+      const uint32_t w = hot_word(z[u], zhot, lane);
+      if (q < nq) {
+        if ((lane & 7) == 0) {
+          hw[q >> 3] = w;
+          hotmask[(size_t)row * nw + (q >> 3)] = w;
+        }
+        zeros += z[u].x + z[u].y + z[u].z + z[u].w;
+      }
+    }
+  }
+  // a wave's sum is below 2^26
+  zeros = wave_incl_scan(zeros);
+  if (lane == 63 && zeros) atomicAdd(&zr, (unsigned long long)zeros);
+  __syncthreads();
+  constexpr uint32_t PER = (1u << SCAN_ROWS_K) / 32 / 1024;
+  const uint32_t w0 = tid * PER;
+  uint32_t m[PER], cnt = 0, total;
+#pragma unroll
+  for (uint32_t u = 0; u < PER; u++) {
+    m[u] = w0 + u < nw ? hw[w0 + u] : 0u;
+    cnt += __popc(m[u]);
+  }
+  const uint32_t ex = block_excl_scan<1024>(cnt, &total, sh);
+  uint32_t *out = he + ((size_t)row << G.k) + ex;
+#pragma unroll
+  for (uint32_t u = 0; u < PER; u++) {
+    while (m[u]) {
+      const uint32_t b = __ffs(m[u]) - 1;
+      *out++ = ((w0 + u) << 5) | b;
+      m[u] &= m[u] - 1;
+    }
+  }
+  if (tid == 0) {
+    st->zr[row] = zr;
+    st->he_count[row] = total;
+  }
+  if (row < 2 || !buckets) return;                     // uniform over the block
+  __syncthreads();                                     // this row's HE
+  row_buckets(G, row, he, total, bk_off, bk_cur, bk_val, lcur, sh);
 }
 
 // ------------------------------------------------------ 5: search choice
@@ -427,6 +607,24 @@ __global__ __launch_bounds__(1024) void k_rows(Geom G, const uint32_t *__restric
 // one LDS read (about a quarter of a join item). Every kernel of both
 // searches evaluates this on the same counts, so exactly one of them runs.
 constexpr double LATTICE_COST = 0.25;
+
+// A row without a zero bit left (psi = 1): nothing to search.
+__device__ __forceinline__ bool no_zeros(const Geom &G, const DevState *st) {
+  for (uint32_t i = 0; i < G.r; i++)
+    if (st->zr[i] == 0) return true;
+  return false;
+}
+
+// Step 4 by the first block of each search launched: both searches' kernels
+// follow the scan, and the estimate follows them.
+__device__ __forceinline__ void search_begin(const Geom &G, DevState *st, double e_theta,
+                                             bool chosen, uint32_t search) {
+  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  const bool full = no_zeros(G, st);
+  if (!chosen && !full) return;
+  scalars(G, st, e_theta);
+  if (!full) st->search = search;
+}
 
 __device__ __forceinline__ bool lattice_chosen(const Geom &G, const DevState *st,
                                                const Lattice &L, uint32_t path) {
@@ -480,10 +678,11 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
     Geom G, Lattice L, uint32_t path, const uint32_t *__restrict__ he,
     const uint32_t *__restrict__ hotmask, DevState *__restrict__ st,
-    uint32_t *__restrict__ cand, size_t cand_cap) {
+    uint32_t *__restrict__ cand, size_t cand_cap, double e_theta) {
   extern __shared__ uint32_t row1[];                   // 2^k bits, then the queues
-  if (st->saturated || !lattice_chosen(G, st, L, path)) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) st->search = 2;
+  const bool chosen = lattice_chosen(G, st, L, path);
+  search_begin(G, st, e_theta, chosen, 2);
+  if (!chosen || no_zeros(G, st)) return;
   const uint32_t k = G.k, kw = 1u << (k - 5);
   for (uint32_t w = threadIdx.x; w < kw; w += blockDim.x) row1[w] = hotmask[kw + w];
   __syncthreads();
@@ -876,14 +1075,15 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
     const uint2 *__restrict__ in, const uint32_t *__restrict__ in_cnt,
     const uint32_t *__restrict__ bk_off, const uint32_t *__restrict__ bk_val,
     DevState *__restrict__ st, uint2 *__restrict__ out, uint32_t *__restrict__ out_cnt,
-    size_t seg_cap, uint32_t *__restrict__ cand, size_t cand_cap) {
+    size_t seg_cap, uint32_t *__restrict__ cand, size_t cand_cap, double e_theta) {
   __shared__ uint16_t t_off[TAB_OFF_MAX];
   __shared__ __attribute__((aligned(16))) uint8_t t_val[TAB_VAL_BYTES];
   __shared__ uint32_t w_incl[JOIN_THREADS];
   __shared__ uint16_t w_own[(JOIN_THREADS / 64) * OWN_MAX];
   __shared__ uint32_t seg_fill;
-  if (st->saturated || lattice_chosen(G, st, Lt, path)) return;
-  if (FIRST && blockIdx.x == 0 && threadIdx.x == 0) st->search = 1;
+  const bool chosen = !lattice_chosen(G, st, Lt, path);
+  if (FIRST) search_begin(G, st, e_theta, chosen, 1);
+  if (!chosen || no_zeros(G, st)) return;
 
   const uint32_t nb = 1u << (G.k - G.alpha), M = nb - 1;
   const uint32_t h = st->he_count[row];
@@ -927,14 +1127,226 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
   }
 }
 
+// ------------------------------------------------- 5c: the join in one launch
+//
+// The join of Algs. 3-4 for sketches with small bucket tables (r >= 4 and
+// 2^(k - alpha) <= WALK_NB), depth first: a wave's stage-1 outputs go to a
+// queue of its own in LDS, and whenever a queue holds 64 partial addresses
+// the wave takes them through the next row, so no partial address leaves the
+// compute unit and the stages need no launches of their own. What bounds it
+// is the same as k_join; the three launches it replaces took 6-7 us each on
+// the 1M-pair window, most of it start-up. The tables of rows 2..r-1 are
+// copied to LDS when they fit, else read where they are.
+
+constexpr uint32_t WALK_NB = 1u << JOIN_WALK_BITS;   // buckets per row, at most
+constexpr uint32_t WALK_VAL_BYTES = 8192;       // bucket entries per row held in LDS
+constexpr uint32_t WALK_QUEUE = 128;            // partial addresses per wave and stage
+
+template <int R, bool TLDS>
+struct JoinWalk {
+  // LDS of one wave
+  struct Wave {
+    uint32_t incl[R - 2][64];
+    uint16_t own[R - 2][OWN_MAX];
+    uint32_t queue_a[R - 3][WALK_QUEUE], queue_c[R - 3][WALK_QUEUE];
+  };
+  const Geom &G;
+  LDSP Wave *W;
+  JoinTable<TLDS> T[R - 2];                     // rows 2..R-1
+  uint32_t fill[R - 2];                         // queue fill of the stage into row i + 2
+  uint32_t outs[R - 2];                         // outputs of the stage into row i + 2
+  DevState *st;
+  uint32_t *cand;
+  size_t cand_cap;
+
+  // 64 items (sub, c0), one per lane, into row ROW; every output goes on.
+  template <int ROW>
+  __device__ __forceinline__ void expand(uint32_t sub, uint32_t c0, bool valid) {
+    constexpr int S = ROW - 2;
+    const uint32_t lane = lane_id();
+    const uint32_t M = (1u << (G.k - G.alpha)) - 1;
+    uint32_t b0 = 0, cnt = 0;
+    if (valid) {
+      const uint32_t sh = G.shift[ROW];
+      const uint32_t key = ((sh < 32 ? sub >> sh : 0u) ^ c0) & M;
+      b0 = T[S].start(key);
+      cnt = T[S].start(key + 1) - b0;
+    }
+    const uint32_t incl = wave_incl_scan(cnt);
+    const uint32_t total = wave_lane(incl, 63);
+    if (total == 0) return;
+    const bool owned = total <= OWN_MAX;        // as in join_items
+    if (owned) {
+      for (uint32_t q = incl - cnt; q < incl; q++) W->own[S][q] = (uint16_t)lane;
+    } else {
+      W->incl[S][lane] = incl;
+    }
+    const int32_t my_base = (int32_t)b0 - (int32_t)(incl - cnt);
+    lds_fence();
+    for (uint32_t base = 0; base < total; base += 64) {
+      const uint32_t slot = base + lane;
+      const bool live = slot < total;
+      const uint32_t sl = live ? slot : total - 1;
+      uint32_t o = 0;
+      if (owned) {
+        o = W->own[S][sl];
+      } else {
+#pragma unroll
+        for (uint32_t q = 32; q; q >>= 1)
+          if (W->incl[S][o + q - 1] <= sl) o += q;
+      }
+      const int32_t ob = __builtin_amdgcn_ds_bpermute((int)(o << 2), my_base);
+      const uint32_t osub = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(o << 2), (int)sub);
+      const uint32_t oc0 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(o << 2), (int)c0);
+      bool ok = false;
+      uint32_t a = 0;
+      if (live) {
+        const uint32_t j = (uint32_t)(ob + (int32_t)slot);
+        const uint32_t top = (oc0 >> (G.k - G.alpha)) ^ T[S].top_bits(j);
+        ok = extend_top(G, ROW, osub, top, &a);
+        if (ROW == R - 1) ok = ok && hash_dh0(G, a) == oc0;
+      }
+      const unsigned long long mask = __ballot(ok);
+      if (mask == 0) continue;
+      const uint32_t n_ok = __popcll(mask), rank = lanes_below(mask);
+      if constexpr (ROW == R - 1) {
+        unsigned long long gb = 0;
+        if (lane == 0) gb = atomicAdd(&st->n_cand, (unsigned long long)n_ok);
+        gb = wave_lane64(gb, 0);
+        if (ok && gb + rank < cand_cap) cand[gb + rank] = a;
+      } else {
+        outs[S] += n_ok;
+        if (ok) {
+          W->queue_a[S][fill[S] + rank] = a;
+          W->queue_c[S][fill[S] + rank] = oc0;
+        }
+        fill[S] += n_ok;                        // at most 63 + 64
+        lds_fence();
+        if (fill[S] >= 64) {
+          fill[S] -= 64;
+          const uint2 p = take(S, fill[S] + lane);
+          lds_fence();
+          expand<ROW + 1>(p.x, p.y, true);
+        }
+      }
+    }
+    lds_fence();
+  }
+  __device__ __forceinline__ uint2 take(int s, uint32_t i) const {
+    return make_uint2(W->queue_a[s][i], W->queue_c[s][i]);
+  }
+  // What is left in the queues, row by row.
+  template <int ROW>
+  __device__ __forceinline__ void flush() {
+    if constexpr (ROW < R) {
+      constexpr int S = ROW - 3;                // the queue of the stage before
+      const uint32_t n = fill[S];
+      if (n) {
+        fill[S] = 0;
+        const uint32_t lane = lane_id();
+        const uint2 p = take(S, lane < n ? lane : 0);
+        lds_fence();
+        expand<ROW>(p.x, p.y, lane < n);
+      }
+      flush<ROW + 1>();
+    }
+  }
+};
+
+template <int R, bool TLDS>
+__device__ __forceinline__ void join_walk(const Geom &G, const uint32_t *he, const uint32_t *bk_off,
+                                          const uint32_t *bk_val, LDSP uint16_t *t_off,
+                                          LDSP uint8_t *t_val, DevState *st, uint32_t *cand,
+                                          size_t cand_cap,
+                                          typename JoinWalk<R, TLDS>::Wave *waves,
+                                          LDSP uint32_t *outs) {
+  const uint32_t nb = 1u << (G.k - G.alpha), lane = lane_id();
+  const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  JoinWalk<R, TLDS> J{G, lds_ptr(waves) + wib, {}, {}, {}, st, cand, cand_cap};
+#pragma unroll
+  for (int s = 0; s < R - 2; s++)
+    J.T[s] = JoinTable<TLDS>{t_off + s * (WALK_NB + 1), t_val + s * WALK_VAL_BYTES,
+                             (LDSP uint16_t *)(t_val + s * WALK_VAL_BYTES),
+                             bk_off + (size_t)(s + 2) * (nb + 1),
+                             bk_val + ((size_t)(s + 2) << G.k), G.k - G.alpha, G.alpha > 8};
+  // stage-1 items (x0, 64 entries of HE(1)) dealt to the waves of the grid
+  // in turn
+  const uint32_t h0 = st->he_count[0], h1 = st->he_count[1], nch = (h1 + 63) >> 6;
+  const uint64_t n_items = (uint64_t)h0 * nch;
+  const uint32_t n_waves = gridDim.x * (JOIN_THREADS / 64);
+  const uint32_t *HE0 = he, *HE1 = he + (1u << G.k);
+  for (uint64_t w = blockIdx.x + (uint64_t)gridDim.x * wib; w < n_items; w += n_waves) {
+    const uint32_t x0 = (uint32_t)(w / nch), x1 = ((uint32_t)(w - (uint64_t)x0 * nch) << 6) + lane;
+    const uint32_t c0 = HE0[x0];
+    const uint32_t sub = c0 ^ HE1[x1 < h1 ? x1 : h1 - 1];     // BL(1)
+    J.template expand<2>(sub, c0, x1 < h1);
+  }
+  J.template flush<3>();
+  if (lane == 0)
+#pragma unroll
+    for (int s = 0; s < R - 3; s++)
+      if (J.outs[s]) atomicAdd((uint32_t *)&outs[s], J.outs[s]);
+}
+
+template <int R>
+__global__ __launch_bounds__(JOIN_THREADS) void k_join_walk(
+    Geom G, Lattice Lt, uint32_t path, const uint32_t *__restrict__ he,
+    const uint32_t *__restrict__ bk_off, const uint32_t *__restrict__ bk_val,
+    DevState *__restrict__ st, uint32_t *__restrict__ cand, size_t cand_cap, double e_theta) {
+  __shared__ uint16_t t_off[(R - 2) * (WALK_NB + 1)];
+  __shared__ __attribute__((aligned(16))) uint8_t t_val[(R - 2) * WALK_VAL_BYTES];
+  __shared__ typename JoinWalk<R, true>::Wave waves[JOIN_THREADS / 64];
+  __shared__ uint32_t outs[R - 2];
+  const bool chosen = !lattice_chosen(G, st, Lt, path);
+  search_begin(G, st, e_theta, chosen, 1);
+  if (!chosen || no_zeros(G, st)) return;
+  const uint32_t nb = 1u << (G.k - G.alpha);
+  const bool wide = G.alpha > 8;
+  uint32_t most = 0;
+  for (int i = 2; i < R; i++) most = max(most, st->he_count[i]);
+  const bool lds = G.alpha <= 16 && most * (wide ? 2 : 1) <= WALK_VAL_BYTES;
+  if (threadIdx.x < R - 2) outs[threadIdx.x] = 0;
+  if (lds) {
+    for (int i = 2; i < R; i++) {
+      const uint32_t *g_off = bk_off + (size_t)i * (nb + 1), *g_val = bk_val + ((size_t)i << G.k);
+      uint16_t *off = t_off + (i - 2) * (WALK_NB + 1);
+      uint8_t *val = t_val + (i - 2) * WALK_VAL_BYTES;
+      const uint32_t h = st->he_count[i];
+      for (uint32_t x = threadIdx.x; x <= nb; x += blockDim.x) off[x] = (uint16_t)g_off[x];
+      for (uint32_t x = threadIdx.x; x < h; x += blockDim.x) {
+        const uint32_t hi = g_val[x] >> (G.k - G.alpha);
+        if (wide) reinterpret_cast<uint16_t *>(val)[x] = (uint16_t)hi;
+        else val[x] = (uint8_t)hi;
+      }
+    }
+  }
+  __syncthreads();
+  if (lds)
+    join_walk<R, true>(G, he, bk_off, bk_val, lds_ptr(t_off), lds_ptr(t_val), st, cand, cand_cap,
+                       waves, lds_ptr(outs));
+  else
+    join_walk<R, false>(G, he, bk_off, bk_val, lds_ptr(t_off), lds_ptr(t_val), st, cand, cand_cap,
+                        reinterpret_cast<typename JoinWalk<R, false>::Wave *>(waves),
+                        lds_ptr(outs));
+  __syncthreads();
+  if (threadIdx.x < R - 3 && outs[threadIdx.x])
+    atomicAdd(&st->n_out[threadIdx.x + 2], (unsigned long long)outs[threadIdx.x]);
+}
+
 // ------------------------------------------------------------ 6: estimate
+
+constexpr uint32_t SMALL_SORT = 16384;                  // see the sort
 
 template <int WPL>
 __global__ __launch_bounds__(256) void k_estimate(Geom G, const uint32_t *__restrict__ sk,
                                                   const uint32_t *__restrict__ cand,
                                                   size_t cand_cap, DevState *__restrict__ st,
-                                                  uint4 *__restrict__ spl, size_t spl_cap) {
+                                                  uint4 *__restrict__ spl, size_t spl_cap,
+                                                  uint32_t *__restrict__ rank) {
   using S = LeShape<WPL>;
+  if (rank)                                             // the sort's ranks, zeroed for it
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < SMALL_SORT; i += gridDim.x * 256)
+      rank[i] = 0;
   if (st->saturated) return;
   const unsigned long long nc_all = st->n_cand;
   const uint64_t nc = nc_all < cand_cap ? nc_all : cand_cap;
@@ -1017,7 +1429,6 @@ __global__ __launch_bounds__(256) void k_estimate(Geom G, const uint32_t *__rest
 // a record's rank is the sum over the tiles of the keys below its own, one
 // binary search per tile: n * (n / SORT_TILE) * log2(SORT_TILE) steps
 // rather than n^2 compares.
-constexpr uint32_t SMALL_SORT = 16384;
 constexpr uint32_t RANK_SPLIT = 64;
 constexpr uint32_t SORT_TILE = 4096;
 
@@ -1133,6 +1544,11 @@ __global__ __launch_bounds__(256) void k_rank_place(const T *__restrict__ in,
     out[rank[j]] = in[j];
 }
 
+// The first SMALL_SORT sort ranks to zero (a grid of SMALL_SORT threads).
+__global__ __launch_bounds__(1024) void k_zero_ranks(uint32_t *rank) {
+  rank[blockIdx.x * 1024 + threadIdx.x] = 0;
+}
+
 // rank must hold SMALL_SORT zeroed entries and room for cap; skeys room for
 // cap rounded up to SORT_TILE. The kernels of the path a list does not take
 // return at once.
@@ -1171,7 +1587,93 @@ __global__ __launch_bounds__(256) void k_publish(const DevState *__restrict__ st
     h_recs[i] = recs[i];
 }
 
+// Sort and publish in one launch of one block, for lists of at most
+// SORT_ONE records: the keys sorted in LDS (bitonic), each record from its
+// place to its rank. A longer list is left alone (only the state goes out):
+// the host runs the restore again with the kernels above. Four launches took
+// 11 us of kernels, and their gaps, for the 1M-pair window's 33 records.
+constexpr uint32_t SORT_ONE = RESTORE_SORT_ONE;
+
+__global__ __launch_bounds__(1024) void k_sort_publish(
+    const DevState *__restrict__ st, const uint4 *__restrict__ in, size_t cap,
+    uint4 *__restrict__ out, DevState *h_state, uint4 *h_recs, size_t h_cap) {
+  __shared__ unsigned long long key[SORT_ONE];          // address over place
+  const uint32_t tid = threadIdx.x;
+  {
+    const uint32_t *src = reinterpret_cast<const uint32_t *>(st);
+    uint32_t *dst = reinterpret_cast<uint32_t *>(h_state);
+    for (uint32_t i = tid; i < sizeof(DevState) / 4; i += 1024) dst[i] = src[i];
+  }
+  if (st->saturated || st->n_spl > SORT_ONE || st->n_spl > cap) return;
+  const uint32_t n = (uint32_t)st->n_spl;
+  uint32_t p2 = 2;
+  while (p2 < n) p2 <<= 1;
+  for (uint32_t i = tid; i < p2; i += 1024)
+    key[i] = i < n ? ((unsigned long long)in[i].x << 32) | i : ~0ull;   // no record: above all
+  __syncthreads();
+  for (uint32_t size = 2; size <= p2; size <<= 1)
+    for (uint32_t stride = size >> 1; stride; stride >>= 1) {
+      for (uint32_t p = tid; p < p2 / 2; p += 1024) {
+        const uint32_t i = 2 * p - (p & (stride - 1)), j = i + stride;
+        const unsigned long long a = key[i], b = key[j];
+        if ((a > b) == ((i & size) == 0)) {
+          key[i] = b;
+          key[j] = a;
+        }
+      }
+      __syncthreads();
+    }
+  for (uint32_t i = tid; i < n; i += 1024) {
+    const uint4 v = in[(uint32_t)key[i]];
+    out[i] = v;
+    if (h_recs && i < h_cap) h_recs[i] = v;
+  }
+}
+
 // ------------------------------------------------------------ orchestration
+
+// The join's launches: one walk where the bucket tables are small, else a
+// stage per row.
+template <int R>
+static void launch_walk(const Geom &G, const RestoreBufs &B, double e_theta, hipStream_t st) {
+  k_join_walk<R><<<B.jblk, JOIN_THREADS, 0, st>>>(G, B.lat, B.cand_path, B.he, B.bk_off, B.bk_val,
+                                                  B.st, B.cand, B.cand_cap, e_theta);
+}
+
+static void launch_join(const Geom &G, const RestoreBufs &B, double e_theta, hipStream_t st) {
+  const uint32_t r = G.r, jb = B.jblk, pth = B.cand_path;
+  const Lattice &Lt = B.lat;
+  if (B.walk) {
+    switch (r) {
+      case 4: launch_walk<4>(G, B, e_theta, st); break;
+      case 5: launch_walk<5>(G, B, e_theta, st); break;
+      case 6: launch_walk<6>(G, B, e_theta, st); break;
+      case 7: launch_walk<7>(G, B, e_theta, st); break;
+      default: launch_walk<8>(G, B, e_theta, st);
+    }
+  } else if (r == 3) {
+    k_join<true, true><<<jb, JOIN_THREADS, 0, st>>>(G, Lt, pth, 2, B.he, nullptr, nullptr, B.bk_off,
+                                                    B.bk_val, B.st, nullptr, nullptr, 0, B.cand,
+                                                    B.cand_cap, e_theta);
+  } else {
+    k_join<true, false><<<jb, JOIN_THREADS, 0, st>>>(G, Lt, pth, 2, B.he, nullptr, nullptr,
+                                                     B.bk_off, B.bk_val, B.st, B.part[0],
+                                                     B.segc[0], B.seg_cap, B.cand, B.cand_cap,
+                                                     e_theta);
+    for (uint32_t row = 3; row < r; row++) {
+      // stage 1 wrote part[0]; stage `row` reads part[(row-3)%2], writes the other
+      const int ib = (row - 3) & 1, ob = ib ^ 1;
+      if (row + 1 == r)
+        k_join<false, true><<<jb, JOIN_THREADS, 0, st>>>(
+            G, Lt, pth, row, B.he, B.part[ib], B.segc[ib], B.bk_off, B.bk_val, B.st, nullptr,
+            nullptr, B.seg_cap, B.cand, B.cand_cap, e_theta);
+      else
+        k_join<false, false><<<jb, JOIN_THREADS, 0, st>>>(
+            G, Lt, pth, row, B.he, B.part[ib], B.segc[ib], B.bk_off, B.bk_val, B.st, B.part[ob],
+            B.segc[ob], B.seg_cap, B.cand, B.cand_cap, e_theta);
+    }
+  }
+}
 
 template <int WPL>
 static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const RestoreBufs &B,
@@ -1182,18 +1684,16 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
   auto mark = [&](int i) {
     if (marks) (void)hipEventRecord(marks[i], st);
   };
+  // a search is launched unless the sketch's setting or the expectation
+  // rules it out (each returns at once unless it is the chosen one)
+  const bool lattice = B.lat.ok && B.cand_path != 1 && B.expect != 1;
+  const bool join = !(B.lat.ok && B.cand_path == 2) && B.expect != 2;
   mark(0);
-  // 0: clear state and the hot bitmap
-  k_restore_init<<<(int)((n_le / 32 + 255) / 256 < 256 ? (n_le / 32 + 255) / 256 : 256), 256, 0,
-                   st>>>(B.st, B.rank, SMALL_SORT, B.hotmask, n_le / 32);
-  // 1: hot scan
-  if (B.lez) {
-    // HS_LEZ_UNROLL 16-byte loads per lane, the whole array in one pass
-    // (few blocks: each adds its row sums to ZR with global atomics)
-    const uint64_t blocks = (n_le / 4 + 256 * HS_LEZ_UNROLL - 1) / (256 * HS_LEZ_UNROLL);
-    k_hot_scan_lez<<<(int)(blocks < 65535 ? blocks : 65535), 256, 0, st>>>(
-        G, reinterpret_cast<const uint4 *>(B.lez), zhot, B.hotmask, B.st);
-  } else {
+  // 1-3: hot scan, HE(i), bucket tables (which serve only the join)
+  const uint4 *lez4 = reinterpret_cast<const uint4 *>(B.lez);
+  if (!B.lez) {
+    k_restore_init<<<(int)((n_le / 32 + 255) / 256 < 256 ? (n_le / 32 + 255) / 256 : 256), 256, 0,
+                     st>>>(B.st, B.hotmask, n_le / 32);
     using S = LeShape<WPL>;
     const uint64_t pass = (uint64_t)(256 / S::LPL) * HS_UNROLL;
     const uint64_t passes = (n_le + pass - 1) / pass;
@@ -1201,70 +1701,64 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
     const uint64_t chunk = (passes + blocks - 1) / blocks * pass;
     const int gs = (int)((n_le + chunk - 1) / chunk);
     k_hot_scan<WPL><<<gs, 256, 0, st>>>(G, sketch, zhot, B.hotmask, B.st, chunk);
+    mark(1);
+    k_rows<<<r, 1024, 0, st>>>(G, B.hotmask, B.he, B.bk_off, B.bk_cur, B.bk_val, B.st, join);
+  } else {
+    if constexpr (WPL >= 4 && WPL <= 256) {
+      if (B.lez_stale) {
+        const size_t n4 = n_le * (WPL / 4);
+        const size_t blocks = (n4 + 1023) / 1024;
+        k_zero_counts<WPL><<<(int)(blocks < (size_t)grid ? blocks : (size_t)grid), 256, 0, st>>>(
+            G, reinterpret_cast<const uint4 *>(sketch), B.lez);
+      }
+    }
+    // phase events take the larger sketches' kernels, one per phase
+    if (k <= SCAN_ROWS_K && !(marks && k >= 12)) {
+      k_scan_rows<<<r, 1024, 0, st>>>(G, lez4, zhot, B.hotmask, B.he, B.bk_off, B.bk_cur, B.bk_val,
+                                      B.st, join);
+      mark(1);
+    } else {
+      const int chunks = (int)(n_le / SCAN_CHUNK);
+      k_hot_scan_lez<<<chunks, 256, 0, st>>>(G, lez4, zhot, B.hotmask, B.chunks);
+      mark(1);
+      k_compact<<<chunks, 256, 0, st>>>(G, B.hotmask, B.chunks, B.he, B.st);
+      if (join) k_buckets<<<r - 2, 1024, 0, st>>>(G, B.he, B.bk_off, B.bk_cur, B.bk_val, B.st);
+    }
   }
-  mark(1);
-  // 2-4: HE(i), bucket tables of rows 2..r-1, scalars
-  // the bucket tables serve only the join: none when the sketch is set to
-  // the lattice search
-  const uint32_t buckets = !(B.lat.ok && B.cand_path == 2);
-  k_rows<<<r, 1024, 0, st>>>(G, B.hotmask, B.he, B.bk_off, B.bk_cur, B.bk_val, B.st, e_theta,
-                             buckets);
   mark(2);
-  // 5: candidates, by the lattice search or the join (each kernel returns
-  // at once unless its search is the chosen one; a search ruled out by the
-  // sketch's setting is not launched)
-  if (B.lat.ok && B.cand_path != 1) {
+  // 4-5: scalars and candidates
+  if (lattice) {
     // row 1's bitmap and the queues (above 64 KiB by the attribute that
     // prepare_restore_kernels sets)
     const size_t lds = ((size_t)4 << (k - 5)) + LAT_QUEUE_BYTES;
     // half the usual grid: each block first copies row 1's bitmap
     k_lattice<<<grid > 1 ? grid / 2 : 1, LAT_THREADS, lds, st>>>(
-        G, B.lat, B.cand_path, B.he, B.hotmask, B.st, B.cand, B.cand_cap);
+        G, B.lat, B.cand_path, B.he, B.hotmask, B.st, B.cand, B.cand_cap, e_theta);
   }
-  if (!(B.lat.ok && B.cand_path == 2)) {
-    const uint32_t jb = B.jblk;
-    const Lattice &Lt = B.lat;
-    const uint32_t pth = B.cand_path;
-    if (r == 3) {
-      k_join<true, true><<<jb, JOIN_THREADS, 0, st>>>(G, Lt, pth, 2, B.he, nullptr, nullptr, B.bk_off,
-                                                      B.bk_val, B.st, nullptr, nullptr, 0,
-                                                      B.cand, B.cand_cap);
-    } else {
-      k_join<true, false><<<jb, JOIN_THREADS, 0, st>>>(G, Lt, pth, 2, B.he, nullptr, nullptr, B.bk_off,
-                                                       B.bk_val, B.st, B.part[0], B.segc[0],
-                                                       B.seg_cap, B.cand, B.cand_cap);
-      for (uint32_t row = 3; row < r; row++) {
-        // stage 1 wrote part[0]; stage `row` reads part[(row-3)%2], writes the other
-        const int ib = (row - 3) & 1, ob = ib ^ 1;
-        if (row + 1 == r)
-          k_join<false, true><<<jb, JOIN_THREADS, 0, st>>>(
-              G, Lt, pth, row, B.he, B.part[ib], B.segc[ib], B.bk_off, B.bk_val, B.st, nullptr, nullptr,
-              B.seg_cap, B.cand, B.cand_cap);
-        else
-          k_join<false, false><<<jb, JOIN_THREADS, 0, st>>>(
-              G, Lt, pth, row, B.he, B.part[ib], B.segc[ib], B.bk_off, B.bk_val, B.st, B.part[ob],
-              B.segc[ob], B.seg_cap, B.cand, B.cand_cap);
-      }
-    }
-  }
+  if (join) launch_join(G, B, e_theta, st);
   mark(3);
   if (!estimate) {
     mark(4);
+    k_zero_ranks<<<SMALL_SORT / 1024, 1024, 0, st>>>(B.rank);
     launch_sort<uint32_t>(B.cand, &B.st->n_cand, B.cand_cap, B.cand_sorted, B.rank, B.skeys,
                           grid, st);
     k_publish<<<1, 256, 0, st>>>(B.st, nullptr, 0, B.h_state, nullptr, 0);
     mark(5);
     return hipGetLastError();
   }
-  // 6: estimate and report
+  // 6: estimate and report (its first blocks clear the sort ranks)
   k_estimate<WPL><<<grid, 256, 0, st>>>(G, sketch, B.cand, B.cand_cap, B.st, B.spl,
-                                        B.spl_cap);
+                                        B.spl_cap, B.sort_one ? nullptr : B.rank);
   mark(4);
-  // 7: sort
-  launch_sort<uint4>(B.spl, &B.st->n_spl, B.spl_cap, B.spl_sorted, B.rank, B.skeys, grid, st);
-  // 8: state and records to the host
-  k_publish<<<16, 256, 0, st>>>(B.st, B.spl_sorted, B.spl_cap, B.h_state, B.h_recs,
-                                B.h_recs_cap);
+  // 7-8: sort; state and records to the host
+  if (B.sort_one) {
+    k_sort_publish<<<1, 1024, 0, st>>>(B.st, B.spl, B.spl_cap, B.spl_sorted, B.h_state, B.h_recs,
+                                       B.h_recs_cap);
+  } else {
+    launch_sort<uint4>(B.spl, &B.st->n_spl, B.spl_cap, B.spl_sorted, B.rank, B.skeys, grid, st);
+    k_publish<<<16, 256, 0, st>>>(B.st, B.spl_sorted, B.spl_cap, B.h_state, B.h_recs,
+                                  B.h_recs_cap);
+  }
   mark(5);
   return hipGetLastError();
 }
