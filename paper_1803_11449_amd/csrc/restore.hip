@@ -59,16 +59,10 @@ __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
 
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) { return wave_scan_incl(v); }
 
-// Reserve `nout` consecutive slots of a global list for this lane, with one
-// atomic per wave. Must be called by all 64 lanes of the wave.
-__device__ __forceinline__ unsigned long long wave_reserve(
-    unsigned long long *counter, uint32_t nout) {
-  const uint32_t incl = wave_incl_scan(nout);
-  const uint32_t total = wave_lane(incl, 63);
-  unsigned long long base = 0;
-  if (lane_id() == 63 && total) base = atomicAdd(counter, (unsigned long long)total);
-  base = wave_lane64(base, 63);
-  return base + (incl - nout);
+// Lanes below this one whose bit is set in mask.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 // Exclusive prefix sum over a workgroup of NT threads (NT a multiple of 64).
@@ -91,6 +85,52 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *total,
   __syncthreads();
   return off + inc - v;
 }
+
+// A block's candidates on their way to the global list. Every append to that
+// list is an atomic on one address, and those pass at about one in 10 ns
+// whatever their number of lanes: a search that made one per wave and test
+// spent 1.2 of its 1.35 ms on 115,000 candidates. The first CAP of a block
+// are kept in LDS and appended by one atomic when the block ends; the rest
+// go out as they come.
+struct CandBuf {
+  static constexpr uint32_t CAP = 512;
+  uint32_t a[CAP], n;
+  unsigned long long base;
+
+  // add and put_global: all lanes of a wave; ok = the lane has an address.
+  __device__ __forceinline__ static void put_global(uint32_t ad, bool ok, DevState *st,
+                                                    uint32_t *cand, size_t cand_cap) {
+    const unsigned long long m = __ballot(ok);
+    if (m == 0) return;
+    const int first = (int)__builtin_ctzll(m);
+    unsigned long long b = 0;
+    if (lane_id() == (uint32_t)first)
+      b = atomicAdd(&st->n_cand, (unsigned long long)__popcll(m));
+    b = wave_lane64(b, first) + lanes_below(m);
+    if (ok && b < cand_cap) cand[b] = ad;
+  }
+  __device__ __forceinline__ void add(uint32_t ad, bool ok, DevState *st, uint32_t *cand,
+                                      size_t cand_cap) {
+    const unsigned long long m = __ballot(ok);
+    if (m == 0) return;
+    const int first = (int)__builtin_ctzll(m);
+    uint32_t b = 0;
+    if (lane_id() == (uint32_t)first) b = atomicAdd(&n, (uint32_t)__popcll(m));
+    b = wave_lane(b, first);
+    const uint32_t i = b + lanes_below(m);
+    if (ok && i < CAP) a[i] = ad;
+    if (b + (uint32_t)__popcll(m) > CAP) put_global(ad, ok && i >= CAP, st, cand, cand_cap);
+  }
+  // The whole block, after its last add.
+  __device__ __forceinline__ void flush(DevState *st, uint32_t *cand, size_t cand_cap) {
+    __syncthreads();
+    const uint32_t k = n < CAP ? n : CAP;
+    if (threadIdx.x == 0 && k) base = atomicAdd(&st->n_cand, (unsigned long long)k);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < k; i += blockDim.x)
+      if (base + i < cand_cap) cand[base + i] = a[i];
+  }
+};
 
 // The most rows a sketch has.
 constexpr uint32_t R_MAX = 8;
@@ -657,80 +697,105 @@ __device__ __forceinline__ bool lattice_chosen(const Geom &G, const DevState *st
 // the appends. The walk runs in step across the wave (a lane whose line is
 // done walks no points), so the queue's fill is the same in every lane.
 // Each address lies in exactly one cell, so there are no duplicates.
+//
+// Bound by the vector ALU's issue: about 6 instructions and an LDS read per
+// address, and 3 to 4 for the survivors. 16 addresses per trip (the survivors'
+// prefix sum and loop once for them), the bit field extract's own masking, a
+// compute unit filled with waves, and candidates kept in LDS took the
+// 100M-pair window's search (119M addresses) from 97 to 67 us, a k = 19
+// sketch's from 126 to 58, and one of 511M addresses with 115,000 candidates
+// (k = 17, 12% of the LEs hot) from 1346 to 340 us. Survivors taken per
+// point by the wave's compare mask instead (9 vector instructions per
+// address, but a branch each) were slower: 84 us for the first.
 
-constexpr int LAT_THREADS = 512;
-constexpr uint32_t LAT_TRIP = 8;                        // points per lane per trip
-constexpr uint32_t LAT_QUEUE = 63 + LAT_TRIP * 64 + 1;  // survivors per wave
+constexpr int LAT_THREADS = 1024;
+constexpr uint32_t LAT_TRIP = 16;                       // points per lane per trip
+constexpr uint32_t LAT_PUSH = 512;                      // survivors appended at once, at most
+constexpr uint32_t LAT_QUEUE = 63 + LAT_PUSH + 1;       // survivors per wave
 constexpr uint32_t LAT_QUEUE_BYTES = (LAT_THREADS / 64) * LAT_QUEUE * 4;
-// row 1's bitmap for k <= 20, and the queues
-constexpr uint32_t LATTICE_LDS_MAX = 131072 + LAT_QUEUE_BYTES;
+constexpr uint32_t LAT_FOUND_BYTES = sizeof(CandBuf) + 8;
+// row 1's bitmap for k <= 20 (128 KiB; fewer waves, whose queues fit beside
+// it), and the queues
+constexpr uint32_t LATTICE_LDS_MAX = 163840;
+
+// Rows whose hot bitmaps a block of the search holds in LDS: rows 1..n, as
+// many as leave a compute unit two blocks (80 KiB each). Row 1 takes every
+// address, row 2 those that pass it (61M of 511M addresses at k = 17 with 12%
+// of the LEs hot).
+inline uint32_t lattice_rows(const Geom &G) {
+  const uint32_t row = 4u << (G.k - 5);
+  uint32_t n = 1;
+  while (n + 1 < G.r && (n + 1) * row + LAT_FOUND_BYTES + LAT_QUEUE_BYTES <= 81920) n++;
+  return n;
+}
+inline uint32_t lattice_lds(const Geom &G, uint32_t rows, uint32_t threads) {
+  return rows * (4u << (G.k - 5)) + LAT_FOUND_BYTES + threads / 64 * LAT_QUEUE * 4;
+}
+// Threads of a block: as many waves as have room for their queues.
+inline uint32_t lattice_threads(const Geom &G, uint32_t rows) {
+  uint32_t t = LAT_THREADS;
+  while (lattice_lds(G, rows, t) > LATTICE_LDS_MAX) t /= 2;
+  return t;
+}
 
 __device__ __forceinline__ int64_t mul_hi_s(int64_t m, uint64_t y) {
   return (int64_t)(((__int128)m * (__int128)(unsigned __int128)y) >> 64);
 }
 
-// Lanes below this one whose bit is set in mask.
-__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
 __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
     Geom G, Lattice L, uint32_t path, const uint32_t *__restrict__ he,
     const uint32_t *__restrict__ hotmask, DevState *__restrict__ st,
-    uint32_t *__restrict__ cand, size_t cand_cap, double e_theta) {
-  extern __shared__ uint32_t row1[];                   // 2^k bits, then the queues
+    uint32_t *__restrict__ cand, size_t cand_cap, double e_theta, uint32_t lds_rows) {
+  // lds_rows * 2^k bits, the candidates, then the queues
+  extern __shared__ __attribute__((aligned(16))) uint32_t row1[];
   const bool chosen = lattice_chosen(G, st, L, path);
   search_begin(G, st, e_theta, chosen, 2);
   if (!chosen || no_zeros(G, st)) return;
   const uint32_t k = G.k, kw = 1u << (k - 5);
-  for (uint32_t w = threadIdx.x; w < kw; w += blockDim.x) row1[w] = hotmask[kw + w];
+  CandBuf *found = reinterpret_cast<CandBuf *>(row1 + lds_rows * kw + (lds_rows * kw & 1));
+  if (threadIdx.x == 0) found->n = 0;
+  for (uint32_t w = threadIdx.x; w < lds_rows * kw; w += blockDim.x) row1[w] = hotmask[kw + w];
   __syncthreads();
   const uint32_t lane = threadIdx.x & 63;
-  uint32_t *queue = row1 + kw + (threadIdx.x >> 6) * LAT_QUEUE;
+  uint32_t *queue = reinterpret_cast<uint32_t *>(found + 1) + (threadIdx.x >> 6) * LAT_QUEUE;
   uint32_t qn = 0;                                       // queue fill, wave-uniform
 
-  // one survivor of row 1 per lane (ok = the lane has one): its LEs in row
-  // 0 and rows 2..r-1 all hot -> a candidate
+  // one survivor of row 1 per lane (ok = the lane has one): its LEs in rows
+  // 2..r-1 all hot -> a candidate (row 0's is: every address walked is in a
+  // hot row-0 cell). Rows in LDS first, one by one; the rest together.
   auto test = [&](uint32_t ad, bool ok) {
     const uint32_t c = hash_dh0(G, ad);
-    uint32_t wv[8], bit[8];
-    bit[0] = c;
-    // BL(row) of ad, its shift (row-1)*alpha (0 past bit 31) worked out
-    // here rather than read from G, which would hold six more scalar
-    // registers through the walk
-#pragma unroll
-    for (uint32_t row = 2; row < 8; row++)
-      if (row < G.r) {
-        const uint32_t sh = (row - 1) * G.alpha;
-        const uint32_t blk = sh < 32 ? (ad >> sh) & ((1u << k) - 1) : 0u;
-        bit[row] = (row << k) | (c ^ blk);
-      }
+    // the row's word and bit of ad; its block's shift (row-1)*alpha (0 past
+    // bit 31) worked out here rather than read from G, which would hold six
+    // more scalar registers through the walk
+    auto cell = [&](uint32_t row) {
+      const uint32_t sh = (row - 1) * G.alpha;
+      return c ^ __builtin_amdgcn_ubfe(ad, sh, sh < 32 ? k : 0u);
+    };
+    for (uint32_t row = 2; row <= lds_rows; row++) {
+      const uint32_t x = cell(row);
+      ok = ok && ((row1[(row - 1) * kw + (x >> 5)] >> (x & 31)) & 1u);
+      if (__ballot(ok) == 0) return;
+    }
     if (ok) {
-      wv[0] = hotmask[bit[0] >> 5];
+      uint32_t wv[8], x[8];
 #pragma unroll
       for (uint32_t row = 2; row < 8; row++)
-        if (row < G.r) wv[row] = hotmask[bit[row] >> 5];
-      ok = (wv[0] >> (bit[0] & 31)) & 1u;
+        if (row > lds_rows && row < G.r) {
+          x[row] = cell(row);
+          wv[row] = hotmask[row * kw + (x[row] >> 5)];
+        }
 #pragma unroll
       for (uint32_t row = 2; row < 8; row++)
-        if (row < G.r) ok = ok && ((wv[row] >> (bit[row] & 31)) & 1u);
+        if (row > lds_rows && row < G.r) ok = ok && ((wv[row] >> (x[row] & 31)) & 1u);
     }
-    const uint64_t m = __ballot(ok);
-    if (m) {
-      unsigned long long b = 0;
-      if (lane == (uint32_t)__builtin_ctzll(m)) b = atomicAdd(&st->n_cand, (unsigned long long)__popcll(m));
-      b = wave_lane64(b, (int)__builtin_ctzll(m));
-      const unsigned long long slot = b + lanes_below(m);
-      if (ok && slot < cand_cap) cand[slot] = ad;
-    }
+    found->add(ad, ok, st, cand, cand_cap);
   };
   // append the points of this trip that passed row 1 (bit q of hit: point
   // b + q step), placed by a prefix sum over the wave; test 64 at a time
-  // while the queue holds them (it holds at most 63 + LAT_TRIP*64 entries)
-  auto push = [&](uint32_t b, uint32_t step_, uint32_t hit) {
-    const uint32_t cnt = __popc(hit);
-    const uint32_t incl = wave_scan_incl(cnt);
+  // while the queue holds them. The queue has room for half of a trip's
+  // points: a trip with more survivors goes in two halves
+  auto append = [&](uint32_t b, uint32_t step_, uint32_t hit, uint32_t cnt, uint32_t incl) {
     uint32_t pos = qn + incl - cnt;
     for (uint32_t h = hit; h; h &= h - 1) queue[pos++] = b + (uint32_t)__builtin_ctz(h) * step_;
     qn += wave_lane(incl, 63);
@@ -740,6 +805,18 @@ __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
       const uint32_t ad2 = queue[qn + lane];
       __builtin_amdgcn_wave_barrier();
       test(ad2, true);
+    }
+  };
+  auto push = [&](uint32_t b, uint32_t step_, uint32_t hit) {
+    const uint32_t cnt = __popc(hit), incl = wave_scan_incl(cnt);
+    if (wave_lane(incl, 63) <= LAT_PUSH) {
+      append(b, step_, hit, cnt, incl);
+    } else {
+#pragma unroll 1
+      for (uint32_t half = 0xFFu; half <= 0xFF00u; half <<= 8) {
+        const uint32_t h = hit & half, n_h = __popc(h);
+        append(b, step_, h, n_h, wave_scan_incl(n_h));
+      }
     }
   };
 
@@ -819,24 +896,28 @@ __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
         }
       }
     }
-    // the walk: LAT_TRIP points per trip, their row-1 words read together.
-    // Point b's row-1 LE is (c ^ b) mod 2^k: its word is bits 5..k-1 of
-    // c ^ b (byte offset: bits 3..k-4) and its bit bits 0..4. Points past
-    // the line's end read a valid word and are masked out of hit.
+    // the walk: LAT_TRIP points per trip, the row-1 words of 8 read together.
+    // Point b's row-1 LE is x = (c ^ b) mod 2^k: its word is bits 5..k-1 of x
+    // (byte offset: bits 3..k-4) and its bit bits 0..4 (all that the bit field
+    // extract takes of its offset). Points past the line's end read a valid
+    // word and are masked out of hit.
     while (__ballot(n != 0)) {
       const uint32_t m = n < LAT_TRIP ? n : LAT_TRIP;
-      uint32_t cb[LAT_TRIP], w[LAT_TRIP];
-      uint32_t b = a;
+      uint32_t hit = 0, b = a;
 #pragma unroll
-      for (uint32_t q = 0; q < LAT_TRIP; q++) {
-        cb[q] = c ^ b;
-        w[q] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(row1) +
-                                                    ((cb[q] >> 3) & bmask));
-        b += step;
+      for (uint32_t h = 0; h < LAT_TRIP; h += 8) {
+        uint32_t x[8], w[8];
+#pragma unroll
+        for (uint32_t q = 0; q < 8; q++) {
+          x[q] = c ^ b;
+          // the block's dynamic LDS, its only LDS, starts at address 0
+          w[q] = *(const LDSP uint32_t *)(uintptr_t)((x[q] >> 3) & bmask);
+          b += step;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 8; q++)
+          hit |= __builtin_amdgcn_ubfe(w[q], x[q], 1u) << (h + q);
       }
-      uint32_t hit = 0;
-#pragma unroll
-      for (uint32_t q = 0; q < LAT_TRIP; q++) hit |= __builtin_amdgcn_ubfe(w[q], cb[q] & 31u, 1u) << q;
       hit &= (1u << m) - 1;
       push(a, step, hit);
       a += m * step;
@@ -845,6 +926,7 @@ __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
   }
   // what is left in the queue
   if (qn) test(queue[lane < qn ? lane : 0], lane < qn);
+  found->flush(st, cand, cand_cap);
 }
 
 // ------------------------------------------------------------------ 5: join
@@ -924,7 +1006,7 @@ __device__ __forceinline__ void join_items(
     const uint2 *__restrict__ in, const uint32_t *__restrict__ in_cnt,
     const JoinTable<TLDS> &T, DevState *__restrict__ st, uint2 *__restrict__ out,
     size_t seg_cap, uint32_t *__restrict__ cand, size_t cand_cap, uint32_t M,
-    LDSP uint32_t *w_incl, LDSP uint16_t *w_own, LDSP uint32_t *seg_fill_p) {
+    LDSP uint32_t *w_incl, LDSP uint16_t *w_own, LDSP uint32_t *seg_fill_p, CandBuf *found) {
   LDSP uint32_t &seg_fill = *seg_fill_p;
   const uint32_t lane = lane_id();
   const uint32_t wib = threadIdx.x >> 6;                    // wave in block
@@ -1054,10 +1136,7 @@ __device__ __forceinline__ void join_items(
       const uint32_t n_ok = __popcll(mask);
       const uint32_t rank = __popcll(mask & ((1ull << lane) - 1));
       if (LAST) {
-        unsigned long long gb = 0;
-        if (lane == 0) gb = atomicAdd(&st->n_cand, (unsigned long long)n_ok);
-        gb = wave_lane64(gb, 0);
-        if (ok && gb + rank < cand_cap) cand[gb + rank] = a;
+        found->add(a, ok, st, cand, cand_cap);
       } else {
         uint32_t lb = 0;
         if (lane == 0) lb = atomicAdd((uint32_t *)&seg_fill, n_ok);   // an LDS atomic after inlining
@@ -1081,6 +1160,7 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
   __shared__ uint32_t w_incl[JOIN_THREADS];
   __shared__ uint16_t w_own[(JOIN_THREADS / 64) * OWN_MAX];
   __shared__ uint32_t seg_fill;
+  __shared__ CandBuf found;
   const bool chosen = !lattice_chosen(G, st, Lt, path);
   if (FIRST) search_begin(G, st, e_theta, chosen, 1);
   if (!chosen || no_zeros(G, st)) return;
@@ -1092,7 +1172,10 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
                    (size_t)h * (wide ? 2 : 1) <= TAB_VAL_BYTES;
   const uint32_t *g_off = bk_off + (size_t)row * (nb + 1);
   const uint32_t *g_val = bk_val + ((size_t)row << G.k);
-  if (threadIdx.x == 0) seg_fill = 0;
+  if (threadIdx.x == 0) {
+    seg_fill = 0;
+    found.n = 0;
+  }
   if (lds) {
     for (uint32_t x = threadIdx.x; x <= nb; x += blockDim.x) t_off[x] = (uint16_t)g_off[x];
     for (uint32_t x = threadIdx.x; x < h; x += blockDim.x) {
@@ -1108,15 +1191,16 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
                             lds_ptr(reinterpret_cast<uint16_t *>(t_val)), g_off, g_val,
                             G.k - G.alpha, wide_t};
     join_items<FIRST, LAST, true>(G, row, he, in, in_cnt, T, st, out, seg_cap, cand, cand_cap,
-                                  M, lds_ptr(w_incl), lds_ptr(w_own), lds_ptr(&seg_fill));
+                                  M, lds_ptr(w_incl), lds_ptr(w_own), lds_ptr(&seg_fill), &found);
   } else {
     const JoinTable<false> T{lds_ptr(t_off), lds_ptr(t_val),
                              lds_ptr(reinterpret_cast<uint16_t *>(t_val)), g_off, g_val,
                              G.k - G.alpha, wide_t};
     join_items<FIRST, LAST, false>(G, row, he, in, in_cnt, T, st, out, seg_cap, cand,
                                    cand_cap, M, lds_ptr(w_incl), lds_ptr(w_own),
-                                   lds_ptr(&seg_fill));
+                                   lds_ptr(&seg_fill), &found);
   }
+  if (LAST) found.flush(st, cand, cand_cap);
   if (!LAST) {
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1158,6 +1242,7 @@ struct JoinWalk {
   DevState *st;
   uint32_t *cand;
   size_t cand_cap;
+  CandBuf *found;
 
   // 64 items (sub, c0), one per lane, into row ROW; every output goes on.
   template <int ROW>
@@ -1210,10 +1295,7 @@ struct JoinWalk {
       if (mask == 0) continue;
       const uint32_t n_ok = __popcll(mask), rank = lanes_below(mask);
       if constexpr (ROW == R - 1) {
-        unsigned long long gb = 0;
-        if (lane == 0) gb = atomicAdd(&st->n_cand, (unsigned long long)n_ok);
-        gb = wave_lane64(gb, 0);
-        if (ok && gb + rank < cand_cap) cand[gb + rank] = a;
+        found->add(a, ok, st, cand, cand_cap);
       } else {
         outs[S] += n_ok;
         if (ok) {
@@ -1259,10 +1341,11 @@ __device__ __forceinline__ void join_walk(const Geom &G, const uint32_t *he, con
                                           LDSP uint8_t *t_val, DevState *st, uint32_t *cand,
                                           size_t cand_cap,
                                           typename JoinWalk<R, TLDS>::Wave *waves,
-                                          LDSP uint32_t *outs) {
+                                          LDSP uint32_t *outs, CandBuf *found) {
   const uint32_t nb = 1u << (G.k - G.alpha), lane = lane_id();
   const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  JoinWalk<R, TLDS> J{G, lds_ptr(waves) + wib, {}, {}, {}, st, cand, cand_cap};
+  JoinWalk<R, TLDS> J{G, lds_ptr(waves) + wib, {}, {}, {}, st, cand, cand_cap,
+                        found};
 #pragma unroll
   for (int s = 0; s < R - 2; s++)
     J.T[s] = JoinTable<TLDS>{t_off + s * (WALK_NB + 1), t_val + s * WALK_VAL_BYTES,
@@ -1297,6 +1380,7 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join_walk(
   __shared__ __attribute__((aligned(16))) uint8_t t_val[(R - 2) * WALK_VAL_BYTES];
   __shared__ typename JoinWalk<R, true>::Wave waves[JOIN_THREADS / 64];
   __shared__ uint32_t outs[R - 2];
+  __shared__ CandBuf found;
   const bool chosen = !lattice_chosen(G, st, Lt, path);
   search_begin(G, st, e_theta, chosen, 1);
   if (!chosen || no_zeros(G, st)) return;
@@ -1306,6 +1390,7 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join_walk(
   for (int i = 2; i < R; i++) most = max(most, st->he_count[i]);
   const bool lds = G.alpha <= 16 && most * (wide ? 2 : 1) <= WALK_VAL_BYTES;
   if (threadIdx.x < R - 2) outs[threadIdx.x] = 0;
+  if (threadIdx.x == 0) found.n = 0;
   if (lds) {
     for (int i = 2; i < R; i++) {
       const uint32_t *g_off = bk_off + (size_t)i * (nb + 1), *g_val = bk_val + ((size_t)i << G.k);
@@ -1323,12 +1408,12 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join_walk(
   __syncthreads();
   if (lds)
     join_walk<R, true>(G, he, bk_off, bk_val, lds_ptr(t_off), lds_ptr(t_val), st, cand, cand_cap,
-                       waves, lds_ptr(outs));
+                       waves, lds_ptr(outs), &found);
   else
     join_walk<R, false>(G, he, bk_off, bk_val, lds_ptr(t_off), lds_ptr(t_val), st, cand, cand_cap,
                         reinterpret_cast<typename JoinWalk<R, false>::Wave *>(waves),
-                        lds_ptr(outs));
-  __syncthreads();
+                        lds_ptr(outs), &found);
+  found.flush(st, cand, cand_cap);                      // holds barriers
   if (threadIdx.x < R - 3 && outs[threadIdx.x])
     atomicAdd(&st->n_out[threadIdx.x + 2], (unsigned long long)outs[threadIdx.x]);
 }
@@ -1353,9 +1438,17 @@ __global__ __launch_bounds__(256) void k_estimate(Geom G, const uint32_t *__rest
   const uint32_t szmax = st->szmax;
   const double d = st->d;
   const uint32_t sub = threadIdx.x % S::LPL;
+  // a block's candidates per trip: every wave takes the same trips, and the
+  // block's reports of a trip take their places with one atomic (see CandBuf)
+  __shared__ uint32_t reports[2];
+  __shared__ unsigned long long place[2];
+  if (threadIdx.x < 2) reports[threadIdx.x] = 0;
+  __syncthreads();
   const uint64_t step = (uint64_t)gridDim.x * blockDim.x / S::LPL;
-  for (uint64_t base = ((uint64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63u)) / S::LPL;
-       base < nc; base += step) {
+  uint32_t trip = 0;
+  for (uint64_t block0 = (uint64_t)blockIdx.x * blockDim.x / S::LPL; block0 < nc;
+       block0 += step, trip ^= 1) {
+    const uint64_t base = block0 + (threadIdx.x & ~63u) / S::LPL;
     const uint64_t e = base + lane_id() / S::LPL;
     const bool valid = e < nc;
     const uint32_t a = valid ? cand[e] : 0u;
@@ -1405,7 +1498,17 @@ __global__ __launch_bounds__(256) void k_estimate(Geom G, const uint32_t *__rest
     }
     const uint32_t sz = G.g - ones;
     const bool report = valid && sub == 0 && sz <= szmax;
-    unsigned long long slot = wave_reserve(&st->n_spl, report ? 1u : 0u);
+    const unsigned long long rm = __ballot(report);
+    uint32_t at = 0;
+    if (lane_id() == 0 && rm) at = atomicAdd(&reports[trip], (uint32_t)__popcll(rm));
+    at = wave_lane(at, 0) + lanes_below(rm);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      place[trip] = reports[trip] ? atomicAdd(&st->n_spl, (unsigned long long)reports[trip]) : 0;
+      reports[trip ^ 1] = 0;                            // the next trip's, not yet in use
+    }
+    __syncthreads();
+    const unsigned long long slot = place[trip] + at;
     if (report && slot < spl_cap) {
       const double est = sz ? -(double)G.g * log((double)sz / d) : (double)INFINITY;
       const unsigned long long bits = __double_as_longlong(est);
@@ -1728,12 +1831,12 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
   mark(2);
   // 4-5: scalars and candidates
   if (lattice) {
-    // row 1's bitmap and the queues (above 64 KiB by the attribute that
-    // prepare_restore_kernels sets)
-    const size_t lds = ((size_t)4 << (k - 5)) + LAT_QUEUE_BYTES;
-    // half the usual grid: each block first copies row 1's bitmap
-    k_lattice<<<grid > 1 ? grid / 2 : 1, LAT_THREADS, lds, st>>>(
-        G, B.lat, B.cand_path, B.he, B.hotmask, B.st, B.cand, B.cand_cap, e_theta);
+    // the rows' bitmaps and the queues (above 64 KiB by the attribute that
+    // prepare_restore_kernels sets); two blocks per compute unit, each of
+    // which first copies the bitmaps
+    const uint32_t rows = lattice_rows(G), threads = lattice_threads(G, rows);
+    k_lattice<<<grid > 3 ? grid / 4 : 1, threads, lattice_lds(G, rows, threads), st>>>(
+        G, B.lat, B.cand_path, B.he, B.hotmask, B.st, B.cand, B.cand_cap, e_theta, rows);
   }
   if (join) launch_join(G, B, e_theta, st);
   mark(3);

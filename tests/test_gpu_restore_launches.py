@@ -160,3 +160,25 @@ def test_scans(p):
             sk.set_option(ddhf.SKETCH_OPT_UPDATE_PATH, 1)
             sk.update(to_dev(more))
             pairs = np.concatenate([pairs, more])
+
+
+@pytest.mark.parametrize("k,alpha,path,blocks,frac,m",
+                         [(14, 6, 2, 0, 0.17, 0)] +
+                         [(k, a, 1, 1, 0.0, m) for k, a in ((14, 6), (18, 5))
+                          for m in (512, 513, 700)])
+def test_candidates_past_the_block_buffer(k, alpha, path, blocks, frac, m):
+    """A search block keeps its first 512 candidates until it ends; the rest
+    go out one by one. k = 14 joins in one walk, k = 18 in stages; the crafted
+    sketch's lattice search finds more than 512 per block."""
+    p = oracle.Params(128, k, 5, alpha)
+    words = crafted_hot_sketch(p, frac, 11) if frac else hosts_sketch(p, m, 17)
+    say(f"candidates: k={p.k} path={path} frac={frac} hosts={m}")
+    with make_sketch(p) as sk:
+        sk.set_option(ddhf.SKETCH_OPT_CANDIDATES, path)
+        sk.set_option(ddhf.SKETCH_OPT_JOIN_BLOCKS, blocks)
+        sk.upload(words)
+        cand = sk.candidates(100.0)
+        recs, _ = sk.restore(100.0)
+    want = oracle.candidates(p, words, 100.0, "brute")
+    assert len(want) >= (500_000 if frac else m)
+    assert np.array_equal(cand, want) and np.array_equal(recs["ip"], want)
