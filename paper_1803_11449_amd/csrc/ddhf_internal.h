@@ -22,14 +22,14 @@ struct Geom {
   uint64_t a1, b1;   // H1 coefficients
 };
 
-// DH0: multiply-add-shift to k bits.
+// DH0: multiply-add-shift to k bits (the high word, shifted on: k <= 32).
 __device__ __forceinline__ uint32_t hash_dh0(const Geom &G, uint32_t x) {
-  return (uint32_t)((G.a0 * (uint64_t)x + G.b0) >> (64 - G.k));
+  return (uint32_t)((G.a0 * (uint64_t)x + G.b0) >> 32) >> (32 - G.k);
 }
 
 // H1: multiply-add-shift to log2(g) bits.
 __device__ __forceinline__ uint32_t hash_h1(const Geom &G, uint32_t y) {
-  return (uint32_t)((G.a1 * (uint64_t)y + G.b1) >> (64 - G.log2g));
+  return (uint32_t)((G.a1 * (uint64_t)y + G.b1) >> 32) >> (32 - G.log2g);
 }
 
 // BL(i): k bits of x starting at bit (i-1)*alpha (0 past bit 31): one bit
@@ -155,8 +155,13 @@ constexpr uint32_t BIN_TILE_BITS = BIN_TILE_WORDS * 32;
 constexpr uint32_t BIN_SLOTS = 4096;                 // tile slots of the per-block arrays
 constexpr uint32_t BIN_MAX = 3276;                   // tiles: a sketch bit index stays
                                                      // below 2^32 (BIN_MAX * BIN_TILE_BITS)
-// The tile of sketch bit index B (a division by a constant).
-__host__ __device__ __forceinline__ uint32_t bin_tile(uint32_t B) { return B / BIN_TILE_BITS; }
+// The tile of sketch bit index B: B / BIN_TILE_BITS, which is 5 * 2^18, as
+// a 24-bit multiply by 2^18/5 of the 14 bits above (exact for all of them),
+// at full rate where the 32-bit high half takes four slots.
+__host__ __device__ __forceinline__ uint32_t bin_tile(uint32_t B) {
+  static_assert(BIN_TILE_BITS == 5u << 18, "the division by 5");
+  return ((B >> 18) * 52429u) >> 18;
+}
 constexpr uint32_t SPLIT_MIN = 1u << 18;             // tiles above this many code words
 constexpr uint32_t APPLY_ITEM = 1u << 17;            //   are cut into items of this many
 

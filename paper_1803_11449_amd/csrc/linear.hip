@@ -69,12 +69,6 @@ __device__ __forceinline__ void tile_out(const UpdJob &J, const uint32_t *tile, 
 
 // ----------------------------------------------------------------- scatter
 
-// The value kept per bit set: tile over code, as in the region scatter.
-__device__ __forceinline__ uint32_t lin_value(uint32_t B, uint32_t ts) {
-  const uint32_t S = B << ts, t = bin_tile(S);
-  return (t << CODE_BITS) | ((S - __umul24(t, BIN_TILE_BITS)) >> ts);
-}
-
 // Each block takes J.chunk consecutive batches of 1024 * PPT pairs. Per
 // batch: the codes' ranks inside their tile's run (LDS atomics), the runs'
 // starts by one wave's scan over the tiles, the codes grouped by tile in
@@ -83,25 +77,33 @@ __device__ __forceinline__ uint32_t lin_value(uint32_t B, uint32_t ts) {
 // by the scan that reads it, and the next batch's first LDS write to the
 // sorted codes follows a barrier that every wave reaches after its last
 // read of them.
+template <int R, int PPT>
+struct LinLds {
+  uint32_t cnt[LIN_TILES], lofs[LIN_TILES], n_words;
+  Filter<lin_filters(PPT) ? LIN_FILT_WORDS : 32> filt;
+  uint32_t sorted[LIN_THREADS * PPT * R + 2 * LIN_TILES];
+};
+
 template <int R, int PPT, bool ONE>
 __global__ __launch_bounds__(LIN_THREADS) void k_lin_scatter(JobArg A) {
   constexpr uint32_t BATCH = LIN_THREADS * PPT;
   constexpr bool FILT = lin_filters(PPT);
-  __shared__ Filter<FILT ? LIN_FILT_WORDS : 32> filt;
-  __shared__ uint32_t sorted[BATCH * R + 2 * LIN_TILES];
-  __shared__ uint32_t cnt[LIN_TILES], lofs[LIN_TILES];
-  __shared__ uint32_t n_words;
+  static_assert(sizeof(LinLds<R, PPT>) <= 163840, "the LDS of a workgroup");
+  __shared__ LinLds<R, PPT> L;
+  uint32_t *const cnt = L.cnt, *const lofs = L.lofs, *const sorted = L.sorted;
+  auto &filt = L.filt;
+  uint32_t &n_words = L.n_words;
   const UpdJob &J = job_of<ONE>(
       A, [](const UpdJob *t, uint32_t n) { return job_of_block(t, n, blockIdx.x); });
   const Geom G = J.G;
   const uint32_t ts = J.tshift, lb = blockIdx.x - J.blk0;
   const GMEM uint2 *__restrict__ pairs = gmem(J.pairs);
-  GMEM uint64_t *__restrict__ words = gmem(reinterpret_cast<uint64_t *>(J.codes));
+  GMEM uint2 *__restrict__ words = gmem(reinterpret_cast<uint2 *>(J.codes));
   GMEM uint16_t *__restrict__ dir = gmem(J.dir);
   const uint32_t n = (uint32_t)J.n;                     // a round's pairs: at most 2^28
   const uint32_t wcap = J.wcap;
   if (threadIdx.x < LIN_TILES) cnt[threadIdx.x] = 0;
-  if constexpr (FILT) filt.clear();
+  if constexpr (FILT) filt.clear(G);
   __syncthreads();
   uint32_t b = lb * (uint32_t)J.chunk;
   const uint32_t b1 = b + (uint32_t)J.chunk < J.nbatch ? b + (uint32_t)J.chunk : J.nbatch;
@@ -114,41 +116,33 @@ __global__ __launch_bounds__(LIN_THREADS) void k_lin_scatter(JobArg A) {
 #pragma unroll
     for (int k = 0; k < PPT; k++) {
       const uint32_t i = bb * BATCH + (uint32_t)k * LIN_THREADS + tid;
-      pr[k] = ld2(pairs + (i < n ? i : n - 1));
+      pr[k] = ld2(pairs + min(i, n - 1));
     }
   };
   load(b);
   const uint32_t b0 = b;
-  bool filtering = FILT;                                // uniform over the block
+  bool filtering = FILT && filt.fits(G);               // uniform over the block
   for (; b < b1; b++) {
     uint32_t tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    uint32_t x[PPT], B0[PPT], live = 0;
+    uint32_t x[PPT], B0[PPT], live = (1u << PPT) - 1;
 #pragma unroll
     for (int k = 0; k < PPT; k++) {
       x[k] = pr[k].x;
       B0[k] = pair_code0(G, pr[k]);
-      if (b * BATCH + (uint32_t)k * LIN_THREADS + tid < n) live |= 1u << k;
     }
     load(b + 1 < b1 ? b + 1 : b);
-    if constexpr (FILT) {
-      if (filtering) live &= ~filt.template repeats<PPT>(G, x, B0, live, b - b0);
+    if ((b + 1) * BATCH > n) {                          // the window's last batch
+#pragma unroll
+      for (int k = 0; k < PPT; k++)
+        if (b * BATCH + (uint32_t)k * LIN_THREADS + tid >= n) live &= ~(1u << k);
+    } else if (FILT && filtering) {
+      live &= ~filt.template repeats<PPT>(G, x, B0, b - b0);
     }
-    // the codes of live pairs; a dropped pair's are not used, and leave its
-    // halves of the rank registers zero
+    // ranks are < BATCH * R <= 2^15: two per register (a dropped pair's codes
+    // are not used, and leave its halves zero)
     uint32_t v[PPT * R], rk2[(PPT * R + 1) / 2] = {};
-#pragma unroll
-    for (int k = 0; k < PPT; k++) {
-      if ((live >> k) & 1u) {
-        uint32_t B[R];
-        codes_of<R>(G, x[k], B0[k], B);
-#pragma unroll
-        for (int row = 0; row < R; row++) {
-          v[k * R + row] = lin_value(B[row], ts);
-          put_rank(rk2, k * R + row, atomicAdd(&cnt[v[k * R + row] >> CODE_BITS], 1u));
-        }
-      }
-    }
+    rank_codes<R, PPT, true>(G, x, B0, live, ts, cnt, v, rk2);   // in tiles of 160 KiB >> ts
     __syncthreads();
     if (tid < 64) {
       constexpr uint32_t TPL = LIN_TILES / 64;          // tiles per lane
@@ -177,26 +171,18 @@ __global__ __launch_bounds__(LIN_THREADS) void k_lin_scatter(JobArg A) {
       }
     }
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PPT; k++) {
-      if ((live >> k) & 1u) {
-#pragma unroll
-        for (int q = k * R; q < (k + 1) * R; q++)
-          sorted[lofs[v[q] >> CODE_BITS] + get_rank(rk2, q)] = v[q];
-      }
-    }
+    group_codes<R, PPT, true>(live, v, rk2, lofs, sorted);
     __syncthreads();
     if constexpr (FILT) {
       if (b - b0 == FILT_CLAIM) filtering = filt.useful(BATCH);
     }
     const uint32_t nw = n_words;
-    GMEM uint64_t *out = words + (size_t)b * wcap;
+    GMEM uint2 *out = words + (size_t)b * wcap;
     for (uint32_t j = tid; j < nw; j += LIN_THREADS) {
       // the word's first slot always holds a code and stands in for a pad
       const uint32_t x = sorted[3 * j], y0 = sorted[3 * j + 1], z0 = sorted[3 * j + 2];
       const uint32_t y = y0 == ~0u ? x : y0, z = z0 == ~0u ? x : z0;
-      out[j] = (uint64_t)(x & CODE_MASK) | ((uint64_t)(y & CODE_MASK) << CODE_BITS) |
-               ((uint64_t)(z & CODE_MASK) << (2 * CODE_BITS));
+      st2(out + j, code_word(x, y, z));
     }
   }
 }
@@ -238,7 +224,7 @@ __global__ __launch_bounds__(LIN_THREADS) void k_lin_apply(JobArg A, uint32_t ti
     // wave-uniform, so that the walk over the runs is scalar work
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t wcap = J.wcap, nb = J.nbatch;
+    const uint32_t wcap = J.wcap, nb = J.nbatch, ts = J.tshift;
     const uint32_t runs = nb > wv ? (nb - wv + WAVES - 1) / WAVES : 0;   // this wave's
     for (uint32_t i0 = 0; i0 < runs; i0 += 64) {
       uint32_t start = 0, len = 0;                      // run i0 + lane of the wave
@@ -274,7 +260,7 @@ __global__ __launch_bounds__(LIN_THREADS) void k_lin_apply(JobArg A, uint32_t ti
       while (n[0]) {
 #pragma unroll
         for (int u = 0; u < LIN_DEPTH; u++) {
-          if (lane < n[u]) or_word(ltile, x[u]);
+          if (lane < n[u]) or_word(ltile, x[u], ts);
           fetch(u);
         }
       }

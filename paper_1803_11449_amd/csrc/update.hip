@@ -55,7 +55,9 @@ __device__ __forceinline__ void count_pair(const Geom &G, uint2 p, uint32_t *h) 
   uint32_t B[R];
   pair_codes<R>(G, p, B);
 #pragma unroll
-  for (int row = 0; row < R; row++) atomicAdd(&h[bin_tile(B[row])], 1u);
+  for (int row = 0; row < R; row++) atomicAdd(at4(h, tile4_of(B[row])), 1u);
+  // one pair at a time under the register cap (see count_waves_per_eu)
+  if constexpr (R == 4) __builtin_amdgcn_sched_barrier(0);
 }
 
 // Codes are stored three to a 64-bit word (bits 0-20, 21-41, 42-62), and
@@ -409,46 +411,62 @@ constexpr int SCATTER_UNROLL = 4;
 // window's end or a pad slot) is neither.
 template <int TMAX> struct ScatterValue {
   static constexpr bool SPLIT = TMAX <= 2048;
-  __device__ __forceinline__ static uint32_t make(uint32_t B) {
-    if constexpr (SPLIT) {
-      const uint32_t t = bin_tile(B);
-      return (t << CODE_BITS) | (B - t * BIN_TILE_BITS);
-    } else {
-      return B;
-    }
+  __device__ __forceinline__ static uint32_t tile4(uint32_t v) {
+    if constexpr (SPLIT) return tile4_of_code(v);
+    else return tile4_of(v);
   }
-  __device__ __forceinline__ static uint32_t tile(uint32_t v) {
-    if constexpr (SPLIT) return v >> CODE_BITS;
-    else return bin_tile(v);
-  }
-  __device__ __forceinline__ static uint32_t code(uint32_t v, uint32_t t) {
-    if constexpr (SPLIT) return v & CODE_MASK;
-    else return v - t * BIN_TILE_BITS;
+  __device__ __forceinline__ static uint32_t code(uint32_t v, uint32_t t4) {
+    if constexpr (SPLIT) return v;                      // code_word masks it
+    else return v - (t4 >> 2) * BIN_TILE_BITS;
   }
 };
 
 // TMAX: tiles the LDS arrays hold (1024, 2048, 3072 or 4096), at least the
-// jobs' tiles.
+// jobs' tiles. Up to 2048 tiles the block drops repeated pairs (Filter, in
+// update_dev.h), with as many slots as the LDS leaves: 128 sources at
+// g = 1024 beside 1024 tiles, 64 beside 2048.
+template <int TMAX> constexpr uint32_t region_filter_words() {
+  return TMAX == 1024 ? 4096 : TMAX == 2048 ? 2048 : 0;
+}
+
+// The scatter's LDS, at most 160 KiB for every (R, PPT, TMAX) the launcher
+// picks.
+template <int R, int PPT, int TMAX>
+struct ScatterLds {
+  static constexpr uint32_t BATCH = 1024 * PPT * R;
+  static constexpr uint32_t FW = region_filter_words<TMAX>();
+  // batch-local run starts (multiples of 3); 32 bits where there is room
+  using Ofs = std::conditional_t<TMAX == 1024, uint32_t, uint16_t>;
+  // codes per tile in this batch. With more than one tile per thread the
+  // counts give their place to dst once read (each thread its own tiles'),
+  // and are cleared after the batch
+  uint32_t cnt[TMAX];
+  uint32_t dst_own[TMAX == 1024 ? TMAX : 1];
+  Ofs lofs[TMAX];
+  uint32_t sh[16];                     // the block scan's
+  Filter<FW ? FW : 32> filt;
+  // a batch's codes grouped by tile, each run padded to whole words (at
+  // most 2 pad slots per tile)
+  uint32_t sorted[BATCH + 2 * TMAX];
+};
+
 template <int R, int PPT, int TMAX>
 __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__ jobs,
                                                       uint32_t nj) {
-  constexpr uint32_t BATCH = 1024 * PPT * R;
+  using Lds = ScatterLds<R, PPT, TMAX>;
+  static_assert(sizeof(Lds) <= 163840, "the LDS of a workgroup");
   constexpr uint32_t TPT = TMAX / 1024;                // tiles per thread
+  constexpr bool FILT = Lds::FW != 0;
   using SV = ScatterValue<TMAX>;
-  // a batch's codes grouped by tile, each run padded to whole words (at
-  // most 2 pad slots per tile); with the three tile arrays this is at most
-  // 160 KiB for every (R, PPT, TMAX) the launcher picks
-  __shared__ uint32_t sorted[BATCH + 2 * TMAX];
-  __shared__ uint32_t cnt[TMAX];       // codes per tile in this batch
-  __shared__ uint32_t lofs[TMAX];      // batch-local run starts (multiples of 3)
-  __shared__ uint32_t dst[TMAX];       // word slot of batch word j is dst[t] + j
-  // the block scan's 16 words: dst is not in use from the end of a batch
-  // until step 3 of the next
-  uint32_t *const sh = dst;
+  __shared__ Lds L;
+  uint32_t *const cnt = L.cnt, *const sorted = L.sorted;
+  uint32_t *const dst = TPT > 1 ? L.cnt : L.dst_own;   // word slot of batch word j is dst[t] + j
+  auto *const lofs = L.lofs;
+  auto &filt = L.filt;
   const UpdJob &J = jobs[job_of_block(jobs, nj, blockIdx.x)];
   const Geom G = J.G;
   const uint32_t lb = blockIdx.x - J.blk0;
-  GMEM uint64_t *__restrict__ words = gmem(reinterpret_cast<uint64_t *>(J.codes));
+  GMEM uint2 *__restrict__ words = gmem(reinterpret_cast<uint2 *>(J.codes));
   // this block's group's regions, one per tile: claim cursors and ends (in
   // words from the job's codes)
   const size_t grow = (size_t)(blockIdx.x % BIN_GROUPS) * J.nbins;
@@ -456,6 +474,7 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
   GMEM uint32_t *gcur = gmem(J.gcur) + grow;
   const GMEM uint32_t *rend = gmem(TS.capg) + grow;
   for (uint32_t t = threadIdx.x; t < TMAX; t += blockDim.x) cnt[t] = 0;
+  if constexpr (FILT) filt.clear(G);
   __syncthreads();
   const size_t p0 = (size_t)lb * J.chunk;
   const size_t p1 = p0 + J.chunk < J.n ? p0 + J.chunk : J.n;
@@ -465,79 +484,73 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
   const uint32_t n = (uint32_t)(p1 - p0);
   constexpr uint32_t step = 1024 * PPT;
   // A batch's pairs are held in pr. The next batch's pairs are loaded into
-  // pr as soon as this batch's codes are made (step 1), so they are in
-  // flight through the claims and the scan (and, with one tile per thread,
-  // the grouping: the first wait that covers them is the one for the
-  // claims, see step 2), and no second set of registers is live. Loads past
-  // the chunk re-read its last pair (their lanes are masked later): with no
-  // branch around them the compiler need not wait for every load in flight.
+  // pr as soon as this batch's row-0 codes are made, so they are in flight
+  // through the claims and the scan (and, with one tile per thread, the
+  // grouping: the first wait that covers them is the one for the claims, see
+  // step 2). Loads past the chunk re-read its last pair (masked later): with
+  // no branch around them the compiler need not wait for every load in
+  // flight.
   uint2 pr[PPT];
   auto load = [&](uint32_t b0, uint32_t tid) {
 #pragma unroll
     for (int k = 0; k < PPT; k++) {
       const uint32_t i = b0 + (uint32_t)k * 1024 + tid;
-      pr[k] = ld2(pairs + (i < n ? i : n - 1));
+      pr[k] = ld2(pairs + min(i, n - 1));
     }
   };
-  // One batch: the pairs [i0, i0 + step) of the chunk, held in pr. A full
-  // batch (FULL) has all its pairs and takes no per-pair bounds test; only
-  // a chunk's last batch can be partial, and its missing pairs get the
-  // code ~0.
-  auto batch = [&](auto full_c, uint32_t i0) {
-    constexpr bool FULL = decltype(full_c)::value;
+  load(0, threadIdx.x);
+  bool filtering = FILT && filt.fits(G);               // uniform over the block
+  uint32_t nth = 0;                                     // batches done
+  for (uint32_t i0 = 0; i0 < n; i0 += step, nth++) {
     // The thread index is taken afresh per batch, so that addresses derived
     // from it are recomputed here rather than held in registers (or spilled)
     // across the batch loop.
     uint32_t tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const uint32_t t0 = tid * TPT;                      // tiles this thread keeps
-    // ranks are < BATCH <= 2^15: two per register
-    uint32_t v[PPT * R], rk2[(PPT * R + 1) / 2];
-    // 1: codes and their rank inside their tile's run of this batch (an
-    // LDS atomic that returns the rank; a plain count here and a returning
-    // placement cursor in step 3 instead was slower: 692 against 608 us
-    // for the 100M-pair window)
+    // 1: row-0 codes; the pairs that exist and do not repeat; their codes
+    // and each code's rank inside its tile's run of this batch
+    uint32_t x[PPT], B0[PPT], live = (1u << PPT) - 1;
 #pragma unroll
     for (int k = 0; k < PPT; k++) {
-      const uint32_t i = i0 + (uint32_t)k * 1024 + tid;
-      if (FULL || i < n) {
-        uint32_t B[R];
-        pair_codes<R>(G, pr[k], B);
-#pragma unroll
-        for (int row = 0; row < R; row++) {
-          v[k * R + row] = SV::make(B[row]);
-          put_rank(rk2, k * R + row, atomicAdd(&cnt[SV::tile(v[k * R + row])], 1u));
-        }
-      } else {
-#pragma unroll
-        for (int row = 0; row < R; row++) v[k * R + row] = ~0u;
-      }
+      x[k] = pr[k].x;
+      B0[k] = pair_code0(G, pr[k]);
     }
     load(i0 + step, tid);
+    if (i0 + step > n) {                                // the chunk's last batch
+#pragma unroll
+      for (int k = 0; k < PPT; k++)
+        if (i0 + (uint32_t)k * 1024 + tid >= n) live &= ~(1u << k);
+    } else if (filtering) {
+      live &= ~filt.template repeats<PPT>(G, x, B0, nth);
+    }
+    // ranks are < BATCH <= 2^15: two per register (a dropped pair's codes
+    // are not used, and leave its halves zero)
+    uint32_t v[PPT * R], rk2[(PPT * R + 1) / 2] = {};
+    rank_codes<R, PPT, SV::SPLIT>(G, x, B0, live, 0, cnt, v, rk2);
     __syncthreads();
     // 2: claim each tile's run, ceil(c / 3) words, in the group's region,
     // and read the region's end; run starts; the pad slots of each run get
-    // the marker ~0. The counts stay in cnt. With one tile per thread the
-    // claimed start stays in a register until after the grouping, so the
-    // wait for the atomic's return (and, the counter being in order, for
-    // the next batch's pairs) falls behind the scan and step 3, not before
-    // them; with more tiles per thread the claimed positions wait in dst
-    // (the scan is done with it): held in registers through the grouping
-    // they would not fit the 6-pair, 5-row variant
-    uint32_t run[TPT], end[TPT], sum = 0;
+    // the marker ~0. With one tile per thread the claimed start stays in a
+    // register until after the grouping, so the wait for the atomic's return
+    // (and, the counter being in order, for the next batch's pairs) falls
+    // behind the scan and step 3, not before them; with more tiles per
+    // thread the claimed positions wait in dst: held in registers through
+    // the grouping they would not fit the 6-pair, 5-row variant
+    uint32_t run[TPT], end[TPT], wd[TPT], sum = 0;
 #pragma unroll
     for (uint32_t u = 0; u < TPT; u++) {
-      const uint32_t w = (cnt[t0 + u] + 2) / 3;       // 0 for the slots past the tiles
-      sum += 3 * w;
-      run[u] = w ? atomicAdd((uint32_t *)&gcur[t0 + u], w) : 0;
-      end[u] = w ? rend[t0 + u] : 0;
+      wd[u] = (cnt[t0 + u] + 2) / 3;                    // 0 for the slots past the tiles
+      sum += 3 * wd[u];
+      run[u] = wd[u] ? atomicAdd((uint32_t *)&gcur[t0 + u], wd[u]) : 0;
+      end[u] = wd[u] ? rend[t0 + u] : 0;
     }
     uint32_t total;
-    uint32_t ex = blk_scan_1024(sum, &total, sh, tid);
+    uint32_t ex = blk_scan_1024(sum, &total, L.sh, tid);
 #pragma unroll
     for (uint32_t u = 0; u < TPT; u++) {
-      const uint32_t t = t0 + u, c = cnt[t], padded = 3 * ((c + 2) / 3);
-      lofs[t] = ex;
+      const uint32_t t = t0 + u, c = cnt[t], padded = 3 * wd[u];
+      lofs[t] = (typename Lds::Ofs)ex;
       if constexpr (TPT > 1) dst[t] = run[u];
       if (padded > c) sorted[ex + c] = ~0u;             // at most two pad slots
       if (padded > c + 1) sorted[ex + c + 1] = ~0u;
@@ -545,14 +558,7 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
     }
     __syncthreads();
     // 3: group by tile in LDS; dst maps a batch word to its word slot
-#pragma unroll
-    for (int q = 0; q < PPT * R; q++) {
-      if (FULL || v[q] != ~0u) sorted[lofs[SV::tile(v[q])] + get_rank(rk2, q)] = v[q];
-      // with more tiles per thread the registers do not hold every code's
-      // run start at once
-      if constexpr (TPT > 1)
-        if (q % 10 == 9) __builtin_amdgcn_sched_barrier(0);
-    }
+    group_codes<R, PPT, SV::SPLIT>(live, v, rk2, lofs, sorted);
     tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     // a run that fits its region goes there; one that does not goes whole
@@ -561,8 +567,8 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
 #pragma unroll
     for (uint32_t u = 0; u < TPT; u++) {
       const uint32_t t = tid * TPT + u;
-      const uint32_t w = (cnt[t] + 2) / 3;
-      cnt[t] = 0;                                       // for the next batch
+      const uint32_t w = wd[u];
+      if constexpr (TPT == 1) cnt[t] = 0;               // for the next batch
       if (!w) continue;
       const uint32_t pos = TPT > 1 ? dst[t] : run[u];
       uint32_t at = pos;
@@ -577,6 +583,9 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
       dst[t] = at - lofs[t] / 3;
     }
     __syncthreads();
+    if constexpr (FILT) {
+      if (nth == FILT_CLAIM) filtering = filt.useful(step);
+    }
     // 4: write the words; batch word j holds sorted slots 3j..3j+2, whose
     // first is always a code of the run and stands in for a pad (a code
     // set twice sets the same bit)
@@ -584,10 +593,8 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
     auto put = [&](uint32_t j) {
       const uint32_t x = sorted[3 * j], y0 = sorted[3 * j + 1], z0 = sorted[3 * j + 2];
       const uint32_t y = y0 == ~0u ? x : y0, z = z0 == ~0u ? x : z0;
-      const uint32_t t = SV::tile(x);                   // the word's three share it
-      const uint64_t wv = (uint64_t)SV::code(x, t) | ((uint64_t)SV::code(y, t) << CODE_BITS) |
-                          ((uint64_t)SV::code(z, t) << (2 * CODE_BITS));
-      words[dst[t] + j] = wv;
+      const uint32_t t4 = SV::tile4(x);                 // the word's three share it
+      st2(words + (*at4(dst, t4) + j), code_word(SV::code(x, t4), SV::code(y, t4), SV::code(z, t4)));
     };
     uint32_t j = tid;
     for (; j + (SCATTER_UNROLL - 1) * 1024 < nw; j += SCATTER_UNROLL * 1024) {
@@ -596,11 +603,11 @@ __global__ __launch_bounds__(1024) void k_bin_scatter(const UpdJob *__restrict__
     }
     for (; j < nw; j += 1024) put(j);
     __syncthreads();
-  };
-  load(0, threadIdx.x);
-  uint32_t i0 = 0;
-  for (; i0 + step <= n; i0 += step) batch(std::true_type{}, i0);
-  if (i0 < n) batch(std::false_type{}, i0);
+    if constexpr (TPT > 1) {                            // dst gives the counts their place back
+      for (uint32_t u = 0; u < TPT; u++) cnt[tid * TPT + u] = 0;
+      __syncthreads();
+    }
+  }
 }
 
 constexpr int APPLY_UNROLL = 4;

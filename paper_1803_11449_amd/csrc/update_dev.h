@@ -28,6 +28,11 @@ __device__ __forceinline__ uint4 ld4(const GMEM uint4 *p) {
   const v4u v = *reinterpret_cast<const GMEM v4u *>(p);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ void st2(GMEM uint2 *p, uint2 x) {
+  v2u v;
+  v.x = x.x; v.y = x.y;
+  *reinterpret_cast<GMEM v2u *>(p) = v;
+}
 __device__ __forceinline__ void st4(GMEM uint4 *p, uint4 x) {
   v4u v;
   v.x = x.x; v.y = x.y; v.z = x.z; v.w = x.w;
@@ -71,12 +76,40 @@ constexpr uint32_t CODE_MASK = (1u << CODE_BITS) - 1;
 __device__ __forceinline__ uint32_t pair_code0(const Geom &G, uint2 p) {
   return (hash_dh0(G, p.x) << G.log2g) | hash_h1(G, p.y);
 }
+// (ts: every index, B0 among them, times 2^ts)
 template <int R>
-__device__ __forceinline__ void codes_of(const Geom &G, uint32_t x, uint32_t B0, uint32_t *B) {
+__device__ __forceinline__ void codes_of(const Geom &G, uint32_t x, uint32_t B0, uint32_t *B,
+                                         uint32_t ts = 0) {
   B[0] = B0;
 #pragma unroll
   for (int row = 1; row < R; row++)
-    B[row] = ((uint32_t)row << (G.k + G.log2g)) | (B0 ^ (bit_block(G, row, x) << G.log2g));
+    B[row] = ((uint32_t)row << (G.k + G.log2g + ts)) |
+             (B0 ^ (bit_block(G, row, x) << (G.log2g + ts)));
+}
+
+// Four times the tile of bit index S (see bin_tile): the byte offset of its
+// entry in an array of words.
+__device__ __forceinline__ uint32_t tile4_of(uint32_t S) {
+  return (__umul24(S >> 18, 52429u) >> 16) & ~3u;
+}
+// A bit set as the scatters keep it, its tile over its code (up to 2048
+// tiles): one multiply-add on the index, S - t * BIN_TILE_BITS + t * 2^CODE_BITS.
+__device__ __forceinline__ uint32_t tile_code(uint32_t S, uint32_t t4) {
+  return S + __umul24(t4, ((1u << CODE_BITS) - BIN_TILE_BITS) / 4);
+}
+__device__ __forceinline__ uint32_t tile4_of_code(uint32_t v) {
+  return (v >> (CODE_BITS - 2)) & ~3u;
+}
+// The LDS word at a byte offset from base.
+__device__ __forceinline__ uint32_t *at4(uint32_t *base, uint32_t bytes) {
+  return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(base) + bytes);
+}
+// Three of them to a code word. Bits above a field that the next field or
+// the word's end does not take are left as they come: the apply masks them.
+__device__ __forceinline__ uint2 code_word(uint32_t a, uint32_t b, uint32_t c) {
+  return make_uint2((a & CODE_MASK) | (b << CODE_BITS),
+                    __builtin_amdgcn_ubfe(b, 32 - CODE_BITS, 2 * CODE_BITS - 32) |
+                        (c << (2 * CODE_BITS - 32)));
 }
 
 // A pair's bit set in every row, as sketch bit indexes (< 2^32: a binned
@@ -98,46 +131,75 @@ __device__ __forceinline__ void pair_codes(const Geom &G, uint2 p, uint32_t *B) 
 // the words that pile up on the busiest source's tiles, whose workgroups
 // the apply pass otherwise waits for: 4M pairs at g = 512, r = 4 (Zipf 1.1),
 // apply 73 -> 27 us for 4 us more in the scatter; 15M pairs at k = 16 (Zipf
-// 1.0), 139 -> 79 us for 15 us. A table shared by the blocks of an XCD drops
+// 1.0), 139 -> 79 us for 15 us; in the regions, 100M pairs (Zipf 1.0, 128
+// slots) apply and merge 396 -> 333 us, 190M pairs (Zipf 1.1, 64 slots) 745 ->
+// 515 us, for about a tenth of the scatter. A table shared by the blocks of an XCD drops
 // more (15M pairs: apply 66 us) but its busiest lines are read by every
 // wave: the scatter went from 85 to 650 us and more.
 //
 // Slots are claimed in a block's first FILT_CLAIM batches only (in every
 // batch it cost twice as much). The next batch's drops are counted, and a
-// block where fewer than one pair in 32 repeats goes on without the filter.
-constexpr uint32_t FILT_FREE = 0xFFFFFFFFu;             // no source: passes unfiltered
+// block where fewer than one pair in FILT_WORTH repeats goes on without the
+// filter, whose lookups take about a tenth of the scatter.
+//
+// An unowned slot holds a source that belongs to another slot, so that one
+// compare tells a pair's source from every other owner and from none.
 constexpr uint32_t FILT_CLAIM = 1;
+constexpr uint32_t FILT_WORTH = 32;
 
 template <uint32_t WORDS>
 struct Filter {
   static constexpr uint32_t SLOTS = WORDS / 32;         // at most, for LEs of 32 words and less
-  uint32_t bits[WORDS + 64], own[SLOTS], last[SLOTS], drops;
+  uint32_t bits[WORDS], own[SLOTS], last[SLOTS], drops;
 
-  __device__ __forceinline__ void clear() {
-    for (uint32_t i = threadIdx.x; i < WORDS + 64; i += blockDim.x) bits[i] = 0;
-    for (uint32_t i = threadIdx.x; i < SLOTS; i += blockDim.x) own[i] = last[i] = FILT_FREE;
+  // slots - 1: as many as SLOTS and the words allow (WORDS >= 2048, the
+  // largest LE)
+  __device__ __forceinline__ static uint32_t mask(const Geom &G) {
+    return (G.wpl <= 32 ? SLOTS : WORDS / G.wpl) - 1;
+  }
+  // The source an unowned slot holds: 0, or in 0's own slot the next one of
+  // another (there is no other with one slot: 0 then passes for its owner,
+  // and other sources may claim the slot, whose bits are then theirs and
+  // source 0's alike, so one-slot filters are not used).
+  __device__ __forceinline__ static uint32_t stranger(const Geom &G) {
+    const uint32_t m = mask(G), s0 = hash_dh0(G, 0) & m;
+    uint32_t z = 1;
+    while (z < 4096 && (hash_dh0(G, z) & m) == s0) z++;
+    return z;
+  }
+  // Whether the sketch's LEs leave slots to tell apart.
+  __device__ __forceinline__ static bool fits(const Geom &G) {
+    return mask(G) != 0 && (hash_dh0(G, stranger(G)) & mask(G)) != (hash_dh0(G, 0) & mask(G));
+  }
+  __device__ __forceinline__ void clear(const Geom &G) {
+    const uint32_t z = stranger(G), s0 = hash_dh0(G, 0) & mask(G);
+    for (uint32_t i = threadIdx.x; i < WORDS; i += blockDim.x) bits[i] = 0;
+    for (uint32_t i = threadIdx.x; i < SLOTS; i += blockDim.x)
+      own[i] = last[i] = i == s0 ? z : 0u;
     if (threadIdx.x == 0) drops = 0;
   }
   // Which of N pairs (sources x, row-0 bit indexes B0) repeat an earlier one:
-  // bit k of the result. live: the pairs that exist. The lookups, and the
-  // test-and-sets, of all N go out together: a lane without an owned slot
-  // sets nothing in a word of its own.
+  // bit k of the result. Every lane has N pairs of its own (a pair given
+  // twice drops the one that is written). The lookups, and the
+  // test-and-sets, of all N go out together; a lane without an owned slot
+  // sets nothing, in any word. A slot's bits are the low bits of its source's
+  // row-0 bit index: slot over H1's bit.
   template <int N>
   __device__ __forceinline__ uint32_t repeats(const Geom &G, const uint32_t *x,
-                                              const uint32_t *B0, uint32_t live,
-                                              uint32_t batch) {
-    const uint32_t mask = (G.wpl <= 32 ? SLOTS : WORDS / G.wpl) - 1;   // WORDS >= 2048, the largest LE
+                                              const uint32_t *B0, uint32_t batch) {
+    const uint32_t ms = mask(G), mb = (ms << G.log2g) | (G.g - 1);
     uint32_t o[N], seen = 0;
 #pragma unroll
-    for (int k = 0; k < N; k++) o[k] = own[(B0[k] >> G.log2g) & mask];
+    for (int k = 0; k < N; k++) o[k] = own[(B0[k] >> G.log2g) & ms];
     if (batch < FILT_CLAIM) {                           // uniform over the block
+      const uint32_t z = stranger(G), s0 = hash_dh0(G, 0) & ms;
 #pragma unroll
       for (int k = 0; k < N; k++) {
-        const uint32_t slot = (B0[k] >> G.log2g) & mask;
-        if (((live >> k) & 1u) && x[k] != FILT_FREE && o[k] == FILT_FREE) {
+        const uint32_t slot = (B0[k] >> G.log2g) & ms, unowned = slot == s0 ? z : 0u;
+        if (o[k] == unowned) {
           if (last[slot] == x[k]) {
-            const uint32_t old = atomicCAS(&own[slot], FILT_FREE, x[k]);
-            o[k] = old == FILT_FREE ? x[k] : old;
+            const uint32_t old = atomicCAS(&own[slot], unowned, x[k]);
+            o[k] = old == unowned ? x[k] : old;
           } else {
             last[slot] = x[k];
           }
@@ -147,10 +209,8 @@ struct Filter {
     uint32_t old[N], m[N];
 #pragma unroll
     for (int k = 0; k < N; k++) {
-      const uint32_t slot = (B0[k] >> G.log2g) & mask, bit = B0[k] & (G.g - 1);
-      const bool mine = o[k] == x[k] && x[k] != FILT_FREE && ((live >> k) & 1u);
-      m[k] = mine ? 1u << (bit & 31) : 0u;
-      old[k] = atomicOr(&bits[mine ? slot * G.wpl + (bit >> 5) : WORDS + (threadIdx.x & 63)], m[k]);
+      m[k] = o[k] == x[k] ? 1u << (B0[k] & 31) : 0u;
+      old[k] = atomicOr(&bits[(B0[k] & mb) >> 5], m[k]);
     }
 #pragma unroll
     for (int k = 0; k < N; k++) seen |= (old[k] & m[k]) ? 1u << k : 0u;
@@ -158,7 +218,9 @@ struct Filter {
     return seen;
   }
   // After a barrier that follows batch FILT_CLAIM: whether to go on.
-  __device__ __forceinline__ bool useful(uint32_t pairs) const { return drops * 32 >= pairs; }
+  __device__ __forceinline__ bool useful(uint32_t pairs) const {
+    return drops * FILT_WORTH >= pairs;
+  }
 };
 
 // Two 16-bit ranks per register (q is a compile-time index after unrolling).
@@ -168,6 +230,58 @@ __device__ __forceinline__ void put_rank(uint32_t *rk2, int q, uint32_t r) {
 }
 __device__ __forceinline__ uint32_t get_rank(const uint32_t *rk2, int q) {
   return (q & 1) ? rk2[q >> 1] >> 16 : rk2[q >> 1] & 0xFFFFu;
+}
+
+// The two steps of a scatter batch that touch every code. The scatters are
+// bound by vector instructions and LDS cycles about alike, so both are
+// written for few of the former: byte offsets instead of indexes, LDS arrays
+// whose addresses fit an instruction's offset (the arrays that are looked up
+// come first in LDS, the sorted codes last), one multiply-add for tile and
+// code: 33 -> 23 vector instructions per code, 604 -> 575 us for the 100M-pair
+// window's scatter with its filter. (With the vector ALU at about half its
+// issue slots and LDS at about half its cycles, what is left is that the
+// waves of a block go through the phases together.) SPLIT: values are tile_code's, else bit indexes.
+//
+// Codes of the live pairs (bit k of live; x: sources, B0: row-0 bit indexes),
+// and each one's rank inside its tile's run: an LDS atomic that returns it
+// (a plain count here and a returning placement cursor in the grouping was
+// slower: 692 against 608 us for the 100M-pair window).
+template <int R, int PPT, bool SPLIT>
+__device__ __forceinline__ void rank_codes(const Geom &G, const uint32_t *x, const uint32_t *B0,
+                                           uint32_t live, uint32_t ts, uint32_t *cnt, uint32_t *v,
+                                           uint32_t *rk2) {
+#pragma unroll
+  for (int k = 0; k < PPT; k++) {
+    if ((live >> k) & 1u) {
+      uint32_t B[R];
+      codes_of<R>(G, x[k], B0[k] << ts, B, ts);
+#pragma unroll
+      for (int row = 0; row < R; row++) {
+        const int q = k * R + row;
+        const uint32_t t4 = tile4_of(B[row]);
+        v[q] = SPLIT ? tile_code(B[row], t4) : B[row];
+        put_rank(rk2, q, atomicAdd(at4(cnt, t4), 1u));
+      }
+    }
+  }
+}
+// The codes grouped by tile: each to its run's start (lofs, in codes) plus its
+// rank.
+template <int R, int PPT, bool SPLIT, typename L>
+__device__ __forceinline__ void group_codes(uint32_t live, const uint32_t *v, const uint32_t *rk2,
+                                            L *lofs, uint32_t *sorted) {
+#pragma unroll
+  for (int k = 0; k < PPT; k++) {
+    if ((live >> k) & 1u) {
+#pragma unroll
+      for (int q = k * R; q < (k + 1) * R; q++) {
+        const uint32_t t4 = SPLIT ? tile4_of_code(v[q]) : tile4_of(v[q]);
+        const uint32_t o = *reinterpret_cast<L *>(reinterpret_cast<char *>(lofs) +
+                                                  t4 / (4 / sizeof(L)));
+        sorted[o + get_rank(rk2, q)] = v[q];
+      }
+    }
+  }
 }
 
 // Zero count of the LE that holds sketch words [w, w+4) (v), when the LE's
@@ -181,18 +295,19 @@ __device__ __forceinline__ void le_zeros(const Geom &G, GMEM uint32_t *lez, size
   if ((w / 4) % L == 0) lez[w / G.wpl] = G.g - ones;
 }
 
-// The three codes of a word into the LDS tile. Per code: its word's byte
-// offset (bits 5..20 of the code, times 4) and its bit (a shift takes the low
-// 5 bits of its count).
-__device__ __forceinline__ void or_code(uint32_t *tile, uint32_t c) {
-  constexpr uint32_t BYTES = (CODE_MASK >> 5) << 2;
-  uint32_t *w = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(tile) + ((c >> 3) & BYTES));
-  atomicOr(w, 1u << (c & 31));
+// The three codes of a word into the LDS tile (ts: codes are stored times
+// 2^ts). Per code: its word's byte offset (bits 5..20 of the code, times 4)
+// and its bit (a shift takes the low 5 bits of its count).
+__device__ __forceinline__ void or_code(uint32_t *tile, uint32_t c, uint32_t ts) {
+  const uint32_t bytes = (CODE_MASK >> (5 + ts)) << 2;
+  uint32_t *w =
+      reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(tile) + ((c >> (3 + ts)) & bytes));
+  atomicOr(w, 1u << ((c >> ts) & 31));
 }
-__device__ __forceinline__ void or_word(uint32_t *tile, uint2 w) {
-  or_code(tile, w.x);
-  or_code(tile, __builtin_amdgcn_alignbit(w.y, w.x, CODE_BITS));
-  or_code(tile, w.y >> (2 * CODE_BITS - 32));
+__device__ __forceinline__ void or_word(uint32_t *tile, uint2 w, uint32_t ts = 0) {
+  or_code(tile, w.x, ts);
+  or_code(tile, __builtin_amdgcn_alignbit(w.y, w.x, CODE_BITS), ts);
+  or_code(tile, w.y >> (2 * CODE_BITS - 32), ts);
 }
 
 }  // namespace ddhf
