@@ -117,9 +117,24 @@ void pinned_free(T *&h, T *&d) {
 // Orders device work on one resource (a shared buffer, a sketch) across
 // streams: work about to be enqueued on a stream waits for the last work
 // that used the resource when that work was enqueued on another stream.
+//
+// Recording an event costs the host about 3.5 us, as much as a launch, and
+// the device a packet between two kernels, and a caller that stays on one
+// stream never needs it. So after work on the null stream (which is never
+// destroyed) it is recorded late, when another stream or the host asks for
+// it; it then covers whatever the null stream holds by then, the work
+// included. A resource that changes streams would wait for more than it has
+// to that way: after a change its events are recorded at once for LANE_EAGER
+// uses. Work that the host has waited for leaves nothing to order. Updates of
+// 16,667 pairs on one sketch: 10.2 -> 7.1 us a call; a window of 3000 pairs
+// from reset to list: 66 -> 50 us.
+constexpr int LANE_EAGER = 4096;
+
 struct Lane {
   hipEvent_t ev = nullptr;
   bool armed = false;
+  bool late = false;              // armed, the event not yet recorded (null stream)
+  int eager = 4;                  // uses still recorded at once
   hipStream_t stream = nullptr;   // stream of the last work
 };
 
@@ -131,20 +146,34 @@ int lane_init(Lane &l) {
   return SKETCH_OK;
 }
 
+// The late event, now that it is needed (the resource's device is current).
+int lane_record(Lane &l) {
+  if (!l.late) return SKETCH_OK;
+  HIP_OK(hipEventRecord(l.ev, nullptr));
+  l.late = false;
+  return SKETCH_OK;
+}
+
 void lane_free(Lane &l) {
-  if (l.armed) (void)hipEventSynchronize(l.ev);
+  if (l.armed && lane_record(l) == SKETCH_OK) (void)hipEventSynchronize(l.ev);
   if (l.ev) (void)hipEventDestroy(l.ev);
   l.ev = nullptr;
-  l.armed = false;
+  l.armed = l.late = false;
 }
 
 int lane_enter(Lane &l, hipStream_t st) {
-  if (l.armed && st != l.stream) HIP_OK(hipStreamWaitEvent(st, l.ev, 0));
+  if (!l.armed || st == l.stream) return SKETCH_OK;
+  l.eager = LANE_EAGER;
+  int rc = lane_record(l);
+  if (rc) return rc;
+  HIP_OK(hipStreamWaitEvent(st, l.ev, 0));
   return SKETCH_OK;
 }
 
 int lane_leave(Lane &l, hipStream_t st) {
-  HIP_OK(hipEventRecord(l.ev, st));
+  l.late = st == nullptr && l.eager == 0;
+  if (l.eager) l.eager--;
+  if (!l.late) HIP_OK(hipEventRecord(l.ev, st));
   l.armed = true;
   l.stream = st;
   return SKETCH_OK;
@@ -152,9 +181,15 @@ int lane_leave(Lane &l, hipStream_t st) {
 
 // Wait on the host until the last work that used the resource is done.
 int lane_idle(Lane &l) {
-  if (l.armed) HIP_OK(hipEventSynchronize(l.ev));
+  if (!l.armed) return SKETCH_OK;
+  int rc = lane_record(l);
+  if (rc) return rc;
+  HIP_OK(hipEventSynchronize(l.ev));
   return SKETCH_OK;
 }
+
+// The host has waited for the last work that used the resource.
+void lane_done(Lane &l) { l.armed = l.late = false; }
 
 // ---------------------------------------------------------- device context
 
@@ -830,9 +865,11 @@ int materialize(sketch *s, hipStream_t st) {
 }
 
 // Enqueue the restore kernels on buffers B, whose shared part is ordered by
-// `pool`, and the copy of the device state (no wait). Caller holds ctx->mu.
+// `pool`, and the copy of the device state (no wait). waited: the caller waits
+// for st before it lets go of ctx->mu, and then calls lane_done for both
+// lanes. Caller holds ctx->mu.
 int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresholds &t,
-                      int estimate, hipStream_t st) {
+                      int estimate, hipStream_t st, bool waited) {
   int rc = lane_enter(s->lane, st);
   if (!rc) rc = materialize(s, st);
   if (!rc) rc = lane_enter(pool, st);
@@ -845,13 +882,15 @@ int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresho
     s->timed = true;
     s->timed_lez = B.lez && !B.lez_stale;
   }
+  if (waited) return SKETCH_OK;
   rc = lane_leave(pool, st);
   if (!rc) rc = lane_leave(s->lane, st);
   return rc;
 }
 
 // The restore on restore pool i, enqueued on st.
-int restore_launch_pool(sketch *s, const Thresholds &t, int estimate, int i, hipStream_t st) {
+int restore_launch_pool(sketch *s, const Thresholds &t, int estimate, int i, hipStream_t st,
+                        bool waited = false) {
   RPool &p = s->ctx->pool[i];
   const RestoreBufs B = restore_bufs(s, p, t);
   s->ran_seg_cap = B.seg_cap;
@@ -859,12 +898,7 @@ int restore_launch_pool(sketch *s, const Thresholds &t, int estimate, int i, hip
   s->ran_spl_cap = B.spl_cap;
   s->ran_h_recs_cap = B.h_recs_cap;
   s->ran_pool = i;
-  return restore_launch_on(s, B, p.lane, t, estimate, st);
-}
-
-// The restore on the device's first restore pool (the caller's stream).
-int restore_launch(sketch *s, const Thresholds &t, int estimate, hipStream_t st) {
-  return restore_launch_pool(s, t, estimate, 0, st);
+  return restore_launch_on(s, B, p.lane, t, estimate, st, waited);
 }
 
 // Relative work of a restore of s: its LEs, and the row-0 addresses the
@@ -1026,9 +1060,12 @@ int restore_check(sketch *s, int estimate, bool *again) {
 // most). Leaves the final state in s->h_state. Caller holds ctx->mu.
 int run_restore(sketch *s, const Thresholds &t, int estimate, hipStream_t st) {
   for (int attempt = 0; attempt < 16; attempt++) {
-    int rc = restore_launch(s, t, estimate, st);
+    // on the device's first restore pool, on the caller's stream
+    int rc = restore_launch_pool(s, t, estimate, 0, st, true);
     if (rc) return rc;
     HIP_OK(hipStreamSynchronize(st));
+    lane_done(s->ctx->pool[0].lane);
+    lane_done(s->lane);
     bool again;
     rc = restore_check(s, estimate, &again);
     if (rc || !again) return rc;
@@ -1860,9 +1897,11 @@ int sketch_restore_noalloc(sketch_t *s, double theta, sketch_sp_t *out, size_t c
   // search or a sort that was expected and not the right one: again with
   // every kernel
   for (;;) {
-    int rc = restore_launch_on(s, B, c->noalloc_lane, t, 1, st);
+    int rc = restore_launch_on(s, B, c->noalloc_lane, t, 1, st, true);
     if (rc) return rc;
     HIP_OK(hipStreamSynchronize(st));
+    lane_done(c->noalloc_lane);
+    lane_done(s->lane);
     const DevState &h = *s->h_state;
     if (h.saturated) break;
     if (B.expect && h.search == 0) {
