@@ -703,6 +703,7 @@ struct sketch {
   double hint_e = -1.0, ran_e = -1.0;
   bool ran_sort_one = false;
   uint2 *chunks = nullptr;      // hot scan chunks (scan_chunks)
+  uint32_t *pair_off = nullptr, *pair_z = nullptr;   // pair index (null: none)
   uint64_t cost_hint = 0;       // the last restore's row-0 cells times their addresses
   uint64_t join_hint = 0;       // the last restore's join wave items of stage 1 (0: none yet)
 };
@@ -731,6 +732,8 @@ void free_sketch(sketch *s) {
   dev_free(s->st);
   dev_free(s->hotmask);
   dev_free(s->chunks);
+  dev_free(s->pair_off);
+  dev_free(s->pair_z);
   dev_free(s->he);
   dev_free(s->bk_off);
   dev_free(s->bk_cur);
@@ -774,7 +777,7 @@ RestoreBufs restore_bufs(const sketch *s, const RPool &p, const Thresholds &t) {
   B.lez_stale = !s->lez_valid;
   B.chunks = s->chunks;
   if (s->hint_e == t.e_theta) {
-    B.expect = s->cand_path == 0 ? s->hint_search : 0;
+    if (s->cand_path == 0 || (s->cand_path == 2 && s->hint_search >= 2)) B.expect = s->hint_search;
     B.sort_one = s->hint_n <= SORT_ONE_HINT;
   }
   B.st = s->st;
@@ -1772,6 +1775,12 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   if (!rc) rc = dev_alloc(&s->bk_off, (size_t)params->r * (nb + 1), "bucket offsets");
   if (!rc) rc = dev_alloc(&s->bk_cur, (size_t)params->r * nb, "bucket cursors");
   if (!rc) rc = dev_alloc(&s->bk_val, n_le, "bucket values");
+  if (!rc && s->lat.ok && pair_indexed(params->k)) {
+    rc = dev_alloc(&s->pair_off, pair_off_words(params->k), "pair index");
+    if (!rc) rc = dev_alloc(&s->pair_z, pair_z_words(params->k), "pair index");
+    s->lat.pair_off = s->pair_off;
+    s->lat.pair_z = s->pair_z;
+  }
   if (!rc) rc = grow_sorted(s, (size_t)1 << 12);
   if (!rc && s->nbins <= BIN_MAX) {
     rc = dev_alloc(&s->hist, (size_t)s->nbins * s->bin_nblk, "tile counts");
@@ -1790,6 +1799,7 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   if (!rc) s->h_recs_cap = (size_t)1 << 12;
   if (!rc) {
     hipError_t e = launch_fill_u32(s->d_sketch, s->words, 0u, s->grid, nullptr);
+    if (e == hipSuccess && s->pair_z) e = launch_pair_index(s->G, s->pair_off, s->pair_z, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess)
       rc = fail(SKETCH_E_HIP, "sketch_create: zero fill: %s", hipGetErrorString(e));
@@ -2176,8 +2186,8 @@ int sketch_timings(sketch_t *s, sketch_timings_t *out) {
   const uint64_t n_le = (uint64_t)s->p.r << s->p.k;
   out->hot_scan_bytes = s->timed_lez ? n_le * 4 : n_le * (s->p.g / 8);
   if (!h.saturated) {
-    out->search = h.search;
-    if (h.search == 2) {
+    out->search = std::min(h.search, 2u);
+    if (h.search >= 2) {
       // every address of every hot row-0 LE: 2^(32-k) per LE
       out->lattice_points = (uint64_t)h.he_count[0] << (32 - s->p.k);
       out->join_outputs = h.n_cand;

@@ -53,7 +53,7 @@ struct DevState {
   uint32_t szmax;
   uint32_t saturated;
   uint32_t seg_max[8];               // largest block segment of join stage i
-  uint32_t search;                   // candidate search that ran: 1 join, 2 lattice
+  uint32_t search;                   // candidate search that ran: 1 join, 2 lattice, 3 lattice by pairs
   uint32_t pad;
 };
 
@@ -70,8 +70,28 @@ struct Lattice {
   uint32_t dneg;           // 1 if that determinant is -2^64
   uint32_t lines;          // lines j = const of a cell's box, at most
   uint32_t ok;             // the basis fits the kernel's 64-bit arithmetic
-  uint32_t pad;
+  // the pair index (k_pairs), null if the sketch has none
+  const uint32_t *pair_off, *pair_z;
 };
+
+// The pair index of row 0's hash: the high address parts z < N = 2^(32-k)
+// by the top 32 - k bits of (A0 z 2^k mod 2^64), bucket after bucket. z holds
+// the parts twice over (so that buckets can be read round the end) and 4
+// words that a wide load may run into; off, per bucket b, the place of its
+// first part and, over PAIR_PLACE_BITS, the parts in buckets b to b +
+// pair_span (PAIR_MANY: that many or more), then the N + pair_span + 1 bucket
+// starts that it was made from. 16 bytes a part: 4 MiB at k = 14.
+constexpr uint32_t PAIR_K_MIN = 14, PAIR_K_MAX = 18, PAIR_PLACE_BITS = 20;
+constexpr uint32_t PAIR_MANY = (1u << (32 - PAIR_PLACE_BITS)) - 1;
+__host__ __device__ constexpr bool pair_indexed(uint32_t k) {
+  return k >= PAIR_K_MIN && k <= PAIR_K_MAX;
+}
+// Buckets that an interval of 2^(64-k) covers past the one it starts in.
+__host__ __device__ constexpr uint32_t pair_span(uint32_t k) {
+  return k <= 16 ? 1u << (32 - 2 * k) : 1u;
+}
+inline size_t pair_off_words(uint32_t k) { return ((size_t)2 << (32 - k)) + pair_span(k) + 1; }
+inline size_t pair_z_words(uint32_t k) { return ((size_t)2 << (32 - k)) + 4; }
 
 // Restore work buffers (device pointers) and capacities.
 struct RestoreBufs {
@@ -110,7 +130,8 @@ struct RestoreBufs {
   Lattice lat;
   uint32_t cand_path;
   // what to launch, by the sketch's last restore: only the search that ran
-  // then (0 = both, 1 = the join, 2 = the lattice), and the one-launch sort.
+  // then (0 = any, 1 = the join, 2 = the lattice, 3 = the lattice by pairs),
+  // and the one-launch sort.
   // A restore whose counts then call for the other search, or whose list is
   // longer, leaves that to see in the state (search 0, n_spl) and is run again
   uint32_t expect;
@@ -374,6 +395,8 @@ hipError_t launch_or_u32(uint32_t *dst, const uint32_t *src, size_t n_words, int
 // Once per device, before any restore (and outside graph capture): lets the
 // lattice search take more than 64 KiB of LDS.
 hipError_t prepare_restore_kernels();
+// Builds a sketch's pair index (pair_off_words, pair_z_words) on st.
+hipError_t launch_pair_index(const Geom &G, uint32_t *off, uint32_t *z, hipStream_t st);
 // Runs every restore step up to and including the candidate list (and, when
 // estimate != 0, the estimate, report filter and sort). All counts stay on
 // the device; the caller reads DevState afterwards.

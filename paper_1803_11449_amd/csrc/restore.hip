@@ -642,11 +642,27 @@ __global__ __launch_bounds__(1024) void k_scan_rows(
 // ------------------------------------------------------ 5: search choice
 
 // The join's work is about its probes and partial addresses, |HE(0)||HE(1)|
-// then times |HE(i)| / 2^(k-alpha) per further row; the lattice search's is
-// 2^(32-k) addresses per hot row-0 cell, each a few integer operations and
-// one LDS read (about a quarter of a join item). Every kernel of both
-// searches evaluates this on the same counts, so exactly one of them runs.
-constexpr double LATTICE_COST = 0.25;
+// then times |HE(i)| / 2^(k-alpha) per further row, 4.5 ps each on a whole
+// chip (9.7M in 44 us, 10.4M in 48 us). The lattice search's is, per hot
+// row-0 cell, all 2^(32-k) addresses of the cell at 0.44 ps (162M at k = 16 in
+// 71 us, 210M at k = 15 in 88 us), or by the pair index a pair per hot row-1
+// cell: 10 ps at k = 16 and 17 at k = 15, where a pair has 2 and 5 parts to
+// look at. Every kernel of the searches evaluates this on the same counts, so
+// exactly one of them runs.
+constexpr double LATTICE_COST = 0.1;                    // an address, in join items
+constexpr double PAIR_COST = 13, PAIR_PART_COST = 5;    // a pair and a part, in addresses
+
+__device__ __forceinline__ double pair_work(const Geom &G, const DevState *st) {
+  return (double)st->he_count[1] * (PAIR_COST + PAIR_PART_COST * (pair_span(G.k) + 1));
+}
+// ways: what the sketch has, LAT_OK and LAT_PAIRS (see Lattice).
+constexpr uint32_t LAT_OK = 1, LAT_PAIRS = 2;
+inline uint32_t lattice_ways(const Lattice &L) {
+  return (L.ok ? LAT_OK : 0u) | (L.pair_z ? LAT_PAIRS : 0u);
+}
+__device__ __forceinline__ bool pairs_chosen(const Geom &G, const DevState *st, uint32_t ways) {
+  return (ways & LAT_PAIRS) && pair_work(G, st) < (double)(1ull << (32 - G.k));
+}
 
 // A row without a zero bit left (psi = 1): nothing to search.
 __device__ __forceinline__ bool no_zeros(const Geom &G, const DevState *st) {
@@ -667,8 +683,8 @@ __device__ __forceinline__ void search_begin(const Geom &G, DevState *st, double
 }
 
 __device__ __forceinline__ bool lattice_chosen(const Geom &G, const DevState *st,
-                                               const Lattice &L, uint32_t path) {
-  if (!L.ok || path == 1) return false;
+                                               uint32_t ways, uint32_t path) {
+  if (!(ways & LAT_OK) || path == 1) return false;
   if (path == 2) return true;
   const double nb = (double)(1u << (G.k - G.alpha));
   double p = (double)st->he_count[0] * (double)st->he_count[1], join = p;
@@ -676,7 +692,8 @@ __device__ __forceinline__ bool lattice_chosen(const Geom &G, const DevState *st
     p *= (double)st->he_count[i] / nb;
     join += p;
   }
-  const double lat = (double)st->he_count[0] * (double)(1ull << (32 - G.k)) * LATTICE_COST;
+  const double cell = pairs_chosen(G, st, ways) ? pair_work(G, st) : (double)(1ull << (32 - G.k));
+  const double lat = (double)st->he_count[0] * cell * LATTICE_COST;
   return lat < join;
 }
 
@@ -743,12 +760,12 @@ __device__ __forceinline__ int64_t mul_hi_s(int64_t m, uint64_t y) {
 }
 
 __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
-    Geom G, Lattice L, uint32_t path, const uint32_t *__restrict__ he,
+    Geom G, Lattice L, uint32_t ways, uint32_t path, const uint32_t *__restrict__ he,
     const uint32_t *__restrict__ hotmask, DevState *__restrict__ st,
     uint32_t *__restrict__ cand, size_t cand_cap, double e_theta, uint32_t lds_rows) {
   // lds_rows * 2^k bits, the candidates, then the queues
   extern __shared__ __attribute__((aligned(16))) uint32_t row1[];
-  const bool chosen = lattice_chosen(G, st, L, path);
+  const bool chosen = lattice_chosen(G, st, ways, path) && !pairs_chosen(G, st, ways);
   search_begin(G, st, e_theta, chosen, 2);
   if (!chosen || no_zeros(G, st)) return;
   const uint32_t k = G.k, kw = 1u << (k - 5);
@@ -927,6 +944,182 @@ __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
   // what is left in the queue
   if (qn) test(queue[lane < qn ? lane : 0], lane < qn);
   found->flush(st, cand, cand_cap);
+}
+
+// --------------------------------------------------- 5b: the search by pairs
+//
+// The lattice search's other way through the hot row-0 cells, for sketches
+// with a pair index: a hot row-1 cell c1 with c0 fixes an address's low k
+// bits, c0 ^ c1, and of its 2^(32-k) high parts z only those are in cell c0
+// for which A0 z 2^k (mod 2^64) lies in an interval of 2^(64-k): 2^(32-2k)
+// parts on average, which the index gives by the bucket the interval starts
+// in. So the walk's addresses that fail row 1 are never made. A wave takes
+// 64 PAIR_UNROLL pairs of one c0 and looks at all parts of the interval's
+// buckets, which may hold some outside it: each part's LE in row 2 is tested
+// in LDS, those that pass (a few percent) go to the wave's queue, and 64 of
+// them together are hashed (exactly the addresses of cell c0 stay) and
+// tested in the rows past 2. Each address has one (c0, c1), so there are no
+// duplicates. Bound by the cache lines that the lookups bring (two to three
+// a pair, from the L2). Search of a 9M-pair window, k = 15, 2.6M pairs (210M
+// addresses): 88 -> 43 us; a 4M-pair one, k = 15, r = 4, which took the join,
+// 44 -> 14 us; k = 16, 6.1M pairs (162M addresses) 71 -> 61 us.
+constexpr uint32_t PAIR_UNROLL = 4;                     // pairs per lane at once
+constexpr uint32_t PAIR_QUEUE = 128;                    // 63 + 64 addresses per wave
+constexpr uint32_t PAIR_THREADS = 1024;
+constexpr uint32_t PAIR_QUEUE_BYTES = PAIR_THREADS / 64 * PAIR_QUEUE * 4;
+
+// Rows 2.. whose hot bitmaps a block holds in LDS, two blocks to a compute
+// unit (row 2 always: 32 KiB at k = 18).
+inline uint32_t pair_rows(const Geom &G) {
+  const uint32_t row = 4u << (G.k - 5);
+  uint32_t n = 1;
+  while (n + 2 < G.r && (n + 1) * row + LAT_FOUND_BYTES + PAIR_QUEUE_BYTES <= 81920) n++;
+  return n;
+}
+
+__global__ __launch_bounds__(PAIR_THREADS) void k_pairs(
+    Geom G, const uint32_t *__restrict__ pair_off, const uint32_t *__restrict__ pair_z,
+    uint32_t ways, uint32_t path, const uint32_t *__restrict__ he,
+    const uint32_t *__restrict__ hotmask, DevState *__restrict__ st,
+    uint32_t *__restrict__ cand, size_t cand_cap, double e_theta, uint32_t lds_rows) {
+  // lds_rows * 2^k bits, the candidates, then the queues
+  extern __shared__ __attribute__((aligned(16))) uint32_t row2[];
+  const bool chosen = lattice_chosen(G, st, ways, path) && pairs_chosen(G, st, ways);
+  search_begin(G, st, e_theta, chosen, 3);
+  if (!chosen || no_zeros(G, st)) return;
+  const uint32_t k = G.k, kw = 1u << (k - 5), alpha = G.alpha;
+  CandBuf *found = reinterpret_cast<CandBuf *>(row2 + lds_rows * kw);
+  if (threadIdx.x == 0) found->n = 0;
+  for (uint32_t w = threadIdx.x; w < lds_rows * kw; w += blockDim.x) row2[w] = hotmask[2 * kw + w];
+  __syncthreads();
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t *queue = reinterpret_cast<uint32_t *>(found + 1) + wib * PAIR_QUEUE;
+  const uint32_t *HE1 = he + (1u << k);
+  const uint32_t h0 = st->he_count[0], h1 = st->he_count[1];
+  const uint32_t nch = (h1 + 64 * PAIR_UNROLL - 1) / (64 * PAIR_UNROLL);
+  const uint32_t items = h0 * nch, parts = 1u << (32 - k);   // items < 2^32 by the rule on h1
+
+  for (uint32_t w = blockIdx.x + gridDim.x * wib; w < items; w += gridDim.x * (PAIR_THREADS / 64)) {
+    const uint32_t x0 = w / nch, x1 = (w - x0 * nch) * (64 * PAIR_UNROLL) + lane;
+    const uint32_t c0 = __builtin_amdgcn_readfirstlane(he[x0]);
+    uint32_t qn = 0;                                    // queue fill, wave-uniform
+    // one address that passed row 2 per lane
+    auto test = [&](uint32_t ad, bool ok) {
+      ok = ok && hash_dh0(G, ad) == c0;
+      for (uint32_t row = 3; row < G.r; row++) {
+        if (__ballot(ok) == 0) return;
+        const uint32_t sh = (row - 1) * alpha;
+        const uint32_t x = c0 ^ __builtin_amdgcn_ubfe(ad, sh, sh < 32 ? k : 0u);
+        uint32_t v;
+        if (row - 2 < lds_rows) v = row2[(row - 2) * kw + (x >> 5)];
+        else v = hotmask[row * kw + (x >> 5)];
+        ok = ok && ((v >> (x & 31)) & 1u);
+      }
+      found->add(ad, ok, st, cand, cand_cap);
+    };
+    const uint64_t lo0 = ((uint64_t)c0 << (64 - k)) - G.b0;
+    uint32_t low[PAIR_UNROLL], q[PAIR_UNROLL], n[PAIR_UNROLL];
+#pragma unroll
+    for (uint32_t u = 0; u < PAIR_UNROLL; u++)
+      low[u] = c0 ^ HE1[x1 + 64 * u < h1 ? x1 + 64 * u : h1 - 1];
+#pragma unroll
+    for (uint32_t u = 0; u < PAIR_UNROLL; u++)
+      q[u] = pair_off[(uint32_t)((lo0 - G.a0 * low[u]) >> 32) >> k];
+    uint32_t most = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < PAIR_UNROLL; u++) {
+      n[u] = q[u] >> PAIR_PLACE_BITS;
+      if (n[u] == PAIR_MANY) n[u] = parts;              // more than the index says: any part
+      if (x1 + 64 * u >= h1) n[u] = 0;
+      q[u] &= (1u << PAIR_PLACE_BITS) - 1;
+      most = n[u] > most ? n[u] : most;
+    }
+    for (uint32_t t = 0; __ballot(t < most); t += 4) {
+      uint32_t z[PAIR_UNROLL][4];
+#pragma unroll
+      for (uint32_t u = 0; u < PAIR_UNROLL; u++)
+        __builtin_memcpy(z[u], pair_z + q[u] + (t < n[u] ? t : 0u), 16);
+#pragma unroll
+      for (uint32_t u = 0; u < PAIR_UNROLL; u++) {
+#pragma unroll
+        for (uint32_t i = 0; i < 4; i++) {
+          const uint32_t ad = low[u] | (z[u][i] << k);
+          const uint32_t x = c0 ^ __builtin_amdgcn_ubfe(ad, alpha, k);
+          const bool ok = t + i < n[u] && ((row2[x >> 5] >> (x & 31)) & 1u);
+          const unsigned long long m = __ballot(ok);
+          if (m == 0) continue;
+          if (ok) queue[qn + lanes_below(m)] = ad;
+          qn += (uint32_t)__popcll(m);
+          __builtin_amdgcn_wave_barrier();
+          if (qn >= 64) {
+            qn -= 64;
+            const uint32_t ad2 = queue[qn + lane];
+            __builtin_amdgcn_wave_barrier();
+            test(ad2, true);
+          }
+        }
+      }
+    }
+    if (qn) test(queue[lane < qn ? lane : 0], lane < qn);
+    __builtin_amdgcn_wave_barrier();
+  }
+  found->flush(st, cand, cand_cap);
+}
+
+// The pair index, built once per sketch: the counts per bucket become their
+// starts (one block), the parts take their places, and then the second copy
+// of the parts and the bucket words are made.
+__device__ __forceinline__ uint32_t pair_bucket(const Geom &G, uint32_t z) {
+  return (uint32_t)((G.a0 * z) << G.k >> 32) >> G.k;
+}
+
+__global__ __launch_bounds__(256) void k_pair_count(Geom G, uint32_t *__restrict__ cnt) {
+  atomicAdd(&cnt[pair_bucket(G, blockIdx.x * 256 + threadIdx.x)], 1u);
+}
+
+__global__ __launch_bounds__(1024) void k_pair_starts(Geom G, uint32_t *__restrict__ cnt,
+                                                      uint32_t *__restrict__ cur, uint32_t n) {
+  __shared__ uint32_t sh[17];
+  uint32_t done = 0;
+  for (uint32_t b0 = 0; b0 < n; b0 += 4096) {           // n: a multiple of 4096
+    uint4 *p = reinterpret_cast<uint4 *>(cnt + b0) + threadIdx.x;
+    const uint4 c = *p;
+    uint32_t total;
+    const uint32_t x = done + block_excl_scan<1024>(c.x + c.y + c.z + c.w, &total, sh);
+    const uint4 st = make_uint4(x, x + c.x, x + c.x + c.y, x + c.x + c.y + c.z);
+    *p = st;
+    reinterpret_cast<uint4 *>(cur + b0)[threadIdx.x] = st;
+    done += total;
+  }
+  __syncthreads();
+  if (threadIdx.x <= pair_span(G.k)) cnt[n + threadIdx.x] = n + cnt[threadIdx.x];
+}
+
+__global__ __launch_bounds__(256) void k_pair_place(Geom G, uint32_t *__restrict__ z, uint32_t n) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  z[atomicAdd(&z[n + pair_bucket(G, i)], 1u)] = i;      // the cursors: z's second half
+}
+
+__global__ __launch_bounds__(256) void k_pair_finish(Geom G, uint32_t *__restrict__ off,
+                                                     uint32_t *__restrict__ z, uint32_t n) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  const uint32_t *start = off + n;
+  z[n + i] = z[i];
+  if (i < 4) z[2 * n + i] = 0;
+  const uint32_t parts = start[i + pair_span(G.k) + 1] - start[i];
+  off[i] = start[i] | (parts < PAIR_MANY ? parts : PAIR_MANY) << PAIR_PLACE_BITS;
+}
+
+hipError_t launch_pair_index(const Geom &G, uint32_t *off, uint32_t *z, hipStream_t st) {
+  const uint32_t n = 1u << (32 - G.k), blocks = n / 256;
+  hipError_t e = launch_fill_u32(off + n, n, 0u, 64, st);
+  if (e != hipSuccess) return e;
+  k_pair_count<<<blocks, 256, 0, st>>>(G, off + n);
+  k_pair_starts<<<1, 1024, 0, st>>>(G, off + n, z + n, n);
+  k_pair_place<<<blocks, 256, 0, st>>>(G, z, n);
+  k_pair_finish<<<blocks, 256, 0, st>>>(G, off, z, n);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ 5: join
@@ -1150,7 +1343,7 @@ __device__ __forceinline__ void join_items(
 
 template <bool FIRST, bool LAST>
 __global__ __launch_bounds__(JOIN_THREADS) void k_join(
-    Geom G, Lattice Lt, uint32_t path, uint32_t row, const uint32_t *__restrict__ he,
+    Geom G, uint32_t ways, uint32_t path, uint32_t row, const uint32_t *__restrict__ he,
     const uint2 *__restrict__ in, const uint32_t *__restrict__ in_cnt,
     const uint32_t *__restrict__ bk_off, const uint32_t *__restrict__ bk_val,
     DevState *__restrict__ st, uint2 *__restrict__ out, uint32_t *__restrict__ out_cnt,
@@ -1161,7 +1354,7 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
   __shared__ uint16_t w_own[(JOIN_THREADS / 64) * OWN_MAX];
   __shared__ uint32_t seg_fill;
   __shared__ CandBuf found;
-  const bool chosen = !lattice_chosen(G, st, Lt, path);
+  const bool chosen = !lattice_chosen(G, st, ways, path);
   if (FIRST) search_begin(G, st, e_theta, chosen, 1);
   if (!chosen || no_zeros(G, st)) return;
 
@@ -1373,7 +1566,7 @@ __device__ __forceinline__ void join_walk(const Geom &G, const uint32_t *he, con
 
 template <int R>
 __global__ __launch_bounds__(JOIN_THREADS) void k_join_walk(
-    Geom G, Lattice Lt, uint32_t path, const uint32_t *__restrict__ he,
+    Geom G, uint32_t ways, uint32_t path, const uint32_t *__restrict__ he,
     const uint32_t *__restrict__ bk_off, const uint32_t *__restrict__ bk_val,
     DevState *__restrict__ st, uint32_t *__restrict__ cand, size_t cand_cap, double e_theta) {
   __shared__ uint16_t t_off[(R - 2) * (WALK_NB + 1)];
@@ -1381,7 +1574,7 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join_walk(
   __shared__ typename JoinWalk<R, true>::Wave waves[JOIN_THREADS / 64];
   __shared__ uint32_t outs[R - 2];
   __shared__ CandBuf found;
-  const bool chosen = !lattice_chosen(G, st, Lt, path);
+  const bool chosen = !lattice_chosen(G, st, ways, path);
   search_begin(G, st, e_theta, chosen, 1);
   if (!chosen || no_zeros(G, st)) return;
   const uint32_t nb = 1u << (G.k - G.alpha);
@@ -1739,13 +1932,14 @@ __global__ __launch_bounds__(1024) void k_sort_publish(
 // stage per row.
 template <int R>
 static void launch_walk(const Geom &G, const RestoreBufs &B, double e_theta, hipStream_t st) {
-  k_join_walk<R><<<B.jblk, JOIN_THREADS, 0, st>>>(G, B.lat, B.cand_path, B.he, B.bk_off, B.bk_val,
-                                                  B.st, B.cand, B.cand_cap, e_theta);
+  k_join_walk<R><<<B.jblk, JOIN_THREADS, 0, st>>>(G, lattice_ways(B.lat), B.cand_path, B.he,
+                                                  B.bk_off, B.bk_val, B.st, B.cand, B.cand_cap,
+                                                  e_theta);
 }
 
 static void launch_join(const Geom &G, const RestoreBufs &B, double e_theta, hipStream_t st) {
   const uint32_t r = G.r, jb = B.jblk, pth = B.cand_path;
-  const Lattice &Lt = B.lat;
+  const uint32_t ways = lattice_ways(B.lat);
   if (B.walk) {
     switch (r) {
       case 4: launch_walk<4>(G, B, e_theta, st); break;
@@ -1755,11 +1949,11 @@ static void launch_join(const Geom &G, const RestoreBufs &B, double e_theta, hip
       default: launch_walk<8>(G, B, e_theta, st);
     }
   } else if (r == 3) {
-    k_join<true, true><<<jb, JOIN_THREADS, 0, st>>>(G, Lt, pth, 2, B.he, nullptr, nullptr, B.bk_off,
+    k_join<true, true><<<jb, JOIN_THREADS, 0, st>>>(G, ways, pth, 2, B.he, nullptr, nullptr, B.bk_off,
                                                     B.bk_val, B.st, nullptr, nullptr, 0, B.cand,
                                                     B.cand_cap, e_theta);
   } else {
-    k_join<true, false><<<jb, JOIN_THREADS, 0, st>>>(G, Lt, pth, 2, B.he, nullptr, nullptr,
+    k_join<true, false><<<jb, JOIN_THREADS, 0, st>>>(G, ways, pth, 2, B.he, nullptr, nullptr,
                                                      B.bk_off, B.bk_val, B.st, B.part[0],
                                                      B.segc[0], B.seg_cap, B.cand, B.cand_cap,
                                                      e_theta);
@@ -1768,11 +1962,11 @@ static void launch_join(const Geom &G, const RestoreBufs &B, double e_theta, hip
       const int ib = (row - 3) & 1, ob = ib ^ 1;
       if (row + 1 == r)
         k_join<false, true><<<jb, JOIN_THREADS, 0, st>>>(
-            G, Lt, pth, row, B.he, B.part[ib], B.segc[ib], B.bk_off, B.bk_val, B.st, nullptr,
+            G, ways, pth, row, B.he, B.part[ib], B.segc[ib], B.bk_off, B.bk_val, B.st, nullptr,
             nullptr, B.seg_cap, B.cand, B.cand_cap, e_theta);
       else
         k_join<false, false><<<jb, JOIN_THREADS, 0, st>>>(
-            G, Lt, pth, row, B.he, B.part[ib], B.segc[ib], B.bk_off, B.bk_val, B.st, B.part[ob],
+            G, ways, pth, row, B.he, B.part[ib], B.segc[ib], B.bk_off, B.bk_val, B.st, B.part[ob],
             B.segc[ob], B.seg_cap, B.cand, B.cand_cap, e_theta);
     }
   }
@@ -1789,8 +1983,11 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
   };
   // a search is launched unless the sketch's setting or the expectation
   // rules it out (each returns at once unless it is the chosen one)
-  const bool lattice = B.lat.ok && B.cand_path != 1 && B.expect != 1;
-  const bool join = !(B.lat.ok && B.cand_path == 2) && B.expect != 2;
+  const uint32_t ways = lattice_ways(B.lat);
+  const bool lat = B.lat.ok && B.cand_path != 1;
+  const bool lattice = lat && (B.expect == 0 || B.expect == 2);
+  const bool pairs = lat && B.lat.pair_z && (B.expect == 0 || B.expect == 3);
+  const bool join = !(B.lat.ok && B.cand_path == 2) && B.expect <= 1;
   mark(0);
   // 1-3: hot scan, HE(i), bucket tables (which serve only the join)
   const uint4 *lez4 = reinterpret_cast<const uint4 *>(B.lez);
@@ -1836,7 +2033,14 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
     // which first copies the bitmaps
     const uint32_t rows = lattice_rows(G), threads = lattice_threads(G, rows);
     k_lattice<<<grid > 3 ? grid / 4 : 1, threads, lattice_lds(G, rows, threads), st>>>(
-        G, B.lat, B.cand_path, B.he, B.hotmask, B.st, B.cand, B.cand_cap, e_theta, rows);
+        G, B.lat, ways, B.cand_path, B.he, B.hotmask, B.st, B.cand, B.cand_cap, e_theta, rows);
+  }
+  if (pairs) {
+    const uint32_t rows = pair_rows(G);
+    k_pairs<<<grid > 3 ? grid / 4 : 1, PAIR_THREADS,
+              rows * (4u << (k - 5)) + LAT_FOUND_BYTES + PAIR_QUEUE_BYTES, st>>>(
+        G, B.lat.pair_off, B.lat.pair_z, ways, B.cand_path, B.he, B.hotmask, B.st, B.cand,
+        B.cand_cap, e_theta, rows);
   }
   if (join) launch_join(G, B, e_theta, st);
   mark(3);
@@ -1867,8 +2071,13 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
 }
 
 hipError_t prepare_restore_kernels() {
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(k_lattice),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)LATTICE_LDS_MAX);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_lattice),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)LATTICE_LDS_MAX);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_pairs),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 81920);
+  return e;
 }
 
 hipError_t launch_restore(const Geom &G, const uint32_t *sketch, const RestoreBufs &B,
