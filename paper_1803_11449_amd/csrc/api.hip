@@ -703,7 +703,7 @@ struct sketch {
   double hint_e = -1.0, ran_e = -1.0;
   bool ran_sort_one = false;
   uint2 *chunks = nullptr;      // hot scan chunks (scan_chunks)
-  uint32_t *pair_off = nullptr, *pair_z = nullptr;   // pair index (null: none)
+  uint32_t *pairs = nullptr;    // pair index (see Lattice; null: none)
   uint64_t cost_hint = 0;       // the last restore's row-0 cells times their addresses
   uint64_t join_hint = 0;       // the last restore's join wave items of stage 1 (0: none yet)
 };
@@ -732,8 +732,7 @@ void free_sketch(sketch *s) {
   dev_free(s->st);
   dev_free(s->hotmask);
   dev_free(s->chunks);
-  dev_free(s->pair_off);
-  dev_free(s->pair_z);
+  dev_free(s->pairs);
   dev_free(s->he);
   dev_free(s->bk_off);
   dev_free(s->bk_cur);
@@ -1775,11 +1774,17 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   if (!rc) rc = dev_alloc(&s->bk_off, (size_t)params->r * (nb + 1), "bucket offsets");
   if (!rc) rc = dev_alloc(&s->bk_cur, (size_t)params->r * nb, "bucket cursors");
   if (!rc) rc = dev_alloc(&s->bk_val, n_le, "bucket values");
+  uint32_t *pair_rec = nullptr, *pair_off = nullptr, *pair_z = nullptr;
   if (!rc && s->lat.ok && pair_indexed(params->k)) {
-    rc = dev_alloc(&s->pair_off, pair_off_words(params->k), "pair index");
-    if (!rc) rc = dev_alloc(&s->pair_z, pair_z_words(params->k), "pair index");
-    s->lat.pair_off = s->pair_off;
-    s->lat.pair_z = s->pair_z;
+    // one allocation: the records (16-byte aligned), the parts, the buckets
+    const size_t rec = ((size_t)2 * pair_rec_words(params->k)) << (32 - params->k);
+    rc = dev_alloc(&s->pairs, rec + pair_z_words(params->k) + pair_off_words(params->k),
+                   "pair index");
+    if (!rc) {
+      s->lat.pair_rec = pair_rec = s->pairs;
+      s->lat.pair_z = pair_z = pair_rec + rec;
+      s->lat.pair_off = pair_off = pair_z + pair_z_words(params->k);
+    }
   }
   if (!rc) rc = grow_sorted(s, (size_t)1 << 12);
   if (!rc && s->nbins <= BIN_MAX) {
@@ -1799,7 +1804,8 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   if (!rc) s->h_recs_cap = (size_t)1 << 12;
   if (!rc) {
     hipError_t e = launch_fill_u32(s->d_sketch, s->words, 0u, s->grid, nullptr);
-    if (e == hipSuccess && s->pair_z) e = launch_pair_index(s->G, s->pair_off, s->pair_z, nullptr);
+    if (e == hipSuccess && pair_z)
+      e = launch_pair_index(s->G, pair_off, pair_z, pair_rec, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess)
       rc = fail(SKETCH_E_HIP, "sketch_create: zero fill: %s", hipGetErrorString(e));

@@ -71,7 +71,7 @@ struct Lattice {
   uint32_t lines;          // lines j = const of a cell's box, at most
   uint32_t ok;             // the basis fits the kernel's 64-bit arithmetic
   // the pair index (k_pairs), null if the sketch has none
-  const uint32_t *pair_off, *pair_z;
+  const uint32_t *pair_off, *pair_z, *pair_rec;
 };
 
 // The pair index of row 0's hash: the high address parts z < N = 2^(32-k)
@@ -80,7 +80,13 @@ struct Lattice {
 // words that a wide load may run into; off, per bucket b, the place of its
 // first part and, over PAIR_PLACE_BITS, the parts in buckets b to b +
 // pair_span (PAIR_MANY: that many or more), then the N + pair_span + 1 bucket
-// starts that it was made from. 16 bytes a part: 4 MiB at k = 14.
+// starts that it was made from. From k = 15 on, where buckets b to b +
+// pair_span hold 2 to 5 parts as a rule, rec has those parts themselves, in
+// pair_rec_words(k) 64-bit words per bucket. k = 15: three of 21 bits to a
+// word (PAIR_NONE: no part); where the parts do not fit, the words' top bits
+// and no part. k >= 16: four of 16 bits, the unused ones copies of the first
+// (which is some part of another bucket when there is none); where they do not
+// fit, 0, 0, 1, 1. 16 to 32 bytes a part: 4 MiB at k = 14 and 15.
 constexpr uint32_t PAIR_K_MIN = 14, PAIR_K_MAX = 18, PAIR_PLACE_BITS = 20;
 constexpr uint32_t PAIR_MANY = (1u << (32 - PAIR_PLACE_BITS)) - 1;
 __host__ __device__ constexpr bool pair_indexed(uint32_t k) {
@@ -91,6 +97,10 @@ __host__ __device__ constexpr uint32_t pair_span(uint32_t k) {
   return k <= 16 ? 1u << (32 - 2 * k) : 1u;
 }
 inline size_t pair_off_words(uint32_t k) { return ((size_t)2 << (32 - k)) + pair_span(k) + 1; }
+constexpr uint32_t PAIR_NONE = 0x1FFFFF;
+__host__ __device__ constexpr uint32_t pair_rec_words(uint32_t k) {
+  return k == 14 ? 0 : k == 15 ? 2 : 1;
+}
 inline size_t pair_z_words(uint32_t k) { return ((size_t)2 << (32 - k)) + 4; }
 
 // Restore work buffers (device pointers) and capacities.
@@ -395,8 +405,10 @@ hipError_t launch_or_u32(uint32_t *dst, const uint32_t *src, size_t n_words, int
 // Once per device, before any restore (and outside graph capture): lets the
 // lattice search take more than 64 KiB of LDS.
 hipError_t prepare_restore_kernels();
-// Builds a sketch's pair index (pair_off_words, pair_z_words) on st.
-hipError_t launch_pair_index(const Geom &G, uint32_t *off, uint32_t *z, hipStream_t st);
+// Builds a sketch's pair index (pair_off_words, pair_z_words, and
+// pair_rec_words per bucket) on st.
+hipError_t launch_pair_index(const Geom &G, uint32_t *off, uint32_t *z, uint32_t *rec,
+                             hipStream_t st);
 // Runs every restore step up to and including the candidate list (and, when
 // estimate != 0, the estimate, report filter and sort). All counts stay on
 // the device; the caller reads DevState afterwards.

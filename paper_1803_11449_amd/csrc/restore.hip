@@ -18,7 +18,7 @@
 //                  D = g(1 - psi^r) (eq. (4)), T_rep = D*exp(-theta/g) and
 //                  the integer report bound floor(T_rep), in float64, by one
 //                  thread of the search's first block.
-//  5 candidates   the addresses whose r LEs are all hot, by one of two
+//  5 candidates   the addresses whose r LEs are all hot, by one of three
 //                  searches, chosen on the device from the hot-list sizes
 //                  by their estimated work:
 //                  join     stage 1 (Alg. 3) over HE(0) x HE(1) probing row
@@ -646,14 +646,18 @@ __global__ __launch_bounds__(1024) void k_scan_rows(
 // chip (9.7M in 44 us, 10.4M in 48 us). The lattice search's is, per hot
 // row-0 cell, all 2^(32-k) addresses of the cell at 0.44 ps (162M at k = 16 in
 // 71 us, 210M at k = 15 in 88 us), or by the pair index a pair per hot row-1
-// cell: 10 ps at k = 16 and 17 at k = 15, where a pair has 2 and 5 parts to
-// look at. Every kernel of the searches evaluates this on the same counts, so
-// exactly one of them runs.
+// cell: 6.5 ps with the four-part records (6.1M in 44 us), 8.6 with the
+// six-part ones (2.6M in 26 us), and by the lists, as k = 14 has it, 5
+// addresses' worth a part more than 13. Every kernel of the searches evaluates
+// this on the same counts, so exactly one of them runs.
 constexpr double LATTICE_COST = 0.1;                    // an address, in join items
-constexpr double PAIR_COST = 13, PAIR_PART_COST = 5;    // a pair and a part, in addresses
+// a pair, in addresses
+__device__ constexpr double pair_cost(uint32_t k) {
+  return k >= 16 ? 15.0 : k == 15 ? 20.0 : 13.0 + 5.0 * (pair_span(k) + 1);
+}
 
 __device__ __forceinline__ double pair_work(const Geom &G, const DevState *st) {
-  return (double)st->he_count[1] * (PAIR_COST + PAIR_PART_COST * (pair_span(G.k) + 1));
+  return (double)st->he_count[1] * pair_cost(G.k);
 }
 // ways: what the sketch has, LAT_OK and LAT_PAIRS (see Lattice).
 constexpr uint32_t LAT_OK = 1, LAT_PAIRS = 2;
@@ -953,16 +957,20 @@ __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
 // bits, c0 ^ c1, and of its 2^(32-k) high parts z only those are in cell c0
 // for which A0 z 2^k (mod 2^64) lies in an interval of 2^(64-k): 2^(32-2k)
 // parts on average, which the index gives by the bucket the interval starts
-// in. So the walk's addresses that fail row 1 are never made. A wave takes
+// in: in a record, or (k = 14, and where a record does not hold them) in a
+// list. So the walk's addresses that fail row 1 are never made. A wave takes
 // 64 PAIR_UNROLL pairs of one c0 and looks at all parts of the interval's
 // buckets, which may hold some outside it: each part's LE in row 2 is tested
 // in LDS, those that pass (a few percent) go to the wave's queue, and 64 of
 // them together are hashed (exactly the addresses of cell c0 stay) and
 // tested in the rows past 2. Each address has one (c0, c1), so there are no
-// duplicates. Bound by the cache lines that the lookups bring (two to three
-// a pair, from the L2). Search of a 9M-pair window, k = 15, 2.6M pairs (210M
-// addresses): 88 -> 43 us; a 4M-pair one, k = 15, r = 4, which took the join,
-// 44 -> 14 us; k = 16, 6.1M pairs (162M addresses) 71 -> 61 us.
+// duplicates. Bound by vector issue and the cache line that each pair's
+// record brings from the L2: with the records 26 us, by the lists (two to
+// three lines a pair) 43, for the 2.6M pairs (210M addresses, a walk of 88
+// us) of a 9M-pair window at k = 15; k = 16, 6.1M pairs (162M addresses, 71
+// us) 44 us, by the lists 61, with three parts of 21 bits a record 50 (a fifth
+// of the buckets of the default seed held a fourth); a 4M-pair window at k =
+// 15, r = 4, which took the join, 44 -> 13 us.
 constexpr uint32_t PAIR_UNROLL = 4;                     // pairs per lane at once
 constexpr uint32_t PAIR_QUEUE = 128;                    // 63 + 64 addresses per wave
 constexpr uint32_t PAIR_THREADS = 1024;
@@ -977,9 +985,11 @@ inline uint32_t pair_rows(const Geom &G) {
   return n;
 }
 
+// RW: 64-bit words of a bucket's record (pair_rec_words).
+template <int RW>
 __global__ __launch_bounds__(PAIR_THREADS) void k_pairs(
     Geom G, const uint32_t *__restrict__ pair_off, const uint32_t *__restrict__ pair_z,
-    uint32_t ways, uint32_t path, const uint32_t *__restrict__ he,
+    const uint32_t *__restrict__ pair_rec, uint32_t ways, uint32_t path, const uint32_t *__restrict__ he,
     const uint32_t *__restrict__ hotmask, DevState *__restrict__ st,
     uint32_t *__restrict__ cand, size_t cand_cap, double e_theta, uint32_t lds_rows) {
   // lds_rows * 2^k bits, the candidates, then the queues
@@ -1018,47 +1028,91 @@ __global__ __launch_bounds__(PAIR_THREADS) void k_pairs(
       }
       found->add(ad, ok, st, cand, cand_cap);
     };
+    // one part per lane: its address queued if its LE in row 2 is hot
+    auto look = [&](uint32_t low, uint32_t z, bool ok) {
+      const uint32_t ad = low | (z << k), x = c0 ^ __builtin_amdgcn_ubfe(ad, alpha, k);
+      ok = ok && ((row2[x >> 5] >> (x & 31)) & 1u);
+      const unsigned long long m = __ballot(ok);
+      if (m == 0) return;
+      if (ok) queue[qn + lanes_below(m)] = ad;
+      qn += (uint32_t)__popcll(m);
+      __builtin_amdgcn_wave_barrier();
+      if (qn >= 64) {
+        qn -= 64;
+        const uint32_t ad2 = queue[qn + lane];
+        __builtin_amdgcn_wave_barrier();
+        test(ad2, true);
+      }
+    };
     const uint64_t lo0 = ((uint64_t)c0 << (64 - k)) - G.b0;
-    uint32_t low[PAIR_UNROLL], q[PAIR_UNROLL], n[PAIR_UNROLL];
+    uint32_t low[PAIR_UNROLL], b[PAIR_UNROLL];
 #pragma unroll
     for (uint32_t u = 0; u < PAIR_UNROLL; u++)
       low[u] = c0 ^ HE1[x1 + 64 * u < h1 ? x1 + 64 * u : h1 - 1];
 #pragma unroll
     for (uint32_t u = 0; u < PAIR_UNROLL; u++)
-      q[u] = pair_off[(uint32_t)((lo0 - G.a0 * low[u]) >> 32) >> k];
-    uint32_t most = 0;
+      b[u] = (uint32_t)((lo0 - G.a0 * low[u]) >> 32) >> k;
+    uint32_t listed = 0;                                // pairs that go by off and z (bit u)
 #pragma unroll
-    for (uint32_t u = 0; u < PAIR_UNROLL; u++) {
-      n[u] = q[u] >> PAIR_PLACE_BITS;
-      if (n[u] == PAIR_MANY) n[u] = parts;              // more than the index says: any part
-      if (x1 + 64 * u >= h1) n[u] = 0;
-      q[u] &= (1u << PAIR_PLACE_BITS) - 1;
-      most = n[u] > most ? n[u] : most;
-    }
-    for (uint32_t t = 0; __ballot(t < most); t += 4) {
-      uint32_t z[PAIR_UNROLL][4];
+    for (uint32_t u = 0; u < PAIR_UNROLL; u++)
+      if (x1 + 64 * u < h1) listed |= 1u << u;
+    if constexpr (RW > 0) {
+      uint32_t rec[PAIR_UNROLL][2 * RW];
 #pragma unroll
       for (uint32_t u = 0; u < PAIR_UNROLL; u++)
-        __builtin_memcpy(z[u], pair_z + q[u] + (t < n[u] ? t : 0u), 16);
+        __builtin_memcpy(rec[u], __builtin_assume_aligned(pair_rec + (size_t)b[u] * (2 * RW), 8 * RW),
+                         8 * RW);
+      const uint32_t live = listed;
+      listed = 0;
 #pragma unroll
       for (uint32_t u = 0; u < PAIR_UNROLL; u++) {
+        bool on = (live >> u) & 1u;
+        if constexpr (RW == 1) {
+          const uint32_t z0 = rec[u][0] & 0xFFFF, z1 = rec[u][0] >> 16, z2 = rec[u][1] & 0xFFFF,
+                         z3 = rec[u][1] >> 16;
+          if (on && z1 == z0 && z2 != z0) {
+            listed |= 1u << u;
+            on = false;
+          }
+          look(low[u], z0, on);
+          look(low[u], z1, on && z1 != z0);
+          look(low[u], z2, on && z2 != z0);
+          look(low[u], z3, on && z3 != z0);
+        } else {
+          if (on && rec[u][1] >> 31) listed |= 1u << u;   // its words hold no part
 #pragma unroll
-        for (uint32_t i = 0; i < 4; i++) {
-          const uint32_t ad = low[u] | (z[u][i] << k);
-          const uint32_t x = c0 ^ __builtin_amdgcn_ubfe(ad, alpha, k);
-          const bool ok = t + i < n[u] && ((row2[x >> 5] >> (x & 31)) & 1u);
-          const unsigned long long m = __ballot(ok);
-          if (m == 0) continue;
-          if (ok) queue[qn + lanes_below(m)] = ad;
-          qn += (uint32_t)__popcll(m);
-          __builtin_amdgcn_wave_barrier();
-          if (qn >= 64) {
-            qn -= 64;
-            const uint32_t ad2 = queue[qn + lane];
-            __builtin_amdgcn_wave_barrier();
-            test(ad2, true);
+          for (int i = 0; i < RW; i++) {
+            const uint32_t lo = rec[u][2 * i], hi = rec[u][2 * i + 1];
+            const uint32_t z[3] = {lo & PAIR_NONE,
+                                   __builtin_amdgcn_alignbit(hi, lo, 21) & PAIR_NONE,
+                                   __builtin_amdgcn_ubfe(hi, 10, 21)};
+#pragma unroll
+            for (int j = 0; j < 3; j++) look(low[u], z[j], on && z[j] != PAIR_NONE);
           }
         }
+      }
+    }
+    if (RW == 0 || __ballot(listed != 0)) {
+      uint32_t q[PAIR_UNROLL], n[PAIR_UNROLL], most = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < PAIR_UNROLL; u++)
+        q[u] = (listed >> u) & 1u ? pair_off[b[u]] : 0u;
+#pragma unroll
+      for (uint32_t u = 0; u < PAIR_UNROLL; u++) {
+        n[u] = q[u] >> PAIR_PLACE_BITS;
+        if (n[u] == PAIR_MANY) n[u] = parts;            // more than the index says: any part
+        q[u] &= (1u << PAIR_PLACE_BITS) - 1;
+        most = n[u] > most ? n[u] : most;
+      }
+      for (uint32_t t = 0; __ballot(t < most); t += 4) {
+        uint32_t z[PAIR_UNROLL][4] = {};
+#pragma unroll
+        for (uint32_t u = 0; u < PAIR_UNROLL; u++)
+          if (t < n[u]) __builtin_memcpy(z[u], pair_z + q[u] + t, 16);
+#pragma unroll
+        for (uint32_t u = 0; u < PAIR_UNROLL; u++)
+#pragma unroll
+          for (uint32_t i = 0; i < 4; i++) look(low[u], z[u][i], t + i < n[u]);
       }
     }
     if (qn) test(queue[lane < qn ? lane : 0], lane < qn);
@@ -1068,7 +1122,7 @@ __global__ __launch_bounds__(PAIR_THREADS) void k_pairs(
 }
 
 // The pair index, built once per sketch: the counts per bucket become their
-// starts (one block), the parts take their places, and then the second copy
+// starts, the parts take their places, and then the second copy
 // of the parts and the bucket words are made.
 __device__ __forceinline__ uint32_t pair_bucket(const Geom &G, uint32_t z) {
   return (uint32_t)((G.a0 * z) << G.k >> 32) >> G.k;
@@ -1078,22 +1132,31 @@ __global__ __launch_bounds__(256) void k_pair_count(Geom G, uint32_t *__restrict
   atomicAdd(&cnt[pair_bucket(G, blockIdx.x * 256 + threadIdx.x)], 1u);
 }
 
-__global__ __launch_bounds__(1024) void k_pair_starts(Geom G, uint32_t *__restrict__ cnt,
+// Block x: the starts of 4096 buckets, after the parts of all buckets before
+// them, which it adds up itself (one block for all took 80 us at k = 14).
+__global__ __launch_bounds__(1024) void k_pair_starts(Geom G, const uint32_t *__restrict__ cnt,
+                                                      uint32_t *__restrict__ start,
                                                       uint32_t *__restrict__ cur, uint32_t n) {
   __shared__ uint32_t sh[17];
-  uint32_t done = 0;
-  for (uint32_t b0 = 0; b0 < n; b0 += 4096) {           // n: a multiple of 4096
-    uint4 *p = reinterpret_cast<uint4 *>(cnt + b0) + threadIdx.x;
-    const uint4 c = *p;
-    uint32_t total;
-    const uint32_t x = done + block_excl_scan<1024>(c.x + c.y + c.z + c.w, &total, sh);
-    const uint4 st = make_uint4(x, x + c.x, x + c.x + c.y, x + c.x + c.y + c.z);
-    *p = st;
-    reinterpret_cast<uint4 *>(cur + b0)[threadIdx.x] = st;
-    done += total;
+  const uint32_t tid = threadIdx.x, i = blockIdx.x * 1024 + tid;
+  const uint4 *c4 = reinterpret_cast<const uint4 *>(cnt);
+  uint32_t sum = 0, before, total;
+#pragma unroll 4
+  for (uint32_t j = tid; j < blockIdx.x * 1024; j += 1024) {
+    const uint4 c = c4[j];
+    sum += c.x + c.y + c.z + c.w;
   }
-  __syncthreads();
-  if (threadIdx.x <= pair_span(G.k)) cnt[n + threadIdx.x] = n + cnt[threadIdx.x];
+  block_excl_scan<1024>(sum, &before, sh);
+  const uint4 c = c4[i];
+  const uint32_t x = before + block_excl_scan<1024>(c.x + c.y + c.z + c.w, &total, sh);
+  const uint4 st = make_uint4(x, x + c.x, x + c.x + c.y, x + c.x + c.y + c.z);
+  reinterpret_cast<uint4 *>(start)[i] = st;
+  reinterpret_cast<uint4 *>(cur)[i] = st;
+  if (blockIdx.x == 0) {                                // the starts that go round
+    const uint32_t v[4] = {st.x, st.y, st.z, st.w};
+    for (uint32_t u = 0; u < 4; u++)
+      if (4 * i + u <= pair_span(G.k)) start[n + 4 * i + u] = n + v[u];
+  }
 }
 
 __global__ __launch_bounds__(256) void k_pair_place(Geom G, uint32_t *__restrict__ z, uint32_t n) {
@@ -1102,23 +1165,45 @@ __global__ __launch_bounds__(256) void k_pair_place(Geom G, uint32_t *__restrict
 }
 
 __global__ __launch_bounds__(256) void k_pair_finish(Geom G, uint32_t *__restrict__ off,
-                                                     uint32_t *__restrict__ z, uint32_t n) {
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+                                                     uint32_t *__restrict__ z,
+                                                     uint32_t *__restrict__ rec, uint32_t n) {
+  const uint32_t b = blockIdx.x * 256 + threadIdx.x;
   const uint32_t *start = off + n;
-  z[n + i] = z[i];
-  if (i < 4) z[2 * n + i] = 0;
-  const uint32_t parts = start[i + pair_span(G.k) + 1] - start[i];
-  off[i] = start[i] | (parts < PAIR_MANY ? parts : PAIR_MANY) << PAIR_PLACE_BITS;
+  z[n + b] = z[b];
+  if (b < 4) z[2 * n + b] = 0;
+  const uint32_t at = start[b], parts = start[b + pair_span(G.k) + 1] - at;
+  off[b] = at | (parts < PAIR_MANY ? parts : PAIR_MANY) << PAIR_PLACE_BITS;
+  const uint32_t rw = pair_rec_words(G.k);
+  uint64_t *words = reinterpret_cast<uint64_t *>(rec) + (size_t)b * rw;
+  // part i from bucket b on, of the first copy (complete before this kernel)
+  auto part = [&](uint32_t i) { return (uint64_t)z[(at + i) & (n - 1)]; };
+  if (rw == 1) {
+    uint64_t w = 0x0001000100000000ull;
+    if (parts <= 4) {
+      w = 0;
+      for (uint32_t j = 0; j < 4; j++) w |= part(j < parts ? j : 0) << (16 * j);
+    }
+    words[0] = w;
+  } else {
+    const bool fits = parts <= 3 * rw;
+    for (uint32_t i = 0; i < rw; i++) {
+      uint64_t w = fits ? 0 : 1ull << 63;
+      for (uint32_t j = 3 * i; j < 3 * i + 3; j++)
+        w |= (fits && j < parts ? part(j) : PAIR_NONE) << (21 * (j - 3 * i));
+      words[i] = w;
+    }
+  }
 }
 
-hipError_t launch_pair_index(const Geom &G, uint32_t *off, uint32_t *z, hipStream_t st) {
+hipError_t launch_pair_index(const Geom &G, uint32_t *off, uint32_t *z, uint32_t *rec,
+                             hipStream_t st) {
   const uint32_t n = 1u << (32 - G.k), blocks = n / 256;
-  hipError_t e = launch_fill_u32(off + n, n, 0u, 64, st);
+  hipError_t e = launch_fill_u32(off, n, 0u, 64, st);
   if (e != hipSuccess) return e;
-  k_pair_count<<<blocks, 256, 0, st>>>(G, off + n);
-  k_pair_starts<<<1, 1024, 0, st>>>(G, off + n, z + n, n);
+  k_pair_count<<<blocks, 256, 0, st>>>(G, off);
+  k_pair_starts<<<n / 4096, 1024, 0, st>>>(G, off, off + n, z + n, n);
   k_pair_place<<<blocks, 256, 0, st>>>(G, z, n);
-  k_pair_finish<<<blocks, 256, 0, st>>>(G, off, z, n);
+  k_pair_finish<<<blocks, 256, 0, st>>>(G, off, z, rec, n);
   return hipGetLastError();
 }
 
@@ -1937,6 +2022,16 @@ static void launch_walk(const Geom &G, const RestoreBufs &B, double e_theta, hip
                                                   e_theta);
 }
 
+template <int RW>
+static void launch_pairs(const Geom &G, const RestoreBufs &B, uint32_t ways, double e_theta,
+                         int grid, hipStream_t st) {
+  const uint32_t rows = pair_rows(G);
+  k_pairs<RW><<<grid > 3 ? grid / 4 : 1, PAIR_THREADS,
+                rows * (4u << (G.k - 5)) + LAT_FOUND_BYTES + PAIR_QUEUE_BYTES, st>>>(
+      G, B.lat.pair_off, B.lat.pair_z, B.lat.pair_rec, ways, B.cand_path, B.he, B.hotmask, B.st,
+      B.cand, B.cand_cap, e_theta, rows);
+}
+
 static void launch_join(const Geom &G, const RestoreBufs &B, double e_theta, hipStream_t st) {
   const uint32_t r = G.r, jb = B.jblk, pth = B.cand_path;
   const uint32_t ways = lattice_ways(B.lat);
@@ -2036,11 +2131,10 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
         G, B.lat, ways, B.cand_path, B.he, B.hotmask, B.st, B.cand, B.cand_cap, e_theta, rows);
   }
   if (pairs) {
-    const uint32_t rows = pair_rows(G);
-    k_pairs<<<grid > 3 ? grid / 4 : 1, PAIR_THREADS,
-              rows * (4u << (k - 5)) + LAT_FOUND_BYTES + PAIR_QUEUE_BYTES, st>>>(
-        G, B.lat.pair_off, B.lat.pair_z, ways, B.cand_path, B.he, B.hotmask, B.st, B.cand,
-        B.cand_cap, e_theta, rows);
+    const uint32_t rw = pair_rec_words(k);
+    if (rw == 0) launch_pairs<0>(G, B, ways, e_theta, grid, st);
+    else if (rw == 1) launch_pairs<1>(G, B, ways, e_theta, grid, st);
+    else launch_pairs<2>(G, B, ways, e_theta, grid, st);
   }
   if (join) launch_join(G, B, e_theta, st);
   mark(3);
@@ -2074,9 +2168,11 @@ hipError_t prepare_restore_kernels() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_lattice),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)LATTICE_LDS_MAX);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_pairs),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 81920);
+  for (const void *f : {reinterpret_cast<const void *>(k_pairs<0>),
+                        reinterpret_cast<const void *>(k_pairs<1>),
+                        reinterpret_cast<const void *>(k_pairs<2>)})
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 81920);
   return e;
 }
 
