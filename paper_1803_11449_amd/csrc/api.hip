@@ -154,8 +154,10 @@ int lane_record(Lane &l) {
   return SKETCH_OK;
 }
 
+// (Every owner is destroyed after its device was synchronized: an event not
+// yet recorded need not be.)
 void lane_free(Lane &l) {
-  if (l.armed && lane_record(l) == SKETCH_OK) (void)hipEventSynchronize(l.ev);
+  if (l.armed && !l.late) (void)hipEventSynchronize(l.ev);
   if (l.ev) (void)hipEventDestroy(l.ev);
   l.ev = nullptr;
   l.armed = l.late = false;

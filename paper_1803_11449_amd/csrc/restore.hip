@@ -46,7 +46,7 @@
 // With the walk, the one-launch scan and sort, the 1M-pair window's restore
 // went from 11 launches (47 us of kernels) to 4, and the whole window from
 // 125 to 103 us; a 60,000-pair window with a few hundred hot LEs per row
-// from 137 to 77 us.
+// from 137 to 77 us (81 and 56 with fewer ordering events, see Lane).
 #include <math.h>
 
 #include "ddhf_internal.h"
