@@ -772,12 +772,15 @@ uint32_t join_grid(const sketch *s, bool walk) {
   return walk ? 2 * n_cu : most;
 }
 
-RestoreBufs restore_bufs(const sketch *s, const RPool &p, const Thresholds &t) {
+// by_last: the restore may go by what the last one found. Only where it is
+// waited for in the same call: when that turns out wrong it is run again, on
+// the sketch as it is by then.
+RestoreBufs restore_bufs(const sketch *s, const RPool &p, const Thresholds &t, bool by_last) {
   RestoreBufs B{};
   B.lez = s->lez;
   B.lez_stale = !s->lez_valid;
   B.chunks = s->chunks;
-  if (s->hint_e == t.e_theta) {
+  if (by_last && s->hint_e == t.e_theta) {
     if (s->cand_path == 0 || (s->cand_path == 2 && s->hint_search >= 2)) B.expect = s->hint_search;
     B.sort_one = s->hint_n <= SORT_ONE_HINT;
   }
@@ -892,11 +895,11 @@ int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresho
   return rc;
 }
 
-// The restore on restore pool i, enqueued on st.
+// The restore on restore pool i, enqueued on st (by_last: see restore_bufs).
 int restore_launch_pool(sketch *s, const Thresholds &t, int estimate, int i, hipStream_t st,
-                        bool waited = false) {
+                        bool by_last, bool waited = false) {
   RPool &p = s->ctx->pool[i];
-  const RestoreBufs B = restore_bufs(s, p, t);
+  const RestoreBufs B = restore_bufs(s, p, t, by_last);
   s->ran_seg_cap = B.seg_cap;
   s->ran_cand_cap = B.cand_cap;
   s->ran_spl_cap = B.spl_cap;
@@ -982,7 +985,7 @@ hipError_t batch_join(DevCtx *c, const uint8_t *used, hipStream_t st) {
 // sort ranks, segment counts, candidates and records (each with its sorted
 // copy) at fixed sizes, the rest split into the join's partial segments.
 RestoreBufs noalloc_bufs(const sketch *s, uint8_t *base, const Thresholds &t) {
-  RestoreBufs B = restore_bufs(s, s->ctx->pool[0], t);   // every pool buffer replaced below
+  RestoreBufs B = restore_bufs(s, s->ctx->pool[0], t, true);   // every pool buffer replaced below
   // a sketch set to the join keeps its stages here, which refuse partial
   // addresses beyond the array
   if (s->cand_path == 1) {
@@ -1065,7 +1068,7 @@ int restore_check(sketch *s, int estimate, bool *again) {
 int run_restore(sketch *s, const Thresholds &t, int estimate, hipStream_t st) {
   for (int attempt = 0; attempt < 16; attempt++) {
     // on the device's first restore pool, on the caller's stream
-    int rc = restore_launch_pool(s, t, estimate, 0, st, true);
+    int rc = restore_launch_pool(s, t, estimate, 0, st, true, true);
     if (rc) return rc;
     HIP_OK(hipStreamSynchronize(st));
     lane_done(s->ctx->pool[0].lane);
@@ -1532,8 +1535,6 @@ struct PlanJob {
   size_t ran_seg_cap = 0, ran_cand_cap = 0;   // pool capacities of the capture
   int pool = 0;                 // restore pool of the captured restore
   bool eager = false;           // this result comes from an eager rerun
-  bool ran_sort_one = false;    // what the captured restore launches
-  uint32_t ran_expect = 0;
   bool fresh = false;           // RESET plan: the first binned round writes every
                                 // tile from zeros, so no zero fill
 };
@@ -1559,7 +1560,6 @@ struct sketch_plan {
   bool dirty = true;            // a plan-owned buffer changed since the capture
   uint64_t gen = ~0ull;         // device context generation at the capture
   bool ran = false;             // the graph has run at least once
-  bool trimmed = false;         // captured (or about to be) for what the first run showed
   hipStream_t run_stream = nullptr;
 };
 
@@ -1609,7 +1609,9 @@ int plan_alloc_sorted(PlanJob &j, size_t cap) {
 
 RestoreBufs plan_restore_bufs(const sketch_plan *P, const PlanJob &j) {
   const RPool &pool = P->ctx->pool[j.pool];
-  RestoreBufs B = restore_bufs(j.s, pool, j.t);    // the sketch's rows, the job's pool
+  // the sketch's rows, the job's pool; every kernel, as a run is waited for in
+  // another call
+  RestoreBufs B = restore_bufs(j.s, pool, j.t, false);
   // the zero counts are known valid at capture only when each run starts
   // the window and its update writes every tile
   B.lez_stale = !((P->flags & SKETCH_PLAN_RESET) && j.fresh);
@@ -1687,9 +1689,6 @@ int plan_build_graph(sketch_plan *P) {
     j.ran_cand_cap = pool.cand_cap;
     j.ran_spl_cap = std::min(pool.spl_cap, j.sorted_cap);
     j.ran_h_recs_cap = j.h_recs_cap;
-    const RestoreBufs B = plan_restore_bufs(P, j);
-    j.ran_sort_one = B.sort_one;
-    j.ran_expect = B.expect;
   }
   P->gen = c->gen;
   P->dirty = false;
@@ -1973,7 +1972,9 @@ int sketch_restore_noalloc(sketch_t *s, double theta, sketch_sp_t *out, size_t c
   return SKETCH_OK;
 }
 
-int sketch_restore_batch_begin(sketch_restore_job_t *jobs, size_t n_jobs, void *hip_stream) {
+// by_last: see restore_bufs.
+static int restore_batch_begin(sketch_restore_job_t *jobs, size_t n_jobs, void *hip_stream,
+                               bool by_last) {
   if (n_jobs == 0) return SKETCH_OK;
   int rc = check_restore_jobs(jobs, n_jobs, "sketch_restore_batch_begin");
   if (rc) return rc;
@@ -2006,7 +2007,7 @@ int sketch_restore_batch_begin(sketch_restore_job_t *jobs, size_t n_jobs, void *
     sketch *s = jobs[j].sketch;
     const hipStream_t js = pool_stream(c, pools[j], st);
     s->pend_t = thresholds(s, jobs[j].theta);
-    rc = restore_launch_pool(s, s->pend_t, 1, pools[j], js);
+    rc = restore_launch_pool(s, s->pend_t, 1, pools[j], js, by_last);
     if (!rc && hipEventRecord(s->restore_ev, js) != hipSuccess)
       rc = fail(SKETCH_E_HIP, "sketch_restore_batch_begin: hipEventRecord failed");
     if (rc) return rc;
@@ -2015,6 +2016,10 @@ int sketch_restore_batch_begin(sketch_restore_job_t *jobs, size_t n_jobs, void *
   if (batch_join(c, used, st) != hipSuccess)
     return fail(SKETCH_E_HIP, "sketch_restore_batch_begin: stream join failed");
   return SKETCH_OK;
+}
+
+int sketch_restore_batch_begin(sketch_restore_job_t *jobs, size_t n_jobs, void *hip_stream) {
+  return restore_batch_begin(jobs, n_jobs, hip_stream, false);
 }
 
 int sketch_restore_batch_end(sketch_restore_job_t *jobs, size_t n_jobs, void *hip_stream) {
@@ -2056,7 +2061,7 @@ int sketch_restore_batch_end(sketch_restore_job_t *jobs, size_t n_jobs, void *hi
 }
 
 int sketch_restore_batch(sketch_restore_job_t *jobs, size_t n_jobs, void *hip_stream) {
-  int rc = sketch_restore_batch_begin(jobs, n_jobs, hip_stream);
+  int rc = restore_batch_begin(jobs, n_jobs, hip_stream, true);
   if (rc) return rc;
   return sketch_restore_batch_end(jobs, n_jobs, hip_stream);
 }
@@ -2452,9 +2457,6 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
     int rc = SKETCH_OK;
     pj.eager = false;
     note_cost(s, *h, pj.t.e_theta);
-    // the captured restore left out what this window needs (see restore_check)
-    const bool other = !h->saturated && h->search == 0;
-    const bool partial = other || (pj.ran_sort_one && h->n_spl > RESTORE_SORT_ONE);
     if (h->saturated) {
       rc = SKETCH_E_SATURATED;
     } else {
@@ -2464,15 +2466,8 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
       // a stage overflowed if its count passed the capacity the graph ran
       // with; the shared buffers grow as for an eager restore (which moves
       // them, so the next run captures again) and this job runs again alone
-      if (partial) {
-        if (other) s->hint_e = -1.0;
-        P->dirty = true;                // captured again with what it needs
-        rc = run_restore(s, pj.t, 1, st);
-        h = s->h_state;
-        src = s->spl_sorted;
-        pj.eager = true;
-      } else if (need_part > pj.ran_seg_cap || h->n_cand > pj.ran_cand_cap ||
-                 h->n_spl > pj.ran_spl_cap) {
+      if (need_part > pj.ran_seg_cap || h->n_cand > pj.ran_cand_cap ||
+          h->n_spl > pj.ran_spl_cap) {
         if (h->n_spl > pj.sorted_cap) {
           rc = plan_alloc_sorted(pj, grown(h->n_spl, pj.sorted_cap));
           P->dirty = true;
@@ -2517,15 +2512,6 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
     if (rc && !first_err) first_err = rc;
   }
   HIP_OK(hipStreamSynchronize(st));
-  // captured once more now that the first run has shown each job's search and
-  // list size, so that the graph holds only the kernels they need
-  if (!P->trimmed) {
-    P->trimmed = true;
-    for (const PlanJob &pj : P->jobs) {
-      const RestoreBufs B = plan_restore_bufs(P, pj);
-      if (B.expect != pj.ran_expect || (bool)B.sort_one != pj.ran_sort_one) P->dirty = true;
-    }
-  }
   if (first_err)
     return fail(first_err, "sketch_plan_results: a job failed (see each job's status)");
   return SKETCH_OK;

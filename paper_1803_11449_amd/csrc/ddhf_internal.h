@@ -139,9 +139,9 @@ struct RestoreBufs {
   // (0 = by estimated work, 1 = the join of Algs. 3-4, 2 = the lattice)
   Lattice lat;
   uint32_t cand_path;
-  // what to launch, by the sketch's last restore: only the search that ran
-  // then (0 = any, 1 = the join, 2 = the lattice, 3 = the lattice by pairs),
-  // and the one-launch sort.
+  // what to launch, by the sketch's last restore, where the restore is waited
+  // for in the same call: only the search that ran then (0 = any, 1 = the
+  // join, 2 = the lattice, 3 = the lattice by pairs), and the one-launch sort.
   // A restore whose counts then call for the other search, or whose list is
   // longer, leaves that to see in the state (search 0, n_spl) and is run again
   uint32_t expect;

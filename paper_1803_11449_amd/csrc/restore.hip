@@ -42,7 +42,8 @@
 //
 // A restore is a chain of short kernels, and for a small sketch their number
 // sets its time. Where the sketch's last restore at the same threshold says
-// what this one needs, only that is launched (RestoreBufs::expect, sort_one).
+// what this one needs, and the call that launches it also waits for it, only
+// that is launched (RestoreBufs::expect, sort_one).
 // With the walk, the one-launch scan and sort, the 1M-pair window's restore
 // went from 11 launches (47 us of kernels) to 4, and the whole window from
 // 125 to 103 us; a 60,000-pair window with a few hundred hot LEs per row
