@@ -216,7 +216,9 @@ int sketch_restore_batch(sketch_restore_job_t *jobs, size_t n_jobs, void *hip_st
  * returns without waiting; it reads only the sketch and theta of each job.
  * _end waits for each job's restore (not for other work on the stream),
  * runs a job again on hip_stream if its output outgrew the shared buffers,
- * and fills out, info, n_out and status as sketch_restore_batch does.
+ * and fills out, info, n_out and status as sketch_restore_batch does. A job
+ * that has to run again after its sketch was updated meanwhile is lost: its
+ * status is CAPACITY with n_out 0 (the buffers have grown for the next).
  * Between the two calls the jobs' sketches may be used by no other call
  * except sketch_update / sketch_update_batch / sketch_reset, whose device
  * work the library orders after the pending restore (each sketch keeps an
@@ -272,8 +274,10 @@ int sketch_plan_run(sketch_plan_t *plan, void *hip_stream);
  * sketch_restore_batch; theta is written back). Waits for hip_stream. A
  * job whose output overflowed the plan's buffers is restored again on its
  * own and the buffers grow (the graph is rebuilt before the next run), so
- * every job gets exactly what sketch_restore would give. Returns SKETCH_OK
- * if every job succeeded, else the first failing job's code. */
+ * every job gets exactly what sketch_restore would give, unless its sketch
+ * was written again after the run: then its status is CAPACITY with n_out 0.
+ * Returns SKETCH_OK if every job succeeded, else the first failing job's
+ * code. */
 int sketch_plan_results(sketch_plan_t *plan, sketch_restore_job_t *out, size_t n_out,
                         void *hip_stream);
 

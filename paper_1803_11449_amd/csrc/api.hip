@@ -641,9 +641,11 @@ struct sketch {
   DevCtx *ctx = nullptr;
   mutable Lane lane;            // last work on this sketch (any stream)
   // a restore begun by sketch_restore_batch_begin and not yet ended: its
-  // thresholds, and the event that marks the end of its device work
+  // thresholds, the words it reads (writes), and the event that marks the end
+  // of its device work
   bool pending = false;
   Thresholds pend_t{};
+  uint64_t pend_writes = 0;
   hipEvent_t restore_ev = nullptr;
   // SKETCH_OPT_TIMING: events between the restore's phases, and what the
   // last timed restore read
@@ -660,6 +662,10 @@ struct sketch {
   // work that reads the sketch or sets bits in place writes the zeros first
   // (materialize).
   bool fresh = false;
+  // Counts the calls that wrote the sketch's words. A restore that is collected
+  // by a later call can only be run again while they are the ones it read (a
+  // reset alone leaves them in place)
+  uint64_t writes = 0;
   // Zeros per LE as the binned update leaves them (when lez_kept(g)). Valid
   // after a binned update of a fresh window from its first pair (which
   // writes every tile) and through later binned updates (which rewrite the
@@ -866,6 +872,7 @@ Thresholds thresholds(const sketch *s, double theta) {
 int materialize(sketch *s, hipStream_t st) {
   if (!s->fresh) return SKETCH_OK;
   HIP_OK(launch_fill_u32(s->d_sketch, s->words, 0u, s->grid * 4, st));
+  s->writes++;
   s->fresh = false;
   s->lez_valid = false;
   return SKETCH_OK;
@@ -874,11 +881,12 @@ int materialize(sketch *s, hipStream_t st) {
 // Enqueue the restore kernels on buffers B, whose shared part is ordered by
 // `pool`, and the copy of the device state (no wait). waited: the caller waits
 // for st before it lets go of ctx->mu, and then calls lane_done for both
-// lanes. Caller holds ctx->mu.
+// lanes. as_is: of the words in memory, also those of a sketch that has been
+// reset since. Caller holds ctx->mu.
 int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresholds &t,
-                      int estimate, hipStream_t st, bool waited) {
+                      int estimate, hipStream_t st, bool waited, bool as_is = false) {
   int rc = lane_enter(s->lane, st);
-  if (!rc) rc = materialize(s, st);
+  if (!rc && !as_is) rc = materialize(s, st);
   if (!rc) rc = lane_enter(pool, st);
   if (rc) return rc;
   HIP_OK(launch_restore(s->G, s->d_sketch, B, t.zhot, t.e_theta, estimate, s->grid, st,
@@ -895,9 +903,10 @@ int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresho
   return rc;
 }
 
-// The restore on restore pool i, enqueued on st (by_last: see restore_bufs).
+// The restore on restore pool i, enqueued on st (by_last: see restore_bufs;
+// waited, as_is: see restore_launch_on).
 int restore_launch_pool(sketch *s, const Thresholds &t, int estimate, int i, hipStream_t st,
-                        bool by_last, bool waited = false) {
+                        bool by_last, bool waited = false, bool as_is = false) {
   RPool &p = s->ctx->pool[i];
   const RestoreBufs B = restore_bufs(s, p, t, by_last);
   s->ran_seg_cap = B.seg_cap;
@@ -905,7 +914,7 @@ int restore_launch_pool(sketch *s, const Thresholds &t, int estimate, int i, hip
   s->ran_spl_cap = B.spl_cap;
   s->ran_h_recs_cap = B.h_recs_cap;
   s->ran_pool = i;
-  return restore_launch_on(s, B, p.lane, t, estimate, st, waited);
+  return restore_launch_on(s, B, p.lane, t, estimate, st, waited, as_is);
 }
 
 // Relative work of a restore of s: its LEs, and the row-0 addresses the
@@ -1064,11 +1073,13 @@ int restore_check(sketch *s, int estimate, bool *again) {
 
 // Runs the restore pipeline until every buffer held its output (counts are
 // exact on the device even past capacity, so one rerun per grown stage at
-// most). Leaves the final state in s->h_state. Caller holds ctx->mu.
-int run_restore(sketch *s, const Thresholds &t, int estimate, hipStream_t st) {
+// most). Leaves the final state in s->h_state. as_is: see restore_launch_on.
+// Caller holds ctx->mu.
+int run_restore(sketch *s, const Thresholds &t, int estimate, hipStream_t st,
+                bool as_is = false) {
   for (int attempt = 0; attempt < 16; attempt++) {
     // on the device's first restore pool, on the caller's stream
-    int rc = restore_launch_pool(s, t, estimate, 0, st, true, true);
+    int rc = restore_launch_pool(s, t, estimate, 0, st, true, true, as_is);
     if (rc) return rc;
     HIP_OK(hipStreamSynchronize(st));
     lane_done(s->ctx->pool[0].lane);
@@ -1078,6 +1089,16 @@ int run_restore(sketch *s, const Thresholds &t, int estimate, hipStream_t st) {
     if (rc || !again) return rc;
   }
   return fail(SKETCH_E_HIP, "restore: capacities did not settle");
+}
+
+// A restore that a later call collects, whose output outgrew the buffers
+// (which have grown since): again on its own, while the sketch's words are the
+// ones it read (writes: their count then). Caller holds ctx->mu.
+int rerun_restore(sketch *s, const Thresholds &t, uint64_t writes, hipStream_t st) {
+  if (s->writes != writes)
+    return fail(SKETCH_E_CAPACITY, "a restore's output outgrew the buffers after its sketch had "
+                "been written again");
+  return run_restore(s, t, 1, st, true);
 }
 
 // ------------------------------------------------------------------ update
@@ -1483,6 +1504,7 @@ int update_jobs(const sketch_update_job_t *jobs, size_t n_jobs, hipStream_t st) 
     if (jobs[j].n_pairs == 0) continue;
     rc = lane_enter(s->lane, st);
     if (rc) return rc;
+    s->writes++;
     if (s->fresh && writes_all(jobs[j], path[j])) {
       fresh[j] = 1;
       s->fresh = false;
@@ -1535,6 +1557,7 @@ struct PlanJob {
   size_t ran_seg_cap = 0, ran_cand_cap = 0;   // pool capacities of the capture
   int pool = 0;                 // restore pool of the captured restore
   bool eager = false;           // this result comes from an eager rerun
+  uint64_t ran_writes = 0;      // the sketch's writes at the last run
   bool fresh = false;           // RESET plan: the first binned round writes every
                                 // tile from zeros, so no zero fill
 };
@@ -1863,6 +1886,7 @@ int sketch_merge(sketch_t *dst, const sketch_t *src, void *hip_stream) {
   if (!rc) rc = materialize(dst, st);
   if (rc) return rc;
   HIP_OK(launch_or_u32(dst->d_sketch, src->d_sketch, dst->words, dst->grid * 4, st));
+  dst->writes++;
   dst->lez_valid = false;
   rc = lane_leave(dst->lane, st);
   if (!rc) rc = lane_leave(src->lane, st);
@@ -2012,6 +2036,7 @@ static int restore_batch_begin(sketch_restore_job_t *jobs, size_t n_jobs, void *
       rc = fail(SKETCH_E_HIP, "sketch_restore_batch_begin: hipEventRecord failed");
     if (rc) return rc;
     s->pending = true;
+    s->pend_writes = s->writes;
   }
   if (batch_join(c, used, st) != hipSuccess)
     return fail(SKETCH_E_HIP, "sketch_restore_batch_begin: stream join failed");
@@ -2044,7 +2069,7 @@ int sketch_restore_batch_end(sketch_restore_job_t *jobs, size_t n_jobs, void *hi
     s->pending = false;
     bool again = false;
     if (rc == SKETCH_OK) rc = restore_check(s, 1, &again);
-    if (rc == SKETCH_OK && again) rc = run_restore(s, s->pend_t, 1, st);   // this job alone
+    if (rc == SKETCH_OK && again) rc = rerun_restore(s, s->pend_t, s->pend_writes, st);
     const DevState h = *s->h_state;
     if (rc == SKETCH_OK || rc == SKETCH_E_SATURATED)
       fill_info(s, h, s->pend_t.zmin, s->pend_t.zhot, J.info);
@@ -2244,6 +2269,7 @@ int sketch_upload(sketch_t *s, const uint32_t *host_words, size_t n_words, void 
   hipStream_t st = (hipStream_t)hip_stream;
   int rc = lane_enter(s->lane, st);
   if (rc) return rc;
+  s->writes++;
   HIP_OK(hipMemcpyAsync(s->d_sketch, host_words, n_words * 4, hipMemcpyHostToDevice, st));
   HIP_OK(hipStreamSynchronize(st));
   s->fresh = false;
@@ -2408,6 +2434,8 @@ int sketch_plan_run(sketch_plan_t *P, void *hip_stream) {
       if (rc) return rc;
       j.s->lez_valid = false;
     }
+    j.s->writes++;
+    j.ran_writes = j.s->writes;
   }
   int rc = SKETCH_OK;
   for (RPool &p : c->pool)
@@ -2477,7 +2505,7 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
         if (!rc && need_part > pool.seg_cap) rc = grow_partials(c, pool, need_part);
         if (!rc && h->n_cand > pool.cand_cap) rc = grow_cand(c, pool, h->n_cand);
         if (!rc && h->n_spl > pool.spl_cap) rc = grow_pool_spl(c, pool, h->n_spl);
-        if (!rc) rc = run_restore(s, pj.t, 1, st);
+        if (!rc) rc = rerun_restore(s, pj.t, pj.ran_writes, st);
         h = s->h_state;
         src = s->spl_sorted;
         pj.eager = true;

@@ -439,7 +439,7 @@ def _collect(items, res, stream, raise_errors):
         info["status"] = st
         if st == SKETCH_OK:
             out[i] = (recs, info)
-        elif st == SKETCH_E_CAPACITY:
+        elif st == SKETCH_E_CAPACITY and need:
             sk._cap = max(int(need) + 64, 2 * sk._cap)
             retry.append(i)
         elif raise_errors:
@@ -511,7 +511,7 @@ class Plan:
                                                     for sk, _, _ in self.items], s)
             retry = False
             for (sk, _, _), (_, _, st, need) in zip(self.items, res):
-                if st == SKETCH_E_CAPACITY:
+                if st == SKETCH_E_CAPACITY and need:
                     sk._cap = max(int(need) + 64, 2 * sk._cap)
                     retry = True
                 elif st != SKETCH_OK:

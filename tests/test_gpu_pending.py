@@ -81,3 +81,59 @@ def test_plan_run_of_another_kind(what, meanwhile):
         after = next_window(sk, p, meanwhile, words)
         assert_spl_equal(plan.results()[0][0], ip, sz, c)
         assert np.array_equal(sk.download(), after)
+
+
+def overflowing(p, m):
+    """A window of m super points: past the 6144 records a handle's sorted list
+    starts with, so that a first restore is run again."""
+    words = hosts_sketch(p, m, m)
+    return (words, *oracle.restore(p, words, 100.0, mode="brute")[:3])
+
+
+@pytest.mark.parametrize("planned", [False, True])
+@pytest.mark.parametrize("meanwhile", ["reset", "small", "large", "more"])
+def test_a_list_that_outgrows_the_buffers(meanwhile, planned):
+    """Run again on the words that the restore read, or refused when they have
+    been written again; never another window's list."""
+    p = oracle.Params(128, 18, 5, 5)
+    words, ip, sz, c = overflowing(p, 7000)
+    assert len(ip) > 6144
+    with make_sketch(p) as sk:
+        sk._cap = 1 << 13                   # the caller's own buffer is large enough
+        plan = ddhf.Plan([(sk, to_dev(EMPTY), 100.0)], reset=False) if planned else None
+
+        def start():
+            return plan.run() if planned else ddhf.restore_batch_begin([(sk, 100.0)])
+
+        def collect(pend):
+            return (plan.results() if planned else pend.end())[0][0]
+
+        for again in range(2):              # the first time the buffers grow
+            sk.upload(words)
+            pend = start()
+            after = next_window(sk, p, meanwhile, words)
+            say(f"{len(ip)} records, planned {planned}, {meanwhile}, time {again}")
+            if meanwhile == "reset" or again:
+                assert_spl_equal(collect(pend), ip, sz, c)
+            else:
+                with pytest.raises(ddhf.SketchError) as e:
+                    collect(pend)
+                assert e.value.code == ddhf.SKETCH_E_CAPACITY
+            assert np.array_equal(sk.download(), after)
+        if plan:
+            plan.close()
+
+
+def test_a_lost_job_of_a_batch_leaves_the_others():
+    p = oracle.Params(128, 18, 5, 5)
+    words, *_ = overflowing(p, 7000)
+    small = hosts_sketch(p, 40, 3)
+    with make_sketch(p) as sk, make_sketch(p) as other:
+        sk._cap = 1 << 13
+        sk.upload(words)
+        other.upload(small)
+        pend = ddhf.restore_batch_begin([(sk, 100.0), (other, 100.0)])
+        next_window(sk, p, "large", words)
+        (recs, info), (rest, _) = pend.end(raise_errors=False)
+        assert recs is None and info["status"] == ddhf.SKETCH_E_CAPACITY
+        assert_spl_equal(rest, *oracle.restore(p, small, 100.0, mode="brute")[:3])
