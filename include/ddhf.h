@@ -218,7 +218,9 @@ int sketch_restore_batch(sketch_restore_job_t *jobs, size_t n_jobs, void *hip_st
  * runs a job again on hip_stream if its output outgrew the shared buffers,
  * and fills out, info, n_out and status as sketch_restore_batch does. A job
  * that has to run again after its sketch was updated meanwhile is lost: its
- * status is CAPACITY with n_out 0 (the buffers have grown for the next).
+ * status is CAPACITY with n_out 0 (the buffers have grown for the next). A
+ * job whose cap was too small (CAPACITY, n_out the number needed) may be ended
+ * again with more room, until its sketch's next restore.
  * Between the two calls the jobs' sketches may be used by no other call
  * except sketch_update / sketch_update_batch / sketch_reset, whose device
  * work the library orders after the pending restore (each sketch keeps an

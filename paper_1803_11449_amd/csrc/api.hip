@@ -646,6 +646,9 @@ struct sketch {
   bool pending = false;
   Thresholds pend_t{};
   uint64_t pend_writes = 0;
+  // one that has been ended with too small an output buffer: its state and
+  // records stay until the sketch's next restore
+  bool held = false;
   hipEvent_t restore_ev = nullptr;
   // SKETCH_OPT_TIMING: events between the restore's phases, and what the
   // last timed restore read
@@ -891,6 +894,7 @@ int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresho
   if (rc) return rc;
   HIP_OK(launch_restore(s->G, s->d_sketch, B, t.zhot, t.e_theta, estimate, s->grid, st,
                         s->timing ? s->tev : nullptr));
+  s->held = false;
   s->ran_e = t.e_theta;
   s->ran_sort_one = B.sort_one;
   if (s->timing) {
@@ -2052,7 +2056,7 @@ int sketch_restore_batch_end(sketch_restore_job_t *jobs, size_t n_jobs, void *hi
   int rc = check_restore_jobs(jobs, n_jobs, "sketch_restore_batch_end");
   if (rc) return rc;
   for (size_t j = 0; j < n_jobs; j++)
-    if (!jobs[j].sketch->pending)
+    if (!jobs[j].sketch->pending && !jobs[j].sketch->held)
       return fail(SKETCH_E_INVAL, "sketch_restore_batch_end: job %zu's sketch has no begun "
                   "restore", j);
   DEVICE_GUARD(jobs[0].sketch->p.device);
@@ -2063,18 +2067,20 @@ int sketch_restore_batch_end(sketch_restore_job_t *jobs, size_t n_jobs, void *hi
     sketch_restore_job_t &J = jobs[j];
     sketch *s = J.sketch;
     // wait for this restore only (outside the lock: other work may be queued)
-    rc = hipEventSynchronize(s->restore_ev) == hipSuccess
-             ? SKETCH_OK : fail(SKETCH_E_HIP, "sketch_restore_batch_end: hipEventSynchronize");
+    rc = SKETCH_OK;
+    if (s->pending && hipEventSynchronize(s->restore_ev) != hipSuccess)
+      rc = fail(SKETCH_E_HIP, "sketch_restore_batch_end: hipEventSynchronize");
     std::lock_guard<std::mutex> lk(c->mu);
-    s->pending = false;
     bool again = false;
-    if (rc == SKETCH_OK) rc = restore_check(s, 1, &again);
+    if (rc == SKETCH_OK && s->pending) rc = restore_check(s, 1, &again);
+    s->pending = false;
     if (rc == SKETCH_OK && again) rc = rerun_restore(s, s->pend_t, s->pend_writes, st);
     const DevState h = *s->h_state;
     if (rc == SKETCH_OK || rc == SKETCH_E_SATURATED)
       fill_info(s, h, s->pend_t.zmin, s->pend_t.zhot, J.info);
     J.n_out = rc == SKETCH_OK ? (size_t)h.n_spl : 0;
-    if (rc == SKETCH_OK && h.n_spl > J.cap) rc = SKETCH_E_CAPACITY;
+    s->held = rc == SKETCH_OK && h.n_spl > J.cap;
+    if (s->held) rc = SKETCH_E_CAPACITY;
     if (rc == SKETCH_OK)
       rc = copy_records(s, J.out, (size_t)h.n_spl, s->ran_h_recs_cap, st);
     J.status = rc;

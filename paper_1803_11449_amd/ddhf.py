@@ -426,13 +426,14 @@ def restore_batch(items, stream=None, raise_errors: bool = True):
         return []
     dev = items[0][0].device
     s = _stream_handle(stream, dev)
-    res = sketch_restore_batch([(sk.handle, th, sk._cap, sk._buf()) for sk, th in items], s)
-    return _collect(items, res, stream, raise_errors)
+    def run(items):
+        return sketch_restore_batch([(sk.handle, th, sk._cap, sk._buf()) for sk, th in items], s)
+    return _collect(items, run(items), run, raise_errors)
 
 
-def _collect(items, res, stream, raise_errors):
-    """Per-item results of a batched restore; CAPACITY jobs run again in a
-    second (synchronous) batch with room for their lists."""
+def _collect(items, res, again, raise_errors):
+    """Per-item results of a batched restore; again(items): the results of
+    CAPACITY jobs once more, with room for their lists."""
     out = [None] * len(items)
     retry = []
     for i, ((sk, th), (recs, info, st, need)) in enumerate(zip(items, res)):
@@ -447,8 +448,8 @@ def _collect(items, res, stream, raise_errors):
         else:
             out[i] = (None, info)
     if retry:
-        again = restore_batch([items[i] for i in retry], stream, raise_errors)
-        for i, r in zip(retry, again):
+        more = [items[i] for i in retry]
+        for i, r in zip(retry, _collect(more, again(more), again, raise_errors)):
             out[i] = r
     return out
 
@@ -470,8 +471,14 @@ class PendingRestore:
         """[(records, info)] in item order, as restore_batch returns them."""
         if not self.items:
             return []
-        res = sketch_restore_batch_end(self.jobs, _stream_handle(self.stream, self.dev))
-        return _collect(self.items, res, self.stream, raise_errors)
+        s = _stream_handle(self.stream, self.dev)
+
+        def longer(items):
+            # the same restore's list, not a new restore: the sketch may hold
+            # the next window by now
+            return sketch_restore_batch_end(
+                _RestoreJobs([(sk.handle, th, sk._cap, sk._buf()) for sk, th in items]), s)
+        return _collect(self.items, sketch_restore_batch_end(self.jobs, s), longer, raise_errors)
 
 
 def restore_batch_begin(items, stream=None) -> PendingRestore:

@@ -137,3 +137,52 @@ def test_a_lost_job_of_a_batch_leaves_the_others():
         (recs, info), (rest, _) = pend.end(raise_errors=False)
         assert recs is None and info["status"] == ddhf.SKETCH_E_CAPACITY
         assert_spl_equal(rest, *oracle.restore(p, small, 100.0, mode="brute")[:3])
+
+
+@pytest.mark.parametrize("meanwhile", ["reset", "small", "large", "more"])
+def test_a_list_longer_than_the_callers_buffer(meanwhile):
+    """The facade starts with room for 4096 records and asks again for what the
+    same restore found."""
+    p = oracle.Params(128, 18, 5, 5)
+    words, ip, sz, c = overflowing(p, 5000)
+    say(f"{len(ip)} records into 4096, {meanwhile}")
+    with make_sketch(p) as sk:
+        sk.upload(words)
+        pend = ddhf.restore_batch_begin([(sk, 100.0)])
+        after = next_window(sk, p, meanwhile, words)
+        (recs, info), = pend.end()
+        assert_spl_equal(recs, ip, sz, c)
+        assert info["n_reported"] == len(ip)
+        assert np.array_equal(sk.download(), after)
+        for _ in range(2):
+            sk._cap, sk._outbuf = 16, None
+            sk.upload(words)
+            recs, _ = ddhf.restore_batch([(sk, 100.0)])[0]
+            assert_spl_equal(recs, ip, sz, c)
+
+
+def test_an_ended_restore_is_ended_again_only_for_more_room():
+    p = oracle.Params(128, 18, 5, 5)
+    words = hosts_sketch(p, 60, 4)
+    ip, sz, c, _ = oracle.restore(p, words, 100.0, mode="brute")
+    with make_sketch(p) as sk:
+        sk.upload(words)
+
+        def end(cap):
+            jobs = ddhf._RestoreJobs([(sk.handle, 100.0, cap)])
+            return ddhf.sketch_restore_batch_end(jobs)[0]
+
+        ddhf.sketch_restore_batch_begin([(sk.handle, 100.0, 8)])
+        for cap in (8, 1, 0):
+            _, _, st, need = end(cap)
+            assert st == ddhf.SKETCH_E_CAPACITY and need == len(ip)
+        recs, _, st, _ = end(len(ip))
+        assert st == ddhf.SKETCH_OK
+        assert_spl_equal(recs, ip, sz, c)
+        with pytest.raises(ddhf.SketchError):       # its list has been given out
+            end(100)
+        ddhf.sketch_restore_batch_begin([(sk.handle, 100.0, 8)])
+        assert end(8)[2] == ddhf.SKETCH_E_CAPACITY
+        sk.restore(100.0)
+        with pytest.raises(ddhf.SketchError):       # another restore has come since
+            end(100)
