@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -231,6 +232,17 @@ struct RPool {
 
 constexpr int RESTORE_POOLS = 4;
 
+// The pair index (see Lattice) of row 0's multiplier and k: the same for every
+// sketch of one hash family, so the device has one of each and the handles
+// share it (4 MiB beside a sketch of 10 MiB at k = 14).
+struct PairIndex {
+  uint64_t a0 = 0;
+  uint32_t k = 0;
+  int refs = 0;
+  uint32_t *mem = nullptr;
+  PairIndex *next = nullptr;
+};
+
 struct DevCtx {
   static constexpr int SLOTS = 16;
   int dev = -1;
@@ -258,6 +270,7 @@ struct DevCtx {
   // one batch's update can run while another batch's restore does
   Lane arena_lane;
   uint64_t gen = 0;              // bumped whenever the arena or a pool moves
+  PairIndex *pairs = nullptr;    // the pair indexes in use
   // this device's copy of the no-alloc restore's work array (its address
   // from hipGetSymbolAddress at set-up) and the last work that used it
   uint8_t *noalloc = nullptr;
@@ -533,6 +546,67 @@ int launch_jobs(DevCtx *c, const UpdJob *jobs, uint32_t n, UpdPath path, uint32_
   return SKETCH_OK;
 }
 
+// The parts of the pair index at `mem`, in L: the records (16-byte aligned),
+// the parts, the buckets. Returns its words.
+size_t pair_layout(uint32_t *mem, uint32_t k, Lattice *L) {
+  const size_t rec = ((size_t)2 * pair_rec_words(k)) << (32 - k);
+  if (L) {
+    L->pair_rec = mem;
+    L->pair_z = mem + rec;
+    L->pair_off = mem + rec + pair_z_words(k);
+  }
+  return rec + pair_z_words(k) + pair_off_words(k);
+}
+
+// The pair index of G, built if the device has none yet (and complete on
+// return); null where there is no room for it: the search then goes without.
+PairIndex *pairs_acquire(DevCtx *c, const Geom &G) {
+  std::lock_guard<std::mutex> lk(c->mu);
+  for (PairIndex *x = c->pairs; x; x = x->next)
+    if (x->a0 == G.a0 && x->k == G.k) {
+      x->refs++;
+      return x;
+    }
+  PairIndex *x = new (std::nothrow) PairIndex();
+  if (!x) return nullptr;
+  x->a0 = G.a0;
+  x->k = G.k;
+  x->refs = 1;
+  if (dev_alloc(&x->mem, pair_layout(nullptr, G.k, nullptr), "pair index")) {
+    (void)hipGetLastError();
+    delete x;
+    return nullptr;
+  }
+  Lattice L{};
+  (void)pair_layout(x->mem, G.k, &L);
+  hipError_t e = launch_pair_index(G, const_cast<uint32_t *>(L.pair_off),
+                                   const_cast<uint32_t *>(L.pair_z),
+                                   const_cast<uint32_t *>(L.pair_rec), nullptr);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (e != hipSuccess) {
+    dev_free(x->mem);
+    delete x;
+    return nullptr;
+  }
+  x->next = c->pairs;
+  c->pairs = x;
+  return x;
+}
+
+// A handle lets go of its index (whose device the caller has synchronized).
+void pairs_release(DevCtx *c, PairIndex *x) {
+  if (!x) return;
+  std::lock_guard<std::mutex> lk(c->mu);
+  if (--x->refs) return;
+  for (PairIndex **p = &c->pairs; *p; p = &(*p)->next)
+    if (*p == x) {
+      *p = x->next;
+      break;
+    }
+  dev_free(x->mem);
+  delete x;
+}
+
 uint64_t splitmix64_next(uint64_t &state) {
   // SplitMix64 (Steele, Lea and Flood 2014).
   uint64_t z = (state += 0x9E3779B97F4A7C15ull);
@@ -714,7 +788,7 @@ struct sketch {
   double hint_e = -1.0, ran_e = -1.0;
   bool ran_sort_one = false;
   uint2 *chunks = nullptr;      // hot scan chunks (scan_chunks)
-  uint32_t *pairs = nullptr;    // pair index (see Lattice; null: none)
+  PairIndex *pairs = nullptr;   // shared with the device's other handles (null: none)
   uint64_t cost_hint = 0;       // the last restore's row-0 cells times their addresses
   uint64_t join_hint = 0;       // the last restore's join wave items of stage 1 (0: none yet)
 };
@@ -743,7 +817,8 @@ void free_sketch(sketch *s) {
   dev_free(s->st);
   dev_free(s->hotmask);
   dev_free(s->chunks);
-  dev_free(s->pairs);
+  pairs_release(s->ctx, s->pairs);
+  s->pairs = nullptr;
   dev_free(s->he);
   dev_free(s->bk_off);
   dev_free(s->bk_cur);
@@ -1802,17 +1877,9 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   if (!rc) rc = dev_alloc(&s->bk_off, (size_t)params->r * (nb + 1), "bucket offsets");
   if (!rc) rc = dev_alloc(&s->bk_cur, (size_t)params->r * nb, "bucket cursors");
   if (!rc) rc = dev_alloc(&s->bk_val, n_le, "bucket values");
-  uint32_t *pair_rec = nullptr, *pair_off = nullptr, *pair_z = nullptr;
   if (!rc && s->lat.ok && pair_indexed(params->k)) {
-    // one allocation: the records (16-byte aligned), the parts, the buckets
-    const size_t rec = ((size_t)2 * pair_rec_words(params->k)) << (32 - params->k);
-    rc = dev_alloc(&s->pairs, rec + pair_z_words(params->k) + pair_off_words(params->k),
-                   "pair index");
-    if (!rc) {
-      s->lat.pair_rec = pair_rec = s->pairs;
-      s->lat.pair_z = pair_z = pair_rec + rec;
-      s->lat.pair_off = pair_off = pair_z + pair_z_words(params->k);
-    }
+    s->pairs = pairs_acquire(s->ctx, s->G);
+    if (s->pairs) (void)pair_layout(s->pairs->mem, params->k, &s->lat);
   }
   if (!rc) rc = grow_sorted(s, (size_t)1 << 12);
   if (!rc && s->nbins <= BIN_MAX) {
@@ -1832,8 +1899,6 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   if (!rc) s->h_recs_cap = (size_t)1 << 12;
   if (!rc) {
     hipError_t e = launch_fill_u32(s->d_sketch, s->words, 0u, s->grid, nullptr);
-    if (e == hipSuccess && pair_z)
-      e = launch_pair_index(s->G, pair_off, pair_z, pair_rec, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess)
       rc = fail(SKETCH_E_HIP, "sketch_create: zero fill: %s", hipGetErrorString(e));

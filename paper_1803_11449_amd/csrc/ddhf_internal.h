@@ -405,7 +405,7 @@ hipError_t launch_or_u32(uint32_t *dst, const uint32_t *src, size_t n_words, int
 // Once per device, before any restore (and outside graph capture): lets the
 // lattice search take more than 64 KiB of LDS.
 hipError_t prepare_restore_kernels();
-// Builds a sketch's pair index (pair_off_words, pair_z_words, and
+// Builds the pair index of G (pair_off_words, pair_z_words, and
 // pair_rec_words per bucket) on st.
 hipError_t launch_pair_index(const Geom &G, uint32_t *off, uint32_t *z, uint32_t *rec,
                              hipStream_t st);

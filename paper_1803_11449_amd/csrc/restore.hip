@@ -1122,9 +1122,9 @@ __global__ __launch_bounds__(PAIR_THREADS) void k_pairs(
   found->flush(st, cand, cand_cap);
 }
 
-// The pair index, built once per sketch: the counts per bucket become their
-// starts, the parts take their places, and then the second copy
-// of the parts and the bucket words are made.
+// The pair index, built once per hash family (a0, k): the counts per bucket
+// become their starts, the parts take their places, and then the second copy of
+// the parts and the bucket words are made.
 __device__ __forceinline__ uint32_t pair_bucket(const Geom &G, uint32_t z) {
   return (uint32_t)((G.a0 * z) << G.k >> 32) >> G.k;
 }

@@ -49,7 +49,8 @@ def sized_params(n_pairs: int, g: int = 1024, r: int = 5, k_min: int = 14,
 
 def resident_bytes(g: int, k: int, r: int, alpha: int) -> int:
     """Device memory a resident link costs: the sketch plus its per-row
-    restore arrays and per-tile update arrays (the large scratch is shared)."""
+    restore arrays and per-tile update arrays (the large scratch is shared, and
+    so are the search's pair indexes: one per k of 14 to 18, 11 MiB together)."""
     n_le = r << k
     sketch = n_le * g // 8
     rows = n_le // 8 + 3 * 4 * n_le + 8 * r * (1 << (k - alpha))
