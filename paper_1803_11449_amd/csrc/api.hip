@@ -1002,11 +1002,13 @@ double restore_cost(const sketch *s) {
   return (double)((size_t)s->p.r << s->p.k) / 4.0 + (double)s->cost_hint;
 }
 
-// What a finished restore found (e: its threshold's exp(-theta / g)).
-void note_cost(sketch *s, const DevState &h, double e) {
+// What a finished restore found (e: its threshold's exp(-theta / g); estimate:
+// whether it made the list).
+void note_cost(sketch *s, const DevState &h, double e, int estimate) {
   if (h.saturated || h.search == 0) return;
   s->hint_search = h.search;
-  s->hint_n = h.n_spl;
+  if (estimate) s->hint_n = h.n_spl;
+  else if (s->hint_e != e) s->hint_n = ~0ull;
   s->hint_e = e;
   s->cost_hint = (uint64_t)h.he_count[0] << (32 - s->p.k);
   s->join_hint = std::max<uint64_t>(1, (uint64_t)h.he_count[0] * ((h.he_count[1] + 63) / 64));
@@ -1116,7 +1118,7 @@ int restore_check(sketch *s, int estimate, bool *again) {
     *again = true;
     return SKETCH_OK;
   }
-  note_cost(s, h, s->ran_e);
+  note_cost(s, h, s->ran_e, estimate);
   if (estimate && s->ran_sort_one && h.n_spl > RESTORE_SORT_ONE) *again = true;
   // a stage overflowed if its count passed the capacity the run had; the
   // buffer grows only if it has not grown enough since
@@ -2018,7 +2020,7 @@ int sketch_restore_noalloc(sketch_t *s, double theta, sketch_sp_t *out, size_t c
       B.expect = 0;
       continue;
     }
-    note_cost(s, h, t.e_theta);
+    note_cost(s, h, t.e_theta, 1);
     if (B.sort_one && h.n_spl > RESTORE_SORT_ONE) {
       B.sort_one = 0;
       continue;
@@ -2555,7 +2557,7 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
     const uint4 *src = pj.sorted;
     int rc = SKETCH_OK;
     pj.eager = false;
-    note_cost(s, *h, pj.t.e_theta);
+    note_cost(s, *h, pj.t.e_theta, 1);
     if (h->saturated) {
       rc = SKETCH_E_SATURATED;
     } else {
