@@ -2005,9 +2005,11 @@ int sketch_restore_noalloc(sketch_t *s, double theta, sketch_sp_t *out, size_t c
   const Thresholds t = thresholds(s, theta);
   RestoreBufs B = noalloc_bufs(s, c->noalloc, t);
   // a join whose partial addresses outgrow the array gives way to the
-  // lattice search, which makes none (both give the same candidates). A
-  // search or a sort that was expected and not the right one: again with
-  // every kernel
+  // lattice search, which makes none (both give the same candidates; what the
+  // sketch's next restore goes by is then left alone: its own rule takes the
+  // join). A search or a sort that was expected and not the right one: again
+  // with every kernel
+  bool gave_way = false;
   for (;;) {
     int rc = restore_launch_on(s, B, c->noalloc_lane, t, 1, st, true);
     if (rc) return rc;
@@ -2018,23 +2020,28 @@ int sketch_restore_noalloc(sketch_t *s, double theta, sketch_sp_t *out, size_t c
     if (h.saturated) break;
     if (B.expect && h.search == 0) {
       B.expect = 0;
-      continue;
-    }
-    note_cost(s, h, t.e_theta, 1);
-    if (B.sort_one && h.n_spl > RESTORE_SORT_ONE) {
-      B.sort_one = 0;
+      s->hint_e = -1.0;
       continue;
     }
     uint32_t seg = 0;
     for (uint32_t i = 2; i + 1 < s->p.r; i++) seg = std::max(seg, h.seg_max[i]);
-    if (seg <= B.seg_cap) break;
-    if (B.cand_path == 0 && s->lat.ok) {
-      B.cand_path = 2;
-      B.expect = 0;
+    if (seg > B.seg_cap) {
+      if (B.cand_path == 0 && s->lat.ok) {
+        gave_way = true;
+        B.cand_path = 2;
+        B.expect = 0;
+        continue;
+      }
+      return fail(SKETCH_E_CAPACITY, "sketch_restore_noalloc: a join block's %u partial "
+                  "addresses exceed the work array's %zu", seg, B.seg_cap);
+    }
+    if (B.sort_one && h.n_spl > RESTORE_SORT_ONE) {
+      B.sort_one = 0;
+      s->hint_e = -1.0;
       continue;
     }
-    return fail(SKETCH_E_CAPACITY, "sketch_restore_noalloc: a join block's %u partial "
-                "addresses exceed the work array's %zu", seg, B.seg_cap);
+    if (!gave_way && h.n_cand <= B.cand_cap) note_cost(s, h, t.e_theta, 1);
+    break;
   }
   const DevState h = *s->h_state;
   fill_info(s, h, t.zmin, t.zhot, info);
