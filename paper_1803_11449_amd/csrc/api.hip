@@ -696,6 +696,32 @@ Geom make_geom(const sketch_params_t &p) {
   return G;
 }
 
+// What a sketch's restores at one threshold find, window after window, and
+// whether the next one goes by it. Going by it saves a restore five to seven
+// short launches (10 to 20 us of 40 to 90); a window of another kind then costs
+// a second restore. So after the first such window it takes EXPECT_RUN restores
+// in a row of one kind, and a handle whose windows change more often launches
+// everything: windows for the join and for the lattice search in turn, 85 us a
+// restore (median), 125 when each went by the other's.
+constexpr uint32_t EXPECT_RUN = 8;
+
+struct Expectation {
+  double e = -1.0;              // exp(-theta / g) of the threshold
+  uint32_t kind = 0;
+  uint32_t run = 0, need = 1;   // restores in a row of the kind; that it takes
+
+  bool holds(double at) const { return at == e && run >= need; }
+  void found(double at, uint32_t k) {
+    run = at == e && k == kind ? std::min(run + 1, EXPECT_RUN) : 1;
+    e = at;
+    kind = k;
+  }
+  void missed() {
+    run = 0;
+    need = EXPECT_RUN;
+  }
+};
+
 // Thresholds that depend on theta only (host, float64).
 struct Thresholds {
   double e_theta, zmin;
@@ -780,13 +806,11 @@ struct sketch {
   // between its launch and its check when restores are batched)
   size_t ran_seg_cap = 0, ran_cand_cap = 0, ran_spl_cap = 0, ran_h_recs_cap = 0;
   int ran_pool = 0;             // the pool that restore ran on
-  // what the last restore found, for what the next one at that threshold
-  // launches (RestoreBufs::expect, sort_one): the search that ran, the
-  // records, and the thresholds' exp(-theta / g) they belong to
-  uint32_t hint_search = 0;
-  uint64_t hint_n = ~0ull;
-  double hint_e = -1.0, ran_e = -1.0;
-  bool ran_sort_one = false;
+  // what the next restore launches (RestoreBufs::expect, sort_one): the search
+  // that ran, whether the list fits the one-launch sort (1, else 0)
+  Expectation search_seen, list_seen;
+  double ran_e = -1.0;          // the last enqueued restore's exp(-theta / g)
+  bool ran_sort_one = false;    // ... and whether it took the one-launch sort
   uint2 *chunks = nullptr;      // hot scan chunks (scan_chunks)
   PairIndex *pairs = nullptr;   // shared with the device's other handles (null: none)
   uint64_t cost_hint = 0;       // the last restore's row-0 cells times their addresses
@@ -864,10 +888,11 @@ RestoreBufs restore_bufs(const sketch *s, const RPool &p, const Thresholds &t, b
   B.lez = s->lez;
   B.lez_stale = !s->lez_valid;
   B.chunks = s->chunks;
-  if (by_last && s->hint_e == t.e_theta) {
-    if (s->cand_path == 0 || (s->cand_path == 2 && s->hint_search >= 2)) B.expect = s->hint_search;
-    B.sort_one = s->hint_n <= SORT_ONE_HINT;
+  if (by_last && s->search_seen.holds(t.e_theta)) {
+    const uint32_t search = s->search_seen.kind;
+    if (s->cand_path == 0 || (s->cand_path == 2 && search >= 2)) B.expect = search;
   }
+  B.sort_one = by_last && s->list_seen.holds(t.e_theta) && s->list_seen.kind;
   B.st = s->st;
   B.hotmask = s->hotmask;
   B.he = s->he;
@@ -1002,16 +1027,26 @@ double restore_cost(const sketch *s) {
   return (double)((size_t)s->p.r << s->p.k) / 4.0 + (double)s->cost_hint;
 }
 
-// What a finished restore found (e: its threshold's exp(-theta / g); estimate:
-// whether it made the list).
-void note_cost(sketch *s, const DevState &h, double e, int estimate) {
+// The work of a restore that has its counts.
+void note_cost(sketch *s, const DevState &h) {
   if (h.saturated || h.search == 0) return;
-  s->hint_search = h.search;
-  if (estimate) s->hint_n = h.n_spl;
-  else if (s->hint_e != e) s->hint_n = ~0ull;
-  s->hint_e = e;
   s->cost_hint = (uint64_t)h.he_count[0] << (32 - s->p.k);
   s->join_hint = std::max<uint64_t>(1, (uint64_t)h.he_count[0] * ((h.he_count[1] + 63) / 64));
+}
+
+// Whether a restore launched by what was expected lacks what its window needs
+// (and must run again); if not, what it found. whole: no buffer overflowed, so
+// its list (if it made one: estimate) is the window's.
+bool missed_expectation(sketch *s, const DevState &h, double e, bool sort_one, int estimate,
+                        bool whole) {
+  if (h.search == 0 || (estimate && sort_one && h.n_spl > RESTORE_SORT_ONE)) {
+    s->search_seen.missed();
+    s->list_seen.missed();
+    return true;
+  }
+  s->search_seen.found(e, h.search);
+  if (estimate && whole) s->list_seen.found(e, h.n_spl <= SORT_ONE_HINT);
+  return false;
 }
 
 // Pools of a batch's jobs: the costliest job first, each to the pool with
@@ -1113,13 +1148,7 @@ int restore_check(sketch *s, int estimate, bool *again) {
   RPool &p = c->pool[s->ran_pool];
   *again = false;
   if (h.saturated) return SKETCH_E_SATURATED;
-  if (h.search == 0) {                  // the other search's turn
-    s->hint_e = -1.0;
-    *again = true;
-    return SKETCH_OK;
-  }
-  note_cost(s, h, s->ran_e, estimate);
-  if (estimate && s->ran_sort_one && h.n_spl > RESTORE_SORT_ONE) *again = true;
+  note_cost(s, h);
   // a stage overflowed if its count passed the capacity the run had; the
   // buffer grows only if it has not grown enough since
   size_t need_part = 0;
@@ -1149,6 +1178,7 @@ int restore_check(sketch *s, int estimate, bool *again) {
     }
     *again = true;
   }
+  if (missed_expectation(s, h, s->ran_e, s->ran_sort_one, estimate, !*again)) *again = true;
   return SKETCH_OK;
 }
 
@@ -2018,30 +2048,22 @@ int sketch_restore_noalloc(sketch_t *s, double theta, sketch_sp_t *out, size_t c
     lane_done(s->lane);
     const DevState &h = *s->h_state;
     if (h.saturated) break;
-    if (B.expect && h.search == 0) {
-      B.expect = 0;
-      s->hint_e = -1.0;
-      continue;
-    }
+    note_cost(s, h);
     uint32_t seg = 0;
     for (uint32_t i = 2; i + 1 < s->p.r; i++) seg = std::max(seg, h.seg_max[i]);
     if (seg > B.seg_cap) {
       if (B.cand_path == 0 && s->lat.ok) {
         gave_way = true;
         B.cand_path = 2;
-        B.expect = 0;
+        B.expect = B.sort_one = 0;
         continue;
       }
       return fail(SKETCH_E_CAPACITY, "sketch_restore_noalloc: a join block's %u partial "
                   "addresses exceed the work array's %zu", seg, B.seg_cap);
     }
-    if (B.sort_one && h.n_spl > RESTORE_SORT_ONE) {
-      B.sort_one = 0;
-      s->hint_e = -1.0;
-      continue;
-    }
-    if (!gave_way && h.n_cand <= B.cand_cap) note_cost(s, h, t.e_theta, 1);
-    break;
+    if (gave_way) break;
+    if (!missed_expectation(s, h, t.e_theta, B.sort_one, 1, h.n_cand <= B.cand_cap)) break;
+    B.expect = B.sort_one = 0;
   }
   const DevState h = *s->h_state;
   fill_info(s, h, t.zmin, t.zhot, info);
@@ -2564,7 +2586,7 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
     const uint4 *src = pj.sorted;
     int rc = SKETCH_OK;
     pj.eager = false;
-    note_cost(s, *h, pj.t.e_theta, 1);
+    note_cost(s, *h);
     if (h->saturated) {
       rc = SKETCH_E_SATURATED;
     } else {

@@ -10,7 +10,7 @@ from torch.profiler import ProfilerActivity, profile
 
 import oracle
 from paper_1803_11449_amd import ddhf
-from test_gpu_parity import assert_spl_equal, make_sketch, say
+from test_gpu_parity import assert_spl_equal, crafted_hot_sketch, make_sketch, say
 from test_gpu_restore_launches import hosts_sketch
 
 pytestmark = pytest.mark.gpu
@@ -69,3 +69,43 @@ def test_a_join_that_outgrows_the_fixed_array():
         (recs, info), n = kernels(lambda: sk.restore(100.0))
         assert_spl_equal(recs, *want)
         assert n["k_compact"] == 1 and info["n_partials"][2] > 2560
+
+
+def kinds_in_turn(what):
+    """(parameters, theta, windows whose restores need other kernels)."""
+    if what == "search":
+        p, theta = oracle.Params(), 700.0
+        windows = [crafted_hot_sketch(p, f, 3) for f in (0.002, 0.06)]
+    else:
+        p, theta = oracle.Params(128, 18, 5, 5), 100.0
+        windows = [hosts_sketch(p, m, m) for m in (1000, 2500)]
+    return p, theta, [(w, oracle.restore(p, w, theta, mode="brute")[:3]) for w in windows]
+
+
+@pytest.mark.parametrize("fn", ["restore", "restore_noalloc", "batch"])
+@pytest.mark.parametrize("what", ["search", "list"])
+@pytest.mark.parametrize("each", [1, 3])
+def test_windows_of_two_kinds_in_turn(what, fn, each):
+    """`each` windows of a kind at a time: one restore is run again, not every
+    one that follows a window of the other kind."""
+    p, theta, windows = kinds_in_turn(what)
+    passes = 0
+    with make_sketch(p) as sk:
+        sk._cap = 1 << 13
+        restore = {"batch": lambda: ddhf.restore_batch([(sk, theta)])[0]}.get(
+            fn, lambda: getattr(sk, fn)(theta))
+        for i in range(6 * each):
+            words, want = windows[i // each % 2]
+            sk.upload(words)
+            (recs, _), n = kernels(restore)
+            assert_spl_equal(recs, *want)
+            passes += n["k_estimate"]
+        say(f"{what}, {fn}, {each} of a kind: {passes} passes for {6 * each} windows")
+        assert passes <= 6 * each + 1
+        # windows of one kind: only what they need, once that has been so for a while
+        for i in range(10):
+            (recs, _), n = kernels(restore)
+            assert_spl_equal(recs, *want)
+            assert n["k_estimate"] == 1
+        searches = [x for x in ("k_lattice", "k_pairs", "k_join", "k_join_walk") if n[x]]
+        assert len(searches) == 1 and (n["k_sort_publish"] == 1) == (len(want[0]) <= 1536)
