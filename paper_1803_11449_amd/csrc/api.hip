@@ -1251,14 +1251,16 @@ bool wants_binned(const sketch *s, size_t n) {
 // k = 18 (1024 tiles): 16,000 pairs take 58 us, a zero fill and the direct
 // kernel 49 us and the scan of the sketch that the restore then needs 32 us
 // more (8 us from the zero counts); at 64,000 pairs the visits cost more
-// than that.
+// than that. And at most what that leaves LIN_TILES tiles: with fewer, each
+// workgroup still reads every pair (a sketch of 4 tiles: 100,000 pairs 75 us
+// against 103, 1M pairs 572 against 428, 8M 4435 against 520).
 constexpr uint64_t FRESH_VISITS = (uint64_t)1 << 25;
 
 // How an update of n pairs runs: by the sketch's options and n; fresh: the
 // sketch is all zero and not yet written.
 UpdPath update_path(const sketch *s, size_t n, bool fresh) {
   if (wants_binned(s, n)) return s->lin ? UPD_LINEAR : UPD_REGIONS;
-  const uint64_t tiles = s->lin ? s->ltiles : s->nbins;
+  const uint64_t tiles = std::max(s->lin ? s->ltiles : s->nbins, LIN_TILES);
   if (fresh && s->update_path == 0 && s->nbins <= BIN_MAX && n <= FRESH_VISITS / tiles)
     return UPD_FRESH;
   return UPD_DIRECT;
