@@ -316,10 +316,11 @@ int sketch_merge(sketch_t *dst, const sketch_t *src, void *hip_stream);
  * workgroup per tile or part of a tile; sketches of up to 3276 tiles of
  * 160 KiB, 511.9 MiB). Chosen by size, a small update of a sketch that was
  * just reset builds the tiles from all its pairs instead. Sketches of up to
- * 40 MiB write the grouped bit sets batch by batch, larger ones (and every
- * binned job of a call that has such a sketch) in regions per tile, which a
- * count pass sizes: SAMPLE, REGIONS and the per-block minimum below concern
- * those. */
+ * 40 MiB write the grouped bit sets batch by batch, larger ones, large windows
+ * of sketches below 320 KiB or with g over 2048 (whose tiles could hold too
+ * much for a workgroup each), and every binned job of a call that has one of
+ * these, in regions per tile, which a count pass sizes: SAMPLE, REGIONS and the
+ * per-block minimum below concern those. */
 enum {
   SKETCH_OPT_UPDATE_PATH = 1,       /* 0 = choose by size (default),
                                        1 = direct, 2 = binned */

@@ -783,7 +783,7 @@ struct sketch {
   size_t binned_min_pairs = 0;
   size_t binned_round = ARENA_MAX_PAIRS;
   uint32_t nbins = 0;           // tiles of 160 KiB
-  bool lin = false;             // binned rounds take the linear kernels
+  bool lin = false;             // small enough for the linear kernels
   uint32_t tshift = 0, ltiles = 0;   // their tiles: 160 KiB >> tshift
   uint32_t bin_nblk = 0;        // count/scatter blocks per job (hist width)
   uint32_t scatter_ppt = 6;
@@ -1246,6 +1246,34 @@ bool wants_binned(const sketch *s, size_t n) {
   return s->update_path == 2 || (s->update_path == 0 && n >= s->binned_min_pairs);
 }
 
+// The linear apply gives a tile one workgroup, whatever it holds, where the
+// region passes cut heavy tiles over the chip at about 90 us a launch set more.
+// A workgroup sets 1000 words in 0.26 us. With LIN_MANY tiles or more of a
+// window's words (uniform over the tiles) linear is ahead at every size (32
+// tiles: 4M pairs 116 against 199 us, 40M 848 against 1000); with fewer, up
+// to lin_words: 4 tiles, 0.5M pairs 125 against 149, 1M 214 against 160, 10M
+// 1828 against 493; 12 tiles, 2M 149 against 179, 10M 609 against 448; 20
+// tiles, 10M 365 against 388, 40M 1431 against 1287.
+constexpr uint32_t LIN_MANY = 32;
+uint64_t lin_words(uint64_t tiles) { return tiles * SPLIT_MIN * (6 + tiles) / 6; }
+// And a source with a large part of the pairs piles its words up on r tiles,
+// unless the scatter's filter drops its repeats: at g = 2048 it does (16M
+// pairs, a tenth of one source 220 against 244 us, half of one 190 against
+// 384), with larger LEs it has few slots, and bits that repeat too late for it
+// to stay on (g = 4096: 50M pairs, a tenth of one source 810 against 566; g =
+// 65,536: 4M pairs, half of one 226 against 179, 16M 820 against 420; 1M
+// unfiltered pairs, four fifths of one, 99 against 132, 2M 171 against 155).
+constexpr uint32_t LIN_FILTER_G = 2048;
+constexpr uint64_t LIN_UNFILTERED = 3 << 19;
+
+// Whether a binned update of n pairs takes the linear kernels.
+bool takes_linear(const sketch *s, uint64_t n) {
+  if (!s->lin) return false;
+  n = std::min<uint64_t>(n, s->binned_round);
+  if (s->p.g > LIN_FILTER_G && n > LIN_UNFILTERED) return false;
+  return s->ltiles >= LIN_MANY || n * s->p.r / 3 <= lin_words(s->ltiles);
+}
+
 // Pairs times tiles up to which an update of an all-zero sketch that is too
 // small to be binned builds every tile from all the pairs (k_update_fresh).
 // k = 18 (1024 tiles): 16,000 pairs take 58 us, a zero fill and the direct
@@ -1259,7 +1287,7 @@ constexpr uint64_t FRESH_VISITS = (uint64_t)1 << 25;
 // How an update of n pairs runs: by the sketch's options and n; fresh: the
 // sketch is all zero and not yet written.
 UpdPath update_path(const sketch *s, size_t n, bool fresh) {
-  if (wants_binned(s, n)) return s->lin ? UPD_LINEAR : UPD_REGIONS;
+  if (wants_binned(s, n)) return takes_linear(s, n) ? UPD_LINEAR : UPD_REGIONS;
   const uint64_t tiles = std::max(s->lin ? s->ltiles : s->nbins, LIN_TILES);
   if (fresh && s->update_path == 0 && s->nbins <= BIN_MAX && n <= FRESH_VISITS / tiles)
     return UPD_FRESH;

@@ -12,7 +12,9 @@
 //          Tiles are cut small enough (160 KiB >> tshift) to be about one
 //          per compute unit. Against the region passes, update kernels of a
 //          1M-pair window on the default sketch: 76 us in 8 launches and a
-//          copy -> 35 us in 2; 9M pairs at k = 15: 150 -> 113 us.
+//          copy -> 35 us in 2; 9M pairs at k = 15: 150 -> 113 us. Windows
+//          that would leave few workgroups with long tiles stay with the
+//          regions (takes_linear, in api.hip).
 // fresh    A window too small to sort: one workgroup per tile of a sketch
 //          that is all zero builds its tile in LDS from every pair of the
 //          window, and writes it with its LEs' zero counts. It takes the

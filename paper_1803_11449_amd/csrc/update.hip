@@ -7,7 +7,8 @@
 //
 // Four ways compute the same sketch; update_path (api.hip) chooses. The
 // direct, linear and fresh kernels are in linear.hip; here are the passes of
-// the region update, for sketches of more than LIN_TILES tiles.
+// the region update, for sketches of more than LIN_TILES tiles and windows
+// whose tiles want cutting.
 //
 // regions  The bit sets are moved into LDS. Every (pair, row) gives the bit
 //          index B = ((row * 2^k + cell) * g) + bit of the sketch seen as

@@ -29,3 +29,34 @@ def test_a_raised_minimum(p, n, fresh):
         say(f"minimum raised, {n} pairs, {p.words()} words: {dict(k)}")
         assert (k["k_update_fresh"], k["k_update"]) == ((1, 0) if fresh else (0, 1))
         assert np.array_equal(sk.download(), oracle.build_sketch(p, pairs))
+
+
+@pytest.mark.parametrize("p,n,linear", [
+    # 4, 12 and 32 tiles of a sketch of few
+    (oracle.Params(1024, 5, 8, 5), 650_000, True), (oracle.Params(1024, 5, 8, 5), 660_000, False),
+    (oracle.Params(1024, 7, 7, 5), 4_000_000, True), (oracle.Params(1024, 7, 7, 5), 4_050_000, False),
+    (oracle.Params(1024, 9, 5, 8), 12_000_000, True),
+    # large estimators
+    (oracle.Params(2048, 13, 5, 7), 1_600_000, True),
+    (oracle.Params(4096, 13, 5, 7), 1_572_864, True),
+    (oracle.Params(4096, 13, 5, 7), 1_572_865, False)],
+    ids=lambda x: f"g{x.g}k{x.k}r{x.r}" if isinstance(x, oracle.Params) else str(x))
+def test_heavy_tiles(p, n, linear):
+    """A window that would leave few workgroups with long tiles goes through the
+    passes that cut them; half the pairs are one source's."""
+    rng = np.random.default_rng(n)
+    pairs = rand_pairs(rng, n, 4000)
+    pairs[rng.random(n) < 0.5, 0] = 77
+    dev = to_dev(pairs)
+    want = oracle.build_sketch(p, pairs)
+    with make_sketch(p) as sk:
+        for fresh in (True, False):
+            _, k = kernels(lambda: sk.update(dev))
+            say(f"{p} {n} pairs, fresh {fresh}: {dict(k)}")
+            assert bool(k["k_lin_apply"]) == linear and bool(k["k_bin_apply"]) != linear
+            assert np.array_equal(sk.download(), want)
+        if n < 1_000_000:               # the same rounds as one update of a large window
+            sk.set_option(ddhf.SKETCH_OPT_BINNED_ROUND, 100_000)
+            sk.reset()
+            _, k = kernels(lambda: sk.update(dev))
+            assert k["k_lin_apply"] == 7 and np.array_equal(sk.download(), want)
