@@ -780,7 +780,7 @@ struct sketch {
   int update_grid = 0;          // blocks of the direct kernel
   int update_check = 1;
   int update_path = 0;          // 0 by size, 1 direct, 2 binned
-  size_t binned_min_pairs = 0;
+  size_t binned_min_pairs = 0, binned_min_written = 0;   // the latter on a written sketch
   size_t binned_round = ARENA_MAX_PAIRS;
   uint32_t nbins = 0;           // tiles of 160 KiB
   bool lin = false;             // small enough for the linear kernels
@@ -1241,9 +1241,10 @@ void set_tiles(const sketch *s, UpdJob &J) {
   J.nbins = s->lin ? s->ltiles : s->nbins;
 }
 
-bool wants_binned(const sketch *s, size_t n) {
+bool wants_binned(const sketch *s, size_t n, bool fresh) {
   if (s->nbins > BIN_MAX) return false;
-  return s->update_path == 2 || (s->update_path == 0 && n >= s->binned_min_pairs);
+  const size_t least = fresh ? s->binned_min_pairs : s->binned_min_written;
+  return s->update_path == 2 || (s->update_path == 0 && n >= least);
 }
 
 // The linear apply gives a tile one workgroup, whatever it holds, where the
@@ -1287,7 +1288,7 @@ constexpr uint64_t FRESH_VISITS = (uint64_t)1 << 25;
 // How an update of n pairs runs: by the sketch's options and n; fresh: the
 // sketch is all zero and not yet written.
 UpdPath update_path(const sketch *s, size_t n, bool fresh) {
-  if (wants_binned(s, n)) return takes_linear(s, n) ? UPD_LINEAR : UPD_REGIONS;
+  if (wants_binned(s, n, fresh)) return takes_linear(s, n) ? UPD_LINEAR : UPD_REGIONS;
   const uint64_t tiles = std::max(s->lin ? s->ltiles : s->nbins, LIN_TILES);
   if (fresh && s->update_path == 0 && s->nbins <= BIN_MAX && n <= FRESH_VISITS / tiles)
     return UPD_FRESH;
@@ -1918,10 +1919,15 @@ int sketch_create(const sketch_params_t *params, sketch_t **out) {
   // measured crossovers on MI355X (Zipf(1.1) windows). Linear sketches, k =
   // 14 to 16: the linear update takes 23-29 us at 16,000 pairs and 23-30 at
   // 32,000; a reset sketch built from all its pairs 17-24 and 23-29; the
-  // direct kernel on a written sketch about 22 and 40. Larger sketches: the
-  // regions take 91 us at k = 17 and 125 at k = 18 for any small window; the
-  // direct kernel 92 and 105 at 128,000 pairs, 235 and 280 at 256,000
-  s->binned_min_pairs = s->lin ? 24576 : std::max<size_t>(s->words / 256, 1 << 14);
+  // direct kernel on a written sketch about 22 and 40, or less where bits are
+  // set already: a written sketch of 40 MiB, which the linear update reads and
+  // writes in 38, takes 33,000 further pairs in 25 and 40,000 in 26 (a reset
+  // one, window to list: linear 66, built from all pairs 72 and 75). Larger
+  // sketches: the regions take 91 us at k = 17 and 125 at k = 18 for any small
+  // window; the direct kernel 92 and 105 at 128,000 pairs, 235 and 280 at
+  // 256,000
+  s->binned_min_written = std::max<size_t>(s->words / 256, s->lin ? 24576 : 1 << 14);
+  s->binned_min_pairs = s->lin ? 24576 : s->binned_min_written;
 
   const size_t n_le = (size_t)params->r << params->k;
   const size_t nb = (size_t)1 << (params->k - params->alpha);
@@ -2260,7 +2266,7 @@ int sketch_set_option(sketch_t *s, int option, int64_t value) {
       return SKETCH_OK;
     case SKETCH_OPT_BINNED_MIN_PAIRS:
       if (value < 0) break;
-      s->binned_min_pairs = (size_t)value;
+      s->binned_min_pairs = s->binned_min_written = (size_t)value;
       return SKETCH_OK;
     case SKETCH_OPT_UPDATE_GRID:
       if (value < 1 || value > (1 << 20)) break;

@@ -60,3 +60,21 @@ def test_heavy_tiles(p, n, linear):
             sk.reset()
             _, k = kernels(lambda: sk.update(dev))
             assert k["k_lin_apply"] == 7 and np.array_equal(sk.download(), want)
+
+
+@pytest.mark.parametrize("k,alpha,n,reset,written", [
+    (14, 6, 24_575, "k_update_fresh", "k_update"), (14, 6, 24_576, "linear", "linear"),
+    (16, 6, 24_576, "linear", "k_update"), (16, 6, 40_959, "linear", "k_update"),
+    (16, 6, 40_960, "linear", "linear")])
+def test_small_updates(k, alpha, n, reset, written):
+    """Few further pairs are set one by one rather than by rewriting a written
+    sketch, more of them the larger it is."""
+    p = oracle.Params(1024, k, 5, alpha)
+    pairs = rand_pairs(np.random.default_rng(n), 2 * n, 4000)
+    with make_sketch(p) as sk:
+        sk.reset()
+        for dev, name in ((to_dev(pairs[:n]), reset), (to_dev(pairs[n:]), written)):
+            _, kern = kernels(lambda: sk.update(dev))
+            say(f"k={k}, {n} pairs: {dict(kern)}")
+            assert set(kern) == ({"k_lin_scatter", "k_lin_apply"} if name == "linear" else {name})
+        assert np.array_equal(sk.download(), oracle.build_sketch(p, pairs))
