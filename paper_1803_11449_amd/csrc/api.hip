@@ -77,6 +77,7 @@ int dev_alloc(T **p, size_t count, const char *what) {
   hipError_t e = hipMalloc((void **)p, std::max<size_t>(count, 1) * sizeof(T));
   if (e != hipSuccess) {
     *p = nullptr;
+    (void)hipGetLastError();            // not the next launch's error
     return fail(e == hipErrorOutOfMemory ? SKETCH_E_NOMEM : SKETCH_E_HIP,
                 "hipMalloc(%s, %zu bytes): %s", what, count * sizeof(T), hipGetErrorString(e));
   }
@@ -96,6 +97,7 @@ int pinned_alloc(T **h, T **d, size_t count, const char *what) {
   *d = nullptr;
   if (hipHostMalloc((void **)h, std::max<size_t>(count, 1) * sizeof(T)) != hipSuccess) {
     *h = nullptr;
+    (void)hipGetLastError();
     return fail(SKETCH_E_NOMEM, "hipHostMalloc(%s, %zu bytes) failed", what, count * sizeof(T));
   }
   if (hipHostGetDevicePointer((void **)d, *h, 0) != hipSuccess) {
@@ -573,7 +575,6 @@ PairIndex *pairs_acquire(DevCtx *c, const Geom &G) {
   x->k = G.k;
   x->refs = 1;
   if (dev_alloc(&x->mem, pair_layout(nullptr, G.k, nullptr), "pair index")) {
-    (void)hipGetLastError();
     delete x;
     return nullptr;
   }
