@@ -1639,32 +1639,46 @@ int update_jobs(const sketch_update_job_t *jobs, size_t n_jobs, hipStream_t st) 
   // a fresh sketch whose update writes every tile skips its zero fill; any
   // other fresh sketch with pairs gets its zeros first. A linear update
   // always writes every tile, with the zero counts
-  std::vector<char> fresh(n_jobs, 0);
+  std::vector<char> fresh(n_jobs, 0), unwritten(n_jobs, 0);
   const std::vector<UpdPath> path =
       update_paths(jobs, n_jobs, [&](size_t j) { return jobs[j].sketch->fresh; });
-  for (size_t j = 0; j < n_jobs; j++) {
+  for (size_t j = 0; j < n_jobs && !rc; j++) {
     sketch *s = jobs[j].sketch;
     if (jobs[j].n_pairs == 0) continue;
     rc = lane_enter(s->lane, st);
-    if (rc) return rc;
+    if (rc) break;
     s->writes++;
     if (s->fresh && writes_all(jobs[j], path[j])) {
-      fresh[j] = 1;
+      fresh[j] = unwritten[j] = 1;
       s->fresh = false;
       s->lez_valid = s->lez != nullptr;     // every tile is written
     } else {
       rc = materialize(s, st);
-      if (rc) return rc;
       if (path[j] == UPD_LINEAR) s->lez_valid = s->lez != nullptr;
       else if (path[j] == UPD_DIRECT || (((uintptr_t)jobs[j].d_pairs) & 15u))
         s->lez_valid = false;               // the direct kernel sets bits
     }
   }
-  rc = schedule_update(
-      jobs, n_jobs, path, [&](size_t j) { return job_base(jobs[j].sketch); },
-      [&](Group &g) { return flush_group(c, g, st); }, fresh.data());
-  for (size_t j = 0; j < n_jobs && !rc; j++)
-    if (jobs[j].n_pairs) rc = lane_leave(jobs[j].sketch->lane, st);
+  if (!rc)
+    rc = schedule_update(
+        jobs, n_jobs, path, [&](size_t j) { return job_base(jobs[j].sketch); },
+        [&](Group &g) { return flush_group(c, g, st); }, fresh.data());
+  if (rc) {
+    // what was to be written may not have been (no room for the codes, a
+    // launch that failed): a reset sketch is reset as before, and zero counts
+    // are made again
+    for (size_t j = 0; j < n_jobs; j++) {
+      if (jobs[j].n_pairs == 0) continue;
+      if (unwritten[j]) jobs[j].sketch->fresh = true;
+      jobs[j].sketch->lez_valid = false;
+    }
+  }
+  // after a failure too: some of the work may have been enqueued
+  for (size_t j = 0; j < n_jobs; j++) {
+    if (jobs[j].n_pairs == 0) continue;
+    const int left = lane_leave(jobs[j].sketch->lane, st);
+    if (!rc) rc = left;
+  }
   return rc;
 }
 

@@ -38,3 +38,32 @@ def test_the_next_call_does_not_report_it():
         sk.set_option(ddhf.SKETCH_OPT_TRIM_POOLS, 0)
         refused(lambda: sk.update(pairs))
         assert_spl_equal(other.restore(700.0)[0], *want)
+
+
+@pytest.mark.parametrize("reset", [False, True])
+def test_the_sketch_is_what_it_was(reset):
+    """Also what a reset made of it, and zero counts that were stale before."""
+    p = oracle.Params(1024, 16, 5, 6)
+    words = hosts_sketch(p, 50, 6)
+    want = oracle.restore(p, words, 700.0, mode="brute")[:3]
+    pairs = torch.zeros((64 << 20, 2), dtype=torch.int32, device="cuda:0")
+    with make_sketch(p) as sk, make_sketch(p) as other:
+        for s in (sk, other):
+            s.reset()
+            s.update(pairs[:50_000])                # zero counts of other words
+            s.upload(words)
+            if reset:
+                s.reset()
+        sk.set_option(ddhf.SKETCH_OPT_TRIM_POOLS, 0)
+        refused(lambda: ddhf.update_batch([(other, pairs), (sk, pairs)]))
+        for s in (sk, other):
+            recs, info = s.restore(700.0)
+            if reset:
+                assert len(recs) == 0 and not any(info["he_count"])
+            else:
+                assert_spl_equal(recs, *want)
+            assert np.array_equal(s.download(), words * 0 if reset else words)
+        sk.reset()
+        sk.update(pairs[:100])
+        assert np.array_equal(sk.download(),
+                              oracle.build_sketch(p, np.zeros((100, 2), np.uint32)))
