@@ -164,6 +164,8 @@ VALU_LANE_OPS_PEAK = 256 * 4 * 16 * 2.4e9
 # the next address, its row-1 LE (xor, and), the LE's bitmap word (shift),
 # the bit's test (shift, and)
 LATTICE_OPS_PER_POINT = 6
+# The search by pairs reads one cache line per pair of hot LEs
+PAIR_RECORD_BYTES = 128
 
 
 def restore_roofline(timings: list) -> dict:
@@ -176,7 +178,14 @@ def restore_roofline(timings: list) -> dict:
     hs = med["hot_scan_bytes"] / (med["hot_scan_ms"] / 1e3) / 1e9
     eg = med["estimate_bytes"] / (med["estimate_ms"] / 1e3) / 1e9
     search_s = med["join_ms"] / 1e3
-    if int(med["search"]) == 2:
+    if int(med["search"]) == 2 and med.get("pairs"):
+        # by the pair index: each pair brings its record's cache line from the L2
+        traffic = PAIR_RECORD_BYTES * med["pairs"] / search_s
+        search = {"kind": "pairs", "bound": "l2", "pairs": int(med["pairs"]),
+                  "outputs": int(med["join_outputs"]),
+                  "pairs_per_s": round(med["pairs"] / search_s, 1),
+                  "achieved": round(traffic / 1e12, 4), "unit": "TB/s of records"}
+    elif int(med["search"]) == 2:
         ops = LATTICE_OPS_PER_POINT * med["lattice_points"] / search_s
         search = {"kind": "lattice", "bound": "alu", "points": int(med["lattice_points"]),
                   "outputs": int(med["join_outputs"]),

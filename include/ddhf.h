@@ -374,7 +374,10 @@ enum {
                                        of Algs. 3-4, 2 = the lattice search
                                        (every address of each hot row-0 LE,
                                        enumerated from the structure of DH0,
-                                       tested in rows 1..r-1; needs k <= 20) */
+                                       tested in rows 1..r-1; or, where |HE(1)|
+                                       is small and k 14 to 18, those of each
+                                       hot (row-0, row-1) pair from an index;
+                                       needs k <= 20) */
   SKETCH_OPT_BINNED_SAMPLE = 12,    /* binned: the count pass, which sizes
                                        each tile's code regions, reads every
                                        n-th batch of pairs, 1..1024 (1: all,
@@ -403,7 +406,9 @@ enum {
 /* Phases of the last restore that ran with SKETCH_OPT_TIMING on (device
  * time between events recorded on its stream), with the work each phase
  * did, for rooflines of the restore kernels (Alg. 2 and Algs. 3-4 as
- * computed in Sec. 4.2, eq. (4)). */
+ * computed in Sec. 4.2, eq. (4)). With timing on, sketches of k = 12 to 16
+ * take the larger sketches' scan kernels, one or more per phase; without it
+ * one kernel does the first two phases. */
 typedef struct {
   float hot_scan_ms;        /* state reset and hot scan: z0, ZR(i), hot bitmap */
   float rows_ms;            /* HE(i) compaction, bucket tables, scalars */
@@ -420,9 +425,13 @@ typedef struct {
   uint64_t estimate_bytes;  /* candidates * r * g / 8 (the LEs gathered) */
   uint32_t search;          /* the search that ran: 1 join, 2 lattice (0: none,
                                the sketch was saturated) */
-  uint32_t pad;
+  uint32_t pairs;           /* lattice search by pairs: the (row-0, row-1) pairs
+                               of hot LEs that it went through,
+                               |HE(0)| * |HE(1)|; 0 for the walk and the join */
   uint64_t lattice_points;  /* lattice search: addresses of the hot row-0 LEs,
-                               |HE(0)| * 2^(32-k); 0 for the join */
+                               |HE(0)| * 2^(32-k), all of which the walk makes
+                               and tests (by pairs only those of hot row-1 LEs
+                               are made); 0 for the join */
 } sketch_timings_t;
 
 /* The timings of the last timed restore of s (waits for its events).

@@ -2379,7 +2379,9 @@ int sketch_timings(sketch_t *s, sketch_timings_t *out) {
   if (!h.saturated) {
     out->search = std::min(h.search, 2u);
     if (h.search >= 2) {
-      // every address of every hot row-0 LE: 2^(32-k) per LE
+      // every address of every hot row-0 LE: 2^(32-k) per LE (below 2^32 pairs:
+      // the rule leaves them less than 2^32 / 13)
+      if (h.search == 3) out->pairs = h.he_count[0] * h.he_count[1];
       out->lattice_points = (uint64_t)h.he_count[0] << (32 - s->p.k);
       out->join_outputs = h.n_cand;
     } else {

@@ -79,7 +79,7 @@ class sketch_timings_t(ctypes.Structure):
                 ("join_ms", ctypes.c_float), ("estimate_ms", ctypes.c_float),
                 ("sort_publish_ms", ctypes.c_float), ("hot_scan_bytes", c_u64),
                 ("join_probes", c_u64), ("join_outputs", c_u64), ("estimate_bytes", c_u64),
-                ("search", ctypes.c_uint32), ("pad", ctypes.c_uint32),
+                ("search", ctypes.c_uint32), ("pairs", ctypes.c_uint32),
                 ("lattice_points", c_u64)]
 
 
