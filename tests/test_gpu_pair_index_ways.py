@@ -64,7 +64,7 @@ def test_buckets_that_no_record_holds(k, alpha):
     words = np.zeros((p.r, 1 << k, p.g // 32), np.uint32)
     words[0, c0] = 0xFFFFFFFF
     words[1, cells] = 0xFFFFFFFF
-    words[2:, ::2] = 0xFFFFFFFF
+    words[2:, 1:] = 0xFFFFFFFF
     words = words.reshape(-1)
     with make_sketch(p) as sk:
         sk.set_option(ddhf.SKETCH_OPT_CANDIDATES, 2)
