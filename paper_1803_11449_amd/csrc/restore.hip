@@ -932,7 +932,9 @@ __global__ __launch_bounds__(LAT_THREADS) void k_lattice(
 #pragma unroll
         for (uint32_t q = 0; q < 8; q++) {
           x[q] = c ^ b;
-          // the block's dynamic LDS, its only LDS, starts at address 0
+          // the block's dynamic LDS, its only LDS (prepare_restore_kernels sees
+          // to that), starts at address 0; taken from row1, the address costs
+          // an addition, of about six instructions per address
           w[q] = *(const LDSP uint32_t *)(uintptr_t)((x[q] >> 3) & bmask);
           b += step;
         }
@@ -2174,9 +2176,13 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
 }
 
 hipError_t prepare_restore_kernels() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_lattice),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)LATTICE_LDS_MAX);
+  // the walk reads its dynamic LDS from address 0
+  hipFuncAttributes lattice;
+  hipError_t e = hipFuncGetAttributes(&lattice, reinterpret_cast<const void *>(k_lattice));
+  if (e == hipSuccess && lattice.sharedSizeBytes != 0) e = hipErrorInvalidConfiguration;
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_lattice),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)LATTICE_LDS_MAX);
   for (const void *f : {reinterpret_cast<const void *>(k_pairs<0>),
                         reinterpret_cast<const void *>(k_pairs<1>),
                         reinterpret_cast<const void *>(k_pairs<2>)})
