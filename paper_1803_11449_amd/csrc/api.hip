@@ -870,15 +870,18 @@ constexpr uint64_t SORT_ONE_HINT = RESTORE_SORT_ONE - RESTORE_SORT_ONE / 4;
 
 // Blocks of the join kernels; fewer than the device's jblk use the first of
 // the pool's segments. Unset, the join takes four blocks per compute unit (a
-// walk two, the most that its LDS leaves), or one when the sketch's last
-// restore had fewer stage-1 wave items than compute units: short hot lists
+// walk what its LDS leaves room for: two up to r = 5, 68 KiB each, and one from
+// r = 6 on, 91 KiB and more; a second set of blocks would load the tables
+// again: restores at r = 6, k = 14 50 against 44 us, r = 8, k = 16 123 against
+// 110, and r = 5 60 with two against 67 with one), or one when the sketch's
+// last restore had fewer stage-1 wave items than compute units: short hot lists
 // leave most of a larger grid idle, and each block still loads its bucket
 // tables.
 uint32_t join_grid(const sketch *s, bool walk) {
   const uint32_t most = s->ctx->jblk, n_cu = most / 4;
   if (s->join_blocks) return std::min(s->join_blocks, most);
   if (s->join_hint && s->join_hint < n_cu) return n_cu;
-  return walk ? 2 * n_cu : most;
+  return walk ? (s->p.r >= 6 ? n_cu : 2 * n_cu) : most;
 }
 
 // by_last: the restore may go by what the last one found. Only where it is
