@@ -733,6 +733,8 @@ struct Thresholds {
 
 // ------------------------------------------------------------------ handle
 
+struct PlanJob;
+
 struct sketch {
   sketch_params_t p;
   Geom G;
@@ -747,6 +749,14 @@ struct sketch {
   bool pending = false;
   Thresholds pend_t{};
   uint64_t pend_writes = 0;
+  // Restores that went by what the last one found and are not collected yet: the
+  // begun one, and a plan's (PlanJob::linked). A call that writes the sketch
+  // enqueues them again before it, with every kernel (before_write), since
+  // they could not be run again afterwards; from then on (overlaps) restores
+  // of this sketch that a later call collects launch every kernel at once.
+  bool pend_by_last = false;
+  PlanJob *plan_job = nullptr;
+  bool overlaps = false;
   // one that has been ended with too small an output buffer: its state and
   // records stay until the sketch's next restore
   bool held = false;
@@ -811,7 +821,8 @@ struct sketch {
   // that ran, whether the list fits the one-launch sort (1, else 0)
   Expectation search_seen, list_seen;
   double ran_e = -1.0;          // the last enqueued restore's exp(-theta / g)
-  bool ran_sort_one = false;    // ... and whether it took the one-launch sort
+  bool ran_sort_one = false;    // ... whether it took the one-launch sort
+  bool ran_by_last = false;     // ... and whether it left kernels out
   uint2 *chunks = nullptr;      // hot scan chunks (scan_chunks)
   PairIndex *pairs = nullptr;   // shared with the device's other handles (null: none)
   uint64_t cost_hint = 0;       // the last restore's row-0 cells times their addresses
@@ -884,9 +895,9 @@ uint32_t join_grid(const sketch *s, bool walk) {
   return walk ? (s->p.r >= 6 ? n_cu : 2 * n_cu) : most;
 }
 
-// by_last: the restore may go by what the last one found. Only where it is
-// waited for in the same call: when that turns out wrong it is run again, on
-// the sketch as it is by then.
+// by_last: the restore may go by what the last one found. When that turns out
+// wrong it is run again, so the sketch has to be as it was by then: where the
+// restore is not waited for in the same call, before_write sees to that.
 RestoreBufs restore_bufs(const sketch *s, const RPool &p, const Thresholds &t, bool by_last) {
   RestoreBufs B{};
   B.lez = s->lez;
@@ -975,9 +986,13 @@ Thresholds thresholds(const sketch *s, double theta) {
   return t;
 }
 
+int before_write(sketch *s, hipStream_t st);
+
 // Write the zeros of a fresh sketch (on st).
 int materialize(sketch *s, hipStream_t st) {
   if (!s->fresh) return SKETCH_OK;
+  int rc = before_write(s, st);
+  if (rc) return rc;
   HIP_OK(launch_fill_u32(s->d_sketch, s->words, 0u, s->grid * 4, st));
   s->writes++;
   s->fresh = false;
@@ -1015,8 +1030,14 @@ int restore_launch_on(sketch *s, const RestoreBufs &B, Lane &pool, const Thresho
 // waited, as_is: see restore_launch_on).
 int restore_launch_pool(sketch *s, const Thresholds &t, int estimate, int i, hipStream_t st,
                         bool by_last, bool waited = false, bool as_is = false) {
+  if (!as_is && s->fresh) {
+    int rc = lane_enter(s->lane, st);
+    if (!rc) rc = materialize(s, st);
+    if (rc) return rc;
+  }
   RPool &p = s->ctx->pool[i];
   const RestoreBufs B = restore_bufs(s, p, t, by_last);
+  s->ran_by_last = B.expect || B.sort_one;
   s->ran_seg_cap = B.seg_cap;
   s->ran_cand_cap = B.cand_cap;
   s->ran_spl_cap = B.spl_cap;
@@ -1642,13 +1663,15 @@ int update_jobs(const sketch_update_job_t *jobs, size_t n_jobs, hipStream_t st) 
   // a fresh sketch whose update writes every tile skips its zero fill; any
   // other fresh sketch with pairs gets its zeros first. A linear update
   // always writes every tile, with the zero counts
-  std::vector<char> fresh(n_jobs, 0), unwritten(n_jobs, 0);
+  std::vector<char> flags(2 * n_jobs, 0);
+  char *const fresh = flags.data(), *const unwritten = fresh + n_jobs;
   const std::vector<UpdPath> path =
       update_paths(jobs, n_jobs, [&](size_t j) { return jobs[j].sketch->fresh; });
   for (size_t j = 0; j < n_jobs && !rc; j++) {
     sketch *s = jobs[j].sketch;
     if (jobs[j].n_pairs == 0) continue;
-    rc = lane_enter(s->lane, st);
+    rc = before_write(s, st);
+    if (!rc) rc = lane_enter(s->lane, st);
     if (rc) break;
     s->writes++;
     if (s->fresh && writes_all(jobs[j], path[j])) {
@@ -1665,7 +1688,7 @@ int update_jobs(const sketch_update_job_t *jobs, size_t n_jobs, hipStream_t st) 
   if (!rc)
     rc = schedule_update(
         jobs, n_jobs, path, [&](size_t j) { return job_base(jobs[j].sketch); },
-        [&](Group &g) { return flush_group(c, g, st); }, fresh.data());
+        [&](Group &g) { return flush_group(c, g, st); }, fresh);
   if (rc) {
     // what was to be written may not have been (no room for the codes, a
     // launch that failed): a reset sketch is reset as before, and zero counts
@@ -1713,8 +1736,19 @@ struct PlanJob {
   size_t h_recs_cap = 0, ran_h_recs_cap = 0;
   uint4 *sorted = nullptr;
   size_t sorted_cap = 0;
-  size_t ran_spl_cap = 0;       // record capacity the captured restore has
-  size_t ran_seg_cap = 0, ran_cand_cap = 0;   // pool capacities of the capture
+  // a restore's buffers and what it left out: the captured one's, and the one
+  // whose result stands in st and h_state
+  struct Ran {
+    size_t seg_cap = 0, cand_cap = 0, spl_cap = 0;   // entries
+    int pool = 0;
+    bool by_last = false, sort_one = false;
+  } cap, ran;
+  // the last run went by what was found before and is not collected yet
+  // (sketch::plan_job points here)
+  bool linked = false;
+  // the last run's restore was enqueued again (before_write), and its end
+  bool redone = false;
+  hipEvent_t redo_ev = nullptr;
   int pool = 0;                 // restore pool of the captured restore
   bool eager = false;           // this result comes from an eager rerun
   uint64_t ran_writes = 0;      // the sketch's writes at the last run
@@ -1743,6 +1777,11 @@ struct sketch_plan {
   bool dirty = true;            // a plan-owned buffer changed since the capture
   uint64_t gen = ~0ull;         // device context generation at the capture
   bool ran = false;             // the graph has run at least once
+  // Whether the captured restores go by what the sketches' last ones found: from
+  // the first results on, until a window needs something else, or a sketch is
+  // written before its results are collected (each costs another capture, a
+  // millisecond and more)
+  enum { FIRST, BY_LAST, EVERY_KERNEL } mode = FIRST;
   hipStream_t run_stream = nullptr;
 };
 
@@ -1760,6 +1799,8 @@ void plan_free(sketch_plan *P) {
   plan_free_graph(P);
   if (P->cap) (void)hipStreamDestroy(P->cap);
   for (PlanJob &j : P->jobs) {
+    if (j.linked) j.s->plan_job = nullptr;
+    if (j.redo_ev) (void)hipEventDestroy(j.redo_ev);
     dev_free(j.hist);
     dev_free(j.totals);
     dev_free(j.base);
@@ -1790,14 +1831,11 @@ int plan_alloc_sorted(PlanJob &j, size_t cap) {
   return rc;
 }
 
-RestoreBufs plan_restore_bufs(const sketch_plan *P, const PlanJob &j) {
-  const RPool &pool = P->ctx->pool[j.pool];
-  // the sketch's rows, the job's pool; every kernel, as a run is waited for in
-  // another call
-  RestoreBufs B = restore_bufs(j.s, pool, j.t, false);
-  // the zero counts are known valid at capture only when each run starts
-  // the window and its update writes every tile
-  B.lez_stale = !((P->flags & SKETCH_PLAN_RESET) && j.fresh);
+// The buffers of job j's restore on restore pool i: the sketch's rows, the
+// plan's outputs.
+RestoreBufs plan_job_bufs(const PlanJob &j, int i, bool by_last) {
+  const RPool &pool = j.s->ctx->pool[i];
+  RestoreBufs B = restore_bufs(j.s, pool, j.t, by_last);
   B.st = j.st;
   B.spl_sorted = j.sorted;
   B.spl_cap = std::min(pool.spl_cap, j.sorted_cap);
@@ -1805,6 +1843,65 @@ RestoreBufs plan_restore_bufs(const sketch_plan *P, const PlanJob &j) {
   B.h_recs = j.d_h_recs;
   B.h_recs_cap = j.h_recs_cap;
   return B;
+}
+
+PlanJob::Ran plan_ran(const RestoreBufs &B, int pool) {
+  return PlanJob::Ran{B.seg_cap, B.cand_cap, B.spl_cap, pool, B.expect || B.sort_one,
+                      B.sort_one != 0};
+}
+
+// The captured restore of job j.
+RestoreBufs plan_restore_bufs(const sketch_plan *P, const PlanJob &j, bool by_last) {
+  RestoreBufs B = plan_job_bufs(j, j.pool, by_last && !j.s->overlaps);
+  // the zero counts are known valid at capture only when each run starts
+  // the window and its update writes every tile
+  B.lez_stale = !((P->flags & SKETCH_PLAN_RESET) && j.fresh);
+  return B;
+}
+
+// Job j's last run has been collected, or overwritten.
+void plan_unlink(PlanJob &j) {
+  if (j.linked) j.s->plan_job = nullptr;
+  j.linked = false;
+}
+
+// The sketch is about to be written on st: see sketch::pend_by_last. Caller
+// holds ctx->mu.
+int before_write(sketch *s, hipStream_t st) {
+  if (s->pending && s->pend_by_last) {
+    s->overlaps = true;
+    s->pend_by_last = false;
+    int rc = restore_launch_pool(s, s->pend_t, 1, 0, st, false, false, true);
+    if (rc) return rc;
+    HIP_OK(hipEventRecord(s->restore_ev, st));
+    s->pend_writes = s->writes;
+  }
+  if (s->plan_job) {
+    PlanJob &j = *s->plan_job;
+    RPool &p = s->ctx->pool[0];
+    s->overlaps = true;
+    plan_unlink(j);
+    const RestoreBufs B = plan_job_bufs(j, 0, false);
+    int rc = lane_enter(s->lane, st);
+    if (!rc) rc = lane_enter(p.lane, st);
+    if (rc) return rc;
+    HIP_OK(launch_restore(s->G, s->d_sketch, B, j.t.zhot, j.t.e_theta, 1, s->grid, st));
+    HIP_OK(hipEventRecord(j.redo_ev, st));
+    j.redone = true;
+    j.ran = plan_ran(B, 0);
+    j.ran_writes = s->writes;
+    rc = lane_leave(p.lane, st);
+    if (!rc) rc = lane_leave(s->lane, st);
+    return rc;
+  }
+  return SKETCH_OK;
+}
+
+// before_write for calls that hold no lock.
+int before_write_unlocked(sketch *s, hipStream_t st) {
+  if (!s->pending && !s->plan_job) return SKETCH_OK;
+  std::lock_guard<std::mutex> lk(s->ctx->mu);
+  return before_write(s, st);
 }
 
 // Enqueue one whole run on st: resets, update launches, restores and the
@@ -1825,8 +1922,9 @@ int plan_enqueue(sketch_plan *P, hipStream_t st) {
     HIP_OK(batch_fork(P->ctx, used.data(), st));
     for (PlanJob &j : P->jobs) {
       hipStream_t js = pool_stream(P->ctx, j.pool, st);
-      HIP_OK(launch_restore(j.s->G, j.s->d_sketch, plan_restore_bufs(P, j), j.t.zhot,
-                            j.t.e_theta, 1, j.s->grid, js));
+      const RestoreBufs B = plan_restore_bufs(P, j, P->mode == sketch_plan::BY_LAST);
+      HIP_OK(launch_restore(j.s->G, j.s->d_sketch, B, j.t.zhot, j.t.e_theta, 1, j.s->grid, js));
+      j.cap = plan_ran(B, j.pool);
     }
     HIP_OK(batch_join(P->ctx, used.data(), st));
   }
@@ -1867,10 +1965,6 @@ int plan_build_graph(sketch_plan *P) {
   P->graph = g;
   HIP_OK(hipGraphInstantiate(&P->exec, P->graph, nullptr, nullptr, 0));
   for (PlanJob &j : P->jobs) {
-    const RPool &pool = c->pool[j.pool];
-    j.ran_seg_cap = pool.seg_cap;
-    j.ran_cand_cap = pool.cand_cap;
-    j.ran_spl_cap = std::min(pool.spl_cap, j.sorted_cap);
     j.ran_h_recs_cap = j.h_recs_cap;
   }
   P->gen = c->gen;
@@ -2002,6 +2096,7 @@ void sketch_destroy(sketch_t *s) {
   if (!s) return;
   DeviceGuard guard(s->p.device);
   (void)hipDeviceSynchronize();
+  if (s->plan_job) s->plan_job->linked = false;
   free_sketch(s);
   delete s;
 }
@@ -2036,7 +2131,8 @@ int sketch_merge(sketch_t *dst, const sketch_t *src, void *hip_stream) {
   if (src->fresh) return SKETCH_OK;   // OR with zeros
   DEVICE_GUARD(a.device);
   hipStream_t st = (hipStream_t)hip_stream;
-  int rc = lane_enter(dst->lane, st);
+  int rc = before_write_unlocked(dst, st);
+  if (!rc) rc = lane_enter(dst->lane, st);
   if (!rc) rc = lane_enter(src->lane, st);
   if (!rc) rc = materialize(dst, st);
   if (rc) return rc;
@@ -2150,9 +2246,9 @@ int sketch_restore_noalloc(sketch_t *s, double theta, sketch_sp_t *out, size_t c
   return SKETCH_OK;
 }
 
-// by_last: see restore_bufs.
+// collected: by the same call, before anything else is done with the sketches.
 static int restore_batch_begin(sketch_restore_job_t *jobs, size_t n_jobs, void *hip_stream,
-                               bool by_last) {
+                               bool collected) {
   if (n_jobs == 0) return SKETCH_OK;
   int rc = check_restore_jobs(jobs, n_jobs, "sketch_restore_batch_begin");
   if (rc) return rc;
@@ -2185,12 +2281,13 @@ static int restore_batch_begin(sketch_restore_job_t *jobs, size_t n_jobs, void *
     sketch *s = jobs[j].sketch;
     const hipStream_t js = pool_stream(c, pools[j], st);
     s->pend_t = thresholds(s, jobs[j].theta);
-    rc = restore_launch_pool(s, s->pend_t, 1, pools[j], js, by_last);
+    rc = restore_launch_pool(s, s->pend_t, 1, pools[j], js, collected || !s->overlaps);
     if (!rc && hipEventRecord(s->restore_ev, js) != hipSuccess)
       rc = fail(SKETCH_E_HIP, "sketch_restore_batch_begin: hipEventRecord failed");
     if (rc) return rc;
     s->pending = true;
     s->pend_writes = s->writes;
+    s->pend_by_last = s->ran_by_last;
   }
   if (batch_join(c, used, st) != hipSuccess)
     return fail(SKETCH_E_HIP, "sketch_restore_batch_begin: stream join failed");
@@ -2223,7 +2320,7 @@ int sketch_restore_batch_end(sketch_restore_job_t *jobs, size_t n_jobs, void *hi
     std::lock_guard<std::mutex> lk(c->mu);
     bool again = false;
     if (rc == SKETCH_OK && s->pending) rc = restore_check(s, 1, &again);
-    s->pending = false;
+    s->pending = s->pend_by_last = false;
     if (rc == SKETCH_OK && again) rc = rerun_restore(s, s->pend_t, s->pend_writes, st);
     const DevState h = *s->h_state;
     if (rc == SKETCH_OK || rc == SKETCH_E_SATURATED)
@@ -2425,7 +2522,8 @@ int sketch_upload(sketch_t *s, const uint32_t *host_words, size_t n_words, void 
     return fail(SKETCH_E_INVAL, "sketch_upload: n_words %zu, sketch has %zu", n_words, s->words);
   DEVICE_GUARD(s->p.device);
   hipStream_t st = (hipStream_t)hip_stream;
-  int rc = lane_enter(s->lane, st);
+  int rc = before_write_unlocked(s, st);
+  if (!rc) rc = lane_enter(s->lane, st);
   if (rc) return rc;
   s->writes++;
   HIP_OK(hipMemcpyAsync(s->d_sketch, host_words, n_words * 4, hipMemcpyHostToDevice, st));
@@ -2490,6 +2588,10 @@ int sketch_plan_create(const sketch_plan_job_t *jobs, size_t n_jobs, int flags,
     if (!rc) rc = pinned_alloc(&pj.h_state, &pj.d_h_state, 1, "plan state");
     if (!rc) rc = pinned_alloc(&pj.h_recs, &pj.d_h_recs, pj.sorted_cap, "plan records");
     if (!rc) pj.h_recs_cap = pj.sorted_cap;
+    if (!rc && hipEventCreateWithFlags(&pj.redo_ev, hipEventDisableTiming) != hipSuccess) {
+      pj.redo_ev = nullptr;
+      rc = fail(SKETCH_E_HIP, "plan: hipEventCreate failed");
+    }
   }
   if (!rc && hipStreamCreateWithFlags(&P->cap, hipStreamNonBlocking) != hipSuccess) {
     P->cap = nullptr;
@@ -2582,7 +2684,9 @@ int sketch_plan_run(sketch_plan_t *P, void *hip_stream) {
   // a plan that does not reset works on the sketches as they are: write the
   // zeros of fresh ones first; a resetting plan leaves none fresh
   for (PlanJob &j : P->jobs) {
-    int rc = lane_enter(j.s->lane, st);
+    plan_unlink(j);
+    int rc = before_write(j.s, st);
+    if (!rc) rc = lane_enter(j.s->lane, st);
     if (rc) return rc;
     if (P->flags & SKETCH_PLAN_RESET) {
       j.s->fresh = false;
@@ -2592,7 +2696,7 @@ int sketch_plan_run(sketch_plan_t *P, void *hip_stream) {
       if (rc) return rc;
       j.s->lez_valid = false;
     }
-    j.s->writes++;
+    if ((P->flags & SKETCH_PLAN_RESET) || j.n) j.s->writes++;
     j.ran_writes = j.s->writes;
   }
   int rc = SKETCH_OK;
@@ -2607,6 +2711,12 @@ int sketch_plan_run(sketch_plan_t *P, void *hip_stream) {
   for (PlanJob &j : P->jobs)
     if (!rc) rc = lane_leave(j.s->lane, st);
   if (rc) return rc;
+  for (PlanJob &j : P->jobs) {
+    j.ran = j.cap;
+    j.redone = false;
+    j.linked = (P->flags & SKETCH_PLAN_RESTORE) && j.cap.by_last;
+    if (j.linked) j.s->plan_job = &j;
+  }
   P->ran = true;
   P->run_stream = st;
   return SKETCH_OK;
@@ -2633,8 +2743,14 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
   DevCtx *c = P->ctx;
   std::lock_guard<std::mutex> lk(c->mu);
   int first_err = SKETCH_OK;
+  bool by_last = true;                  // whether the next runs may
   for (size_t j = 0; j < n_out; j++) {
     PlanJob &pj = P->jobs[j];
+    plan_unlink(pj);
+    if (pj.redone) {
+      HIP_OK(hipEventSynchronize(pj.redo_ev));
+      by_last = false;
+    }
     sketch *s = pj.s;
     sketch_restore_job_t &J = out[j];
     J.theta = pj.theta;
@@ -2652,14 +2768,18 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
       // a stage overflowed if its count passed the capacity the graph ran
       // with; the shared buffers grow as for an eager restore (which moves
       // them, so the next run captures again) and this job runs again alone
-      if (need_part > pj.ran_seg_cap || h->n_cand > pj.ran_cand_cap ||
-          h->n_spl > pj.ran_spl_cap) {
+      const bool whole = need_part <= pj.ran.seg_cap && h->n_cand <= pj.ran.cand_cap &&
+                         h->n_spl <= pj.ran.spl_cap;
+      const bool missed =
+          missed_expectation(s, *h, pj.t.e_theta, pj.ran.sort_one, 1, whole);
+      if (missed) by_last = false;
+      if (missed || !whole) {
         if (h->n_spl > pj.sorted_cap) {
           rc = plan_alloc_sorted(pj, grown(h->n_spl, pj.sorted_cap));
           P->dirty = true;
         }
         // the job's pool grows for the next runs (a move recaptures the graph)
-        RPool &pool = c->pool[pj.pool];
+        RPool &pool = c->pool[pj.ran.pool];
         if (!rc && need_part > pool.seg_cap) rc = grow_partials(c, pool, need_part);
         if (!rc && h->n_cand > pool.cand_cap) rc = grow_cand(c, pool, h->n_cand);
         if (!rc && h->n_spl > pool.spl_cap) rc = grow_pool_spl(c, pool, h->n_spl);
@@ -2698,6 +2818,14 @@ int sketch_plan_results(sketch_plan_t *P, sketch_restore_job_t *out, size_t n_ou
     if (rc && !first_err) first_err = rc;
   }
   HIP_OK(hipStreamSynchronize(st));
+  if (!by_last) {
+    if (P->mode == sketch_plan::BY_LAST) P->dirty = true;
+    P->mode = sketch_plan::EVERY_KERNEL;
+  } else if (P->mode == sketch_plan::FIRST) {
+    P->mode = sketch_plan::BY_LAST;
+    for (const PlanJob &pj : P->jobs)
+      if (plan_ran(plan_restore_bufs(P, pj, true), pj.pool).by_last) P->dirty = true;
+  }
   if (first_err)
     return fail(first_err, "sketch_plan_results: a job failed (see each job's status)");
   return SKETCH_OK;

@@ -10,6 +10,7 @@ import oracle
 from paper_1803_11449_amd import ddhf
 from test_gpu_parity import assert_spl_equal, crafted_hot_sketch, make_sketch, rand_pairs, say, to_dev
 from test_gpu_restore_launches import hosts_sketch
+from test_gpu_restore_passes import kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -186,3 +187,95 @@ def test_an_ended_restore_is_ended_again_only_for_more_room():
         sk.restore(100.0)
         with pytest.raises(ddhf.SketchError):       # another restore has come since
             end(100)
+
+
+def left_out(k):
+    """Whether a restore's launches (by name) leave a search or the long sort out."""
+    return not (k["k_lattice"] and (k["k_join"] or k["k_join_walk"]) and k["k_rank_place"])
+
+
+@pytest.mark.parametrize("planned", [False, True])
+def test_every_kernel_only_where_the_sketch_is_written_meanwhile(planned):
+    """Collected before the next window, a restore goes by the last one; the
+    first write in between has it enqueued again, and from then on it
+    launches every kernel at once."""
+    p, theta, before, words = crafted("search up")
+    want = [oracle.restore(p, w, theta, mode="brute")[:3] for w in (before, words)]
+    with make_sketch(p) as sk:
+        plan = ddhf.Plan([(sk, to_dev(EMPTY), theta)], reset=False) if planned else None
+        start = plan.run if planned else lambda: ddhf.restore_batch_begin([(sk, theta)])
+        collect = (lambda _: plan.results()[0][0]) if planned else lambda x: x.end()[0][0]
+        sk.upload(before)
+        for i in range(4):
+            pend, k = kernels(start)
+            say(f"planned {planned}, time {i}: {dict(k)}")
+            assert_spl_equal(collect(pend), *want[0])
+        assert left_out(k)
+        for i in range(4):
+            sk.upload((before, words)[i % 2])
+            pend, k = kernels(start)
+            after, more = kernels(lambda: next_window(sk, p, "large", words))
+            say(f"planned {planned}, written {i}: {dict(k)}, then {dict(more)}")
+            assert left_out(k) == (i == 0) and (more["k_estimate"] == 1) == (i == 0)
+            assert_spl_equal(collect(pend), *want[i % 2])
+            assert np.array_equal(sk.download(), after)
+        if plan:
+            plan.close()
+
+
+def test_two_plans_of_one_sketch():
+    """A plan that resets the sketch runs before another's results are asked
+    for; either one's are its own run's, also when the other has gone."""
+    p, theta, before, words = crafted("search down")
+    want = [oracle.restore(p, w, theta, mode="brute")[:3] for w in (before, words)]
+    pairs = rand_pairs(np.random.default_rng(2), 200_000, 900)
+    built = oracle.build_sketch(p, pairs)
+    theirs = oracle.restore(p, built, theta, mode="brute")[:3]
+    with make_sketch(p) as sk:
+        one = ddhf.Plan([(sk, to_dev(EMPTY), theta)], reset=False)
+        two = ddhf.Plan([(sk, to_dev(pairs), theta)])
+        sk.upload(before)
+        for _ in range(3):
+            one.run()
+            assert_spl_equal(one.results()[0][0], *want[0])
+        for i in range(3):
+            sk.upload((words, before)[i % 2])
+            one.run()
+            for _ in range(3):
+                two.run()
+            say(f"two plans, time {i}")
+            assert_spl_equal(one.results()[0][0], *want[1 - i % 2])
+            assert_spl_equal(two.results()[0][0], *theirs)
+            assert np.array_equal(sk.download(), built)
+        sk.upload(words)
+        two.run()
+        two.results()
+        two.run()
+        one.run()
+        one.close()
+        assert_spl_equal(two.results()[0][0], *theirs)
+        two.run()
+        two.close()
+        sk.reset()
+        sk.update(to_dev(pairs))
+        assert_spl_equal(sk.restore(theta)[0], *theirs)
+
+
+def test_written_on_another_stream():
+    """Begun on one stream, written on two others: the restore that is enqueued
+    again waits for the first and goes before the write."""
+    p, theta, before, words = crafted("search up")
+    want = [oracle.restore(p, w, theta, mode="brute")[:3] for w in (before, words)]
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    with make_sketch(p) as sk, make_sketch(p) as other:
+        for i in range(6):
+            kind = i % 2
+            for s in (sk, other):
+                s.upload((before, words)[kind], stream=streams[0])
+            pend = ddhf.restore_batch_begin([(sk, theta), (other, theta)], stream=streams[1])
+            after = next_window(sk, p, "large", words, streams[2])
+            next_window(other, p, "small", words)
+            (recs, _), (rest, _) = pend.end()
+            assert_spl_equal(recs, *want[kind])
+            assert_spl_equal(rest, *want[kind])
+            assert np.array_equal(sk.download(stream=streams[i % 3]), after)
