@@ -93,8 +93,9 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *total,
 // spent 1.2 of its 1.35 ms on 115,000 candidates. The first CAP of a block
 // are kept in LDS and appended by one atomic when the block ends; the rest
 // go out as they come.
-struct CandBuf {
-  static constexpr uint32_t CAP = 512;
+template <uint32_t CAP_>
+struct CandBufOf {
+  static constexpr uint32_t CAP = CAP_;
   uint32_t a[CAP], n;
   unsigned long long base;
 
@@ -132,6 +133,8 @@ struct CandBuf {
       if (base + i < cand_cap) cand[base + i] = a[i];
   }
 };
+
+using CandBuf = CandBufOf<512>;
 
 // The most rows a sketch has.
 constexpr uint32_t R_MAX = 8;
@@ -1280,6 +1283,22 @@ struct JoinTable {
   }
 };
 
+// The candidates of a block of the last stage: as many as its LDS has left
+// beside the tables with four blocks on a compute unit (512 of them left room
+// for three).
+using JoinCand = CandBufOf<496>;
+
+template <bool LAST>
+struct JoinLds {
+  uint16_t off[TAB_OFF_MAX];
+  alignas(16) uint8_t val[TAB_VAL_BYTES];
+  uint32_t incl[JOIN_THREADS];
+  uint16_t own[(JOIN_THREADS / 64) * OWN_MAX];
+  uint32_t seg_fill;
+  alignas(8) uint8_t found[LAST ? sizeof(JoinCand) : 8];
+};
+static_assert(sizeof(JoinLds<true>) <= 163840 / 4, "four blocks on a compute unit");
+
 // The wave items of one join block (see k_join).
 template <bool FIRST, bool LAST, bool TLDS>
 __device__ __forceinline__ void join_items(
@@ -1287,7 +1306,7 @@ __device__ __forceinline__ void join_items(
     const uint2 *__restrict__ in, const uint32_t *__restrict__ in_cnt,
     const JoinTable<TLDS> &T, DevState *__restrict__ st, uint2 *__restrict__ out,
     size_t seg_cap, uint32_t *__restrict__ cand, size_t cand_cap, uint32_t M,
-    LDSP uint32_t *w_incl, LDSP uint16_t *w_own, LDSP uint32_t *seg_fill_p, CandBuf *found) {
+    LDSP uint32_t *w_incl, LDSP uint16_t *w_own, LDSP uint32_t *seg_fill_p, JoinCand *found) {
   LDSP uint32_t &seg_fill = *seg_fill_p;
   const uint32_t lane = lane_id();
   const uint32_t wib = threadIdx.x >> 6;                    // wave in block
@@ -1436,12 +1455,12 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
     const uint32_t *__restrict__ bk_off, const uint32_t *__restrict__ bk_val,
     DevState *__restrict__ st, uint2 *__restrict__ out, uint32_t *__restrict__ out_cnt,
     size_t seg_cap, uint32_t *__restrict__ cand, size_t cand_cap, double e_theta) {
-  __shared__ uint16_t t_off[TAB_OFF_MAX];
-  __shared__ __attribute__((aligned(16))) uint8_t t_val[TAB_VAL_BYTES];
-  __shared__ uint32_t w_incl[JOIN_THREADS];
-  __shared__ uint16_t w_own[(JOIN_THREADS / 64) * OWN_MAX];
-  __shared__ uint32_t seg_fill;
-  __shared__ CandBuf found;
+  __shared__ JoinLds<LAST> L;
+  uint16_t *const t_off = L.off, *const w_own = L.own;
+  uint8_t *const t_val = L.val;
+  uint32_t *const w_incl = L.incl;
+  uint32_t &seg_fill = L.seg_fill;
+  JoinCand *const found = reinterpret_cast<JoinCand *>(L.found);   // last stage only
   const bool chosen = !lattice_chosen(G, st, ways, path);
   if (FIRST) search_begin(G, st, e_theta, chosen, 1);
   if (!chosen || no_zeros(G, st)) return;
@@ -1455,7 +1474,7 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
   const uint32_t *g_val = bk_val + ((size_t)row << G.k);
   if (threadIdx.x == 0) {
     seg_fill = 0;
-    found.n = 0;
+    if (LAST) found->n = 0;
   }
   if (lds) {
     for (uint32_t x = threadIdx.x; x <= nb; x += blockDim.x) t_off[x] = (uint16_t)g_off[x];
@@ -1472,16 +1491,16 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
                             lds_ptr(reinterpret_cast<uint16_t *>(t_val)), g_off, g_val,
                             G.k - G.alpha, wide_t};
     join_items<FIRST, LAST, true>(G, row, he, in, in_cnt, T, st, out, seg_cap, cand, cand_cap,
-                                  M, lds_ptr(w_incl), lds_ptr(w_own), lds_ptr(&seg_fill), &found);
+                                  M, lds_ptr(w_incl), lds_ptr(w_own), lds_ptr(&seg_fill), found);
   } else {
     const JoinTable<false> T{lds_ptr(t_off), lds_ptr(t_val),
                              lds_ptr(reinterpret_cast<uint16_t *>(t_val)), g_off, g_val,
                              G.k - G.alpha, wide_t};
     join_items<FIRST, LAST, false>(G, row, he, in, in_cnt, T, st, out, seg_cap, cand,
                                    cand_cap, M, lds_ptr(w_incl), lds_ptr(w_own),
-                                   lds_ptr(&seg_fill), &found);
+                                   lds_ptr(&seg_fill), found);
   }
-  if (LAST) found.flush(st, cand, cand_cap);
+  if (LAST) found->flush(st, cand, cand_cap);
   if (!LAST) {
     __syncthreads();
     if (threadIdx.x == 0) {
