@@ -506,23 +506,31 @@ __device__ __forceinline__ void bucket_rows(const Geom &G, uint32_t row, const u
 
 // --------------------------------------------------------------- 4: scalars
 
+// The whole first wave of a block: a lane per row takes its logarithm, and the
+// sum runs over the rows in order. One lane alone took 9 us of a search's
+// first block, which has its share of the search to do: the first stage of a
+// staged join 18 -> 26 us.
 __device__ __forceinline__ void scalars(const Geom &G, DevState *st, double e_theta) {
+  const uint32_t i = lane_id();
   const double m = (double)G.g * (double)(1ull << G.k);
-  double lsum = 0.0;
-  for (uint32_t i = 0; i < G.r; i++) {
-    if (st->zr[i] == 0) {
+  const unsigned long long zr = st->zr[i < G.r ? i : 0];
+  if (__ballot(zr == 0)) {
+    if (i == 0) {
       st->saturated = 1;
       st->psi = 1.0;
       st->d = 0.0;
       st->trep = 0.0;
       st->szmax = 0;
-      return;
     }
-    lsum += log((double)st->zr[i] / m);
+    return;
   }
+  const double l = log((double)zr / m);
+  double lsum = 0.0;
+  for (uint32_t row = 0; row < G.r; row++) lsum += __shfl(l, (int)row, 64);
+  if (i != 0) return;
   const double psi = 1.0 - exp(lsum / (double)G.r);
   double pr = 1.0;
-  for (uint32_t i = 0; i < G.r; i++) pr *= psi;
+  for (uint32_t row = 0; row < G.r; row++) pr *= psi;
   const double d = (double)G.g * (1.0 - pr);
   const double trep = d * e_theta;
   st->psi = psi;
@@ -673,31 +681,37 @@ __device__ __forceinline__ bool pairs_chosen(const Geom &G, const DevState *st, 
 }
 
 // A row without a zero bit left (psi = 1): nothing to search.
+// (Every block of a search asks: the loads go out together.)
 __device__ __forceinline__ bool no_zeros(const Geom &G, const DevState *st) {
-  for (uint32_t i = 0; i < G.r; i++)
-    if (st->zr[i] == 0) return true;
-  return false;
+  bool none = false;
+#pragma unroll
+  for (uint32_t i = 0; i < R_MAX; i++) none = none | ((i < G.r) & (st->zr[i] == 0));
+  return none;
 }
 
 // Step 4 by the first block of each search launched: both searches' kernels
 // follow the scan, and the estimate follows them.
 __device__ __forceinline__ void search_begin(const Geom &G, DevState *st, double e_theta,
                                              bool chosen, uint32_t search) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  if (blockIdx.x != 0 || threadIdx.x >= 64) return;
   const bool full = no_zeros(G, st);
   if (!chosen && !full) return;
   scalars(G, st, e_theta);
-  if (!full) st->search = search;
+  if (threadIdx.x == 0 && !full) st->search = search;
 }
 
 __device__ __forceinline__ bool lattice_chosen(const Geom &G, const DevState *st,
                                                uint32_t ways, uint32_t path) {
   if (!(ways & LAT_OK) || path == 1) return false;
   if (path == 2) return true;
-  const double nb = (double)(1u << (G.k - G.alpha));
-  double p = (double)st->he_count[0] * (double)st->he_count[1], join = p;
-  for (uint32_t i = 2; i < G.r; i++) {
-    p *= (double)st->he_count[i] / nb;
+  const double per = 1.0 / (double)(1u << (G.k - G.alpha));   // a power of two: exact
+  uint32_t h[R_MAX];
+#pragma unroll
+  for (uint32_t i = 0; i < R_MAX; i++) h[i] = st->he_count[i];   // all eight, 0 past r
+  double p = (double)h[0] * (double)h[1], join = p;
+#pragma unroll
+  for (uint32_t i = 2; i < R_MAX; i++) {
+    p *= (double)h[i] * per;
     join += p;
   }
   const double cell = pairs_chosen(G, st, ways) ? pair_work(G, st) : (double)(1ull << (32 - G.k));
