@@ -1251,6 +1251,12 @@ hipError_t launch_pair_index(const Geom &G, uint32_t *off, uint32_t *z, uint32_t
 //    candidate list with a global counter.
 
 constexpr int JOIN_THREADS = 512;
+// Scalar registers that leave four blocks of eight waves on a compute unit: a
+// wave takes 16 for the trap handler beside its own, and above 80 of those
+// seven waves fit a SIMD, which the compiler's occupancy does not count. With
+// 83 the last stage of a join of 238M partial addresses took 3.0 ms, with 80
+// 2.5.
+constexpr int JOIN_SGPRS = 80;
 
 // Orders this wave's LDS writes before its later LDS reads by other lanes.
 __device__ __forceinline__ void lds_fence() {
@@ -1463,7 +1469,7 @@ __device__ __forceinline__ void join_items(
 }
 
 template <bool FIRST, bool LAST>
-__global__ __launch_bounds__(JOIN_THREADS) void k_join(
+__global__ __launch_bounds__(JOIN_THREADS) __attribute__((amdgpu_num_sgpr(JOIN_SGPRS))) void k_join(
     Geom G, uint32_t ways, uint32_t path, uint32_t row, const uint32_t *__restrict__ he,
     const uint2 *__restrict__ in, const uint32_t *__restrict__ in_cnt,
     const uint32_t *__restrict__ bk_off, const uint32_t *__restrict__ bk_val,
@@ -1527,8 +1533,8 @@ __global__ __launch_bounds__(JOIN_THREADS) void k_join(
 
 // ------------------------------------------------- 5c: the join in one launch
 //
-// The join of Algs. 3-4 for sketches with small bucket tables (r >= 4 and
-// 2^(k - alpha) <= WALK_NB), depth first: a wave's stage-1 outputs go to a
+// The join of Algs. 3-4 for sketches with small bucket tables (join_walks),
+// depth first: a wave's stage-1 outputs go to a
 // queue of its own in LDS, and whenever a queue holds 64 partial addresses
 // the wave takes them through the next row, so no partial address leaves the
 // compute unit and the stages need no launches of their own. What bounds it

@@ -1,8 +1,9 @@
-"""What the restore kernels' LDS use has to keep to, by the compiler's figures.
+"""What the restore kernels' resources have to keep to, by the compiler's figures.
 
 The lattice walk reads its dynamic LDS from address 0, which holds while the
 kernel has no LDS of its own (the library checks that too when it sets a
-device up). The staged join's grid counts on four blocks per compute unit."""
+device up). The staged join's grid counts on four blocks per compute unit,
+which the LDS and the scalar registers have to leave."""
 import os
 import re
 import subprocess
@@ -16,7 +17,7 @@ pytestmark = pytest.mark.slow
 
 @pytest.fixture(scope="module")
 def usage():
-    """{kernel: {"LDS": bytes per block, "Occupancy": waves per SIMD}}"""
+    """{kernel: {"LDS": bytes per block, "Occupancy": waves per SIMD, "SGPRs": number}}"""
     if not os.path.exists(lib_build._hipcc()):
         pytest.skip("hipcc not installed")
     cmd = [lib_build._hipcc(), *lib_build.HIPCC_FLAGS, "--offload-device-only",
@@ -29,9 +30,10 @@ def usage():
         m = re.search(r"remark: Function Name: (\S+)", line)
         if m:
             cur = out.setdefault(m.group(1), {})
-        m = re.search(r"(LDS) Size \[bytes/block\]: (\d+)|(Occupancy) \[waves/SIMD\]: (\d+)", line)
+        m = re.search(r"(LDS Size|Occupancy|TotalSGPRs)(?: \[[^]]*\])?: (\d+)", line)
         if m:
-            cur[m.group(1) or m.group(3)] = int(m.group(2) or m.group(4))
+            cur[{"LDS Size": "LDS", "TotalSGPRs": "SGPRs"}.get(m.group(1), m.group(1))] = \
+                int(m.group(2))
     return out
 
 
@@ -45,7 +47,10 @@ def test_the_walk_has_no_static_lds(usage):
 
 
 def test_four_join_blocks_on_a_compute_unit(usage):
-    """Of eight waves each: 8 waves per SIMD."""
+    """Of eight waves each: 8 waves per SIMD, whose scalar registers (granules of
+    16, and 16 more for the trap handler, which the compiler's occupancy leaves
+    out) share 800."""
     joins = of(usage, "k_join")
     assert len(joins) == 4
     assert all(v["LDS"] <= 163840 // 4 and v["Occupancy"] == 8 for v in joins), joins
+    assert all(8 * ((v["SGPRs"] + 15) // 16 * 16 + 16) <= 800 for v in joins), joins
