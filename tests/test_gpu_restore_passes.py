@@ -4,6 +4,7 @@ not happen to a caller whose windows do not change."""
 import time
 from collections import Counter
 
+import numpy as np
 import pytest
 import torch
 from torch.profiler import ProfilerActivity, profile
@@ -109,3 +110,18 @@ def test_windows_of_two_kinds_in_turn(what, fn, each):
             assert n["k_estimate"] == 1
         searches = [x for x in ("k_lattice", "k_pairs", "k_join", "k_join_walk") if n[x]]
         assert len(searches) == 1 and (n["k_sort_publish"] == 1) == (len(want[0]) <= 1536)
+
+
+@pytest.mark.parametrize("g,k,r,alpha,walk", [(128, 20, 4, 10, True), (32, 21, 4, 11, False),
+                                              (32, 22, 4, 12, False)])
+def test_long_joins_go_by_stage(g, k, r, alpha, walk):
+    """Without the lattice search (k > 20) a join may be of long lists."""
+    p = oracle.Params(g, k, r, alpha)
+    words = crafted_hot_sketch(p, 0.0004, 3)
+    with make_sketch(p) as sk:
+        sk.set_option(ddhf.SKETCH_OPT_CANDIDATES, 1)
+        sk.upload(words)
+        got, n = kernels(lambda: sk.candidates(0.8 * g))
+    say(f"k={k} r={r}: {dict(n)}, {len(got)} candidates")
+    assert (n["k_join_walk"], n["k_join"]) == ((1, 0) if walk else (0, r - 2))
+    assert np.array_equal(got, oracle.candidates(p, words, 0.8 * g, "brute"))
