@@ -138,9 +138,15 @@ __device__ __forceinline__ void pair_codes(const Geom &G, uint2 p, uint32_t *B) 
 // wave: the scatter went from 85 to 650 us and more.
 //
 // Slots are claimed in a block's first FILT_CLAIM batches only (in every
-// batch it cost twice as much). The next batch's drops are counted, and a
-// block where fewer than one pair in FILT_WORTH repeats goes on without the
-// filter, whose lookups take about a tenth of the scatter.
+// batch it cost twice as much). The next batch's pairs of owned sources are
+// counted, and a block where they are fewer than one in FILT_WORTH goes on
+// without the filter, whose lookups take about a tenth of the scatter. Not
+// the repeats: a source with a tenth of a block's pairs has set few of a
+// large estimator's bits by the second batch, and most of them by the tenth.
+// Going by those, 50M pairs (a power law, g = 1024, k = 15) took 710 us, 30M
+// (Zipf 0.9, g = 512, k = 17) 351, and by the owned ones 505 and 284. Asked
+// for one in eight instead of 32, 50M pairs with a tenth of one source (g =
+// 2048) took 842 us, not 500.
 //
 // An unowned slot holds a source that belongs to another slot, so that one
 // compare tells a pair's source from every other owner and from none.
@@ -150,7 +156,7 @@ constexpr uint32_t FILT_WORTH = 32;
 template <uint32_t WORDS>
 struct Filter {
   static constexpr uint32_t SLOTS = WORDS / 32;         // at most, for LEs of 32 words and less
-  uint32_t bits[WORDS], own[SLOTS], last[SLOTS], drops;
+  uint32_t bits[WORDS], own[SLOTS], last[SLOTS], owned;
 
   // slots - 1: as many as SLOTS and the words allow (WORDS >= 2048, the
   // largest LE)
@@ -176,7 +182,7 @@ struct Filter {
     for (uint32_t i = threadIdx.x; i < WORDS; i += blockDim.x) bits[i] = 0;
     for (uint32_t i = threadIdx.x; i < SLOTS; i += blockDim.x)
       own[i] = last[i] = i == s0 ? z : 0u;
-    if (threadIdx.x == 0) drops = 0;
+    if (threadIdx.x == 0) owned = 0;
   }
   // Which of N pairs (sources x, row-0 bit indexes B0) repeat an earlier one:
   // bit k of the result. Every lane has N pairs of its own (a pair given
@@ -214,12 +220,17 @@ struct Filter {
     }
 #pragma unroll
     for (int k = 0; k < N; k++) seen |= (old[k] & m[k]) ? 1u << k : 0u;
-    if (batch == FILT_CLAIM) atomicAdd(&drops, (uint32_t)__popc(seen));
+    if (batch == FILT_CLAIM) {
+      uint32_t mine = 0;
+#pragma unroll
+      for (int k = 0; k < N; k++) mine += m[k] ? 1u : 0u;
+      atomicAdd(&owned, mine);
+    }
     return seen;
   }
   // After a barrier that follows batch FILT_CLAIM: whether to go on.
   __device__ __forceinline__ bool useful(uint32_t pairs) const {
-    return drops * FILT_WORTH >= pairs;
+    return owned * FILT_WORTH >= pairs;
   }
 };
 

@@ -62,6 +62,27 @@ def test_heavy_tiles(p, n, linear):
             assert k["k_lin_apply"] == 7 and np.array_equal(sk.download(), want)
 
 
+@pytest.mark.parametrize("share", [0.0, 0.03, 0.1, 0.6])
+@pytest.mark.parametrize("p", [oracle.Params(1024, 14, 5, 6), oracle.Params(2048, 13, 4, 10)],
+                         ids=lambda p: f"g{p.g}k{p.k}r{p.r}")
+def test_shares_of_one_source(p, share):
+    """A scatter's filter that goes on past its block's second batch, or does
+    not: more than three batches to each block, pairs that come again, the
+    shares of one source around the line."""
+    rng = np.random.default_rng(int(share * 100))
+    n = 5_100_007
+    pairs = rand_pairs(rng, n, 300_000)
+    pairs[rng.random(n) < share, 0] = 99
+    pairs[n // 2:n // 2 + n // 4] = pairs[:n // 4]
+    dev = to_dev(pairs)
+    want = oracle.build_sketch(p, pairs)
+    with make_sketch(p) as sk:
+        for fresh in (True, False):
+            _, k = kernels(lambda: sk.update(dev))
+            say(f"{p} share {share}, fresh {fresh}: {dict(k)}")
+            assert k["k_lin_scatter"] and np.array_equal(sk.download(), want)
+
+
 @pytest.mark.parametrize("k,alpha,n,reset,written", [
     (14, 6, 24_575, "k_update_fresh", "k_update"), (14, 6, 24_576, "linear", "linear"),
     (16, 6, 24_576, "linear", "k_update"), (16, 6, 40_959, "linear", "k_update"),
