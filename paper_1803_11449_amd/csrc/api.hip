@@ -1283,13 +1283,15 @@ bool wants_binned(const sketch *s, size_t n, bool fresh) {
 constexpr uint32_t LIN_MANY = 32;
 uint64_t lin_words(uint64_t tiles) { return tiles * SPLIT_MIN * (6 + tiles) / 6; }
 // And a source with a large part of the pairs piles its words up on r tiles,
-// unless the scatter's filter drops its repeats: at g = 2048 it does (16M
-// pairs, a tenth of one source 220 against 244 us, half of one 190 against
-// 384), with larger LEs it has few slots, and bits that repeat too late for it
-// to stay on (g = 4096: 50M pairs, a tenth of one source 810 against 566; g =
-// 65,536: 4M pairs, half of one 226 against 179, 16M 820 against 420; 1M
-// unfiltered pairs, four fifths of one, 99 against 132, 2M 171 against 155).
-constexpr uint32_t LIN_FILTER_G = 2048;
+// unless the scatter's filter drops its repeats: up to g = 4096 it does (16M
+// pairs, a tenth of one source 233 against 238 us, half of one 226 against
+// 237, none 178 against 228; 4M pairs 95 against 138, 140 against 156, 73
+// against 117; 50M of several sources, a power law or Zipf 0.97 to 1.04 of the
+// region passes), with larger LEs it has few slots, and bits that repeat late
+// (g = 8192: 30M pairs, Zipf 1.5, 596 against 484; g = 65,536: 4M pairs, half
+// of one 207 against 166, 16M 608 against 336; 1M unfiltered pairs, four
+// fifths of one, 96 against 125, 2M 178 against 160).
+constexpr uint32_t LIN_FILTER_G = 4096;
 constexpr uint64_t LIN_UNFILTERED = 3 << 19;
 
 // Whether a binned update of n pairs takes the linear kernels.

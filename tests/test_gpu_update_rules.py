@@ -38,8 +38,9 @@ def test_a_raised_minimum(p, n, fresh):
     (oracle.Params(1024, 9, 5, 8), 12_000_000, True),
     # large estimators
     (oracle.Params(2048, 13, 5, 7), 1_600_000, True),
-    (oracle.Params(4096, 13, 5, 7), 1_572_864, True),
-    (oracle.Params(4096, 13, 5, 7), 1_572_865, False)],
+    (oracle.Params(4096, 13, 5, 7), 1_600_000, True),
+    (oracle.Params(8192, 12, 5, 7), 1_572_864, True),
+    (oracle.Params(8192, 12, 5, 7), 1_572_865, False)],
     ids=lambda x: f"g{x.g}k{x.k}r{x.r}" if isinstance(x, oracle.Params) else str(x))
 def test_heavy_tiles(p, n, linear):
     """A window that would leave few workgroups with long tiles goes through the
