@@ -41,8 +41,8 @@ __device__ __forceinline__ uint32_t bit_block(const Geom &G, uint32_t i,
   return __builtin_amdgcn_ubfe(x, sh, sh < 32 ? G.k : 0u);
 }
 
-// Device-resident state of one restore. Zeroed at the start of each restore
-// by a fill kernel.
+// Device-resident state of one restore, set anew by each restore's first
+// kernels (k_scan_rows or k_compact, else k_restore_init).
 struct DevState {
   unsigned long long zr[8];          // ZR(i)
   unsigned long long n_out[8];       // outputs of join stage i (2..r-1)

@@ -13,7 +13,8 @@
 //                  accepted tuples and skips only failing ones).
 //                  Small sketches take 1-3 in one launch, one block per row
 //                  (k_scan_rows); larger ones in chunks spread over the chip
-//                  (k_hot_scan_lez, k_compact, and k_buckets for the join).
+//                  (k_hot_scan_lez, k_compact, and k_buckets for the join);
+//                  without zero counts k_hot_scan, then k_rows.
 //  4 scalars       psi (Lemma 1 with the flow-count estimate of Sec. 3.3),
 //                  D = g(1 - psi^r) (eq. (4)), T_rep = D*exp(-theta/g) and
 //                  the integer report bound floor(T_rep), in float64, by one
@@ -33,6 +34,8 @@
 //                           the points of a lattice in a box (see Lattice),
 //                           tested against the hot bitmaps of rows 1..r-1:
 //                           eq. (2) read forwards, no partial addresses.
+//                  pairs    of those addresses only the ones of a hot row-1
+//                           cell, by an index of row 0's hash (k = 14 to 18).
 //  6 estimate      per candidate, AND of its r LEs (ULE), SZ = g - popcount,
 //                  report iff SZ <= floor(T_rep) (<=> C >= theta),
 //                  C = -g*ln(SZ/D) (eq. (4)), +inf when SZ = 0.
@@ -657,11 +660,12 @@ __global__ __launch_bounds__(1024) void k_scan_rows(
 // then times |HE(i)| / 2^(k-alpha) per further row, 4.5 ps each on a whole
 // chip (9.7M in 44 us, 10.4M in 48 us). The lattice search's is, per hot
 // row-0 cell, all 2^(32-k) addresses of the cell at 0.44 ps (162M at k = 16 in
-// 71 us, 210M at k = 15 in 88 us), or by the pair index a pair per hot row-1
-// cell: 6.5 ps with the four-part records (6.1M in 44 us), 8.6 with the
-// six-part ones (2.6M in 26 us), and by the lists, as k = 14 has it, 5
-// addresses' worth a part more than 13. Every kernel of the searches evaluates
-// this on the same counts, so exactly one of them runs.
+// 71 us, 210M at k = 15 in 88 us; with the larger bitmaps 0.62 at k = 18, 263M
+// in 162 us, and 0.71 at k = 19, 114M in 82 us), or by the pair index a pair
+// per hot row-1 cell: 6.5 ps with the four-part records (6.1M in 42 us), 8.6
+// with the six-part ones (2.6M in 26 us; 8.3M in 56), and by the lists, as k =
+// 14 has it, 5 addresses' worth a part more than 13. Every kernel of the
+// searches evaluates this on the same counts, so exactly one of them runs.
 constexpr double LATTICE_COST = 0.1;                    // an address, in join items
 // a pair, in addresses
 __device__ constexpr double pair_cost(uint32_t k) {
@@ -758,7 +762,8 @@ constexpr uint32_t LAT_FOUND_BYTES = sizeof(CandBuf) + 8;
 constexpr uint32_t LATTICE_LDS_MAX = 163840;
 
 // Rows whose hot bitmaps a block of the search holds in LDS: rows 1..n, as
-// many as leave a compute unit two blocks (80 KiB each). Row 1 takes every
+// many as fit half a compute unit's LDS (its scalar registers, 106, leave a
+// unit one block of 16 waves, not two). Row 1 takes every
 // address, row 2 those that pass it (61M of 511M addresses at k = 17 with 12%
 // of the LEs hot).
 inline uint32_t lattice_rows(const Geom &G) {
@@ -997,7 +1002,8 @@ constexpr uint32_t PAIR_THREADS = 1024;
 constexpr uint32_t PAIR_QUEUE_BYTES = PAIR_THREADS / 64 * PAIR_QUEUE * 4;
 
 // Rows 2.. whose hot bitmaps a block holds in LDS, two blocks to a compute
-// unit (row 2 always: 32 KiB at k = 18).
+// unit where their scalar registers allow it (80 and less: not k_pairs<1>, with
+// 87); row 2 always: 32 KiB at k = 18.
 inline uint32_t pair_rows(const Geom &G) {
   const uint32_t row = 4u << (G.k - 5);
   uint32_t n = 1;
@@ -2174,7 +2180,7 @@ static hipError_t launch_wpl(const Geom &G, const uint32_t *sketch, const Restor
   // 4-5: scalars and candidates
   if (lattice) {
     // the rows' bitmaps and the queues (above 64 KiB by the attribute that
-    // prepare_restore_kernels sets); two blocks per compute unit, each of
+    // prepare_restore_kernels sets); two blocks for each compute unit, each of
     // which first copies the bitmaps
     const uint32_t rows = lattice_rows(G), threads = lattice_threads(G, rows);
     k_lattice<<<grid > 3 ? grid / 4 : 1, threads, lattice_lds(G, rows, threads), st>>>(
