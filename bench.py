@@ -172,7 +172,8 @@ def restore_roofline(timings: list) -> dict:
     """Restore-side rooflines from the phase timings of the latency runs
     (median of each phase): the hot scan against HBM bandwidth; the
     candidate search, the lattice walk's integer operations against the
-    vector ALU peak or the join's LDS lane operations against the LDS peak;
+    vector ALU peak, the records of the search by pairs (from the L2) or the
+    join's LDS lane operations against the LDS peak;
     the estimate's LE gathers against HBM bandwidth."""
     med = {k: percentile([t[k] for t in timings], 50) for k in timings[0]}
     hs = med["hot_scan_bytes"] / (med["hot_scan_ms"] / 1e3) / 1e9

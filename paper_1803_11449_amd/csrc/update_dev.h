@@ -132,7 +132,7 @@ __device__ __forceinline__ void pair_codes(const Geom &G, uint2 p, uint32_t *B) 
 // the apply pass otherwise waits for: 4M pairs at g = 512, r = 4 (Zipf 1.1),
 // apply 73 -> 27 us for 4 us more in the scatter; 15M pairs at k = 16 (Zipf
 // 1.0), 139 -> 79 us for 15 us; in the regions, 100M pairs (Zipf 1.0, 128
-// slots) apply and merge 396 -> 333 us, 190M pairs (Zipf 1.1, 64 slots) 745 ->
+// slots) apply and merge 396 -> 326 us, 190M pairs (Zipf 1.1, 64 slots) 745 ->
 // 515 us, for about a tenth of the scatter. A table shared by the blocks of an XCD drops
 // more (15M pairs: apply 66 us) but its busiest lines are read by every
 // wave: the scatter went from 85 to 650 us and more.
