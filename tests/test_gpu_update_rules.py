@@ -84,6 +84,36 @@ def test_shares_of_one_source(p, share):
             assert k["k_lin_scatter"] and np.array_equal(sk.download(), want)
 
 
+@pytest.mark.parametrize("p,n", [(oracle.Params(1024, 12, 5, 7), 1_500_000),
+                                 (oracle.Params(16384, 9, 5, 8), 1_500_000),
+                                 (oracle.Params(65536, 8, 5, 8), 1_600_000),
+                                 (oracle.Params(65536, 9, 5, 8), 1_600_000),
+                                 (oracle.Params(1024, 18, 5, 5), 1_600_000)],
+                         ids=lambda x: f"g{x.g}k{x.k}" if isinstance(x, oracle.Params) else str(x))
+@pytest.mark.parametrize("seed", [oracle.Params().seed, 5, 3])
+def test_source_zero(p, n, seed):
+    """The scatter's filter tells source 0 and the next sources, one of which
+    stands for no owner in 0's slot, from a slot without an owner."""
+    p = oracle.Params(p.g, p.k, p.r, p.alpha, seed)
+    rng = np.random.default_rng(n + seed % 1000)
+    pairs = rand_pairs(rng, n, 4000)
+    u = rng.random(n)
+    pairs[u < 0.3, 0] = 0
+    near = (u > 0.3) & (u < 0.6)
+    pairs[near, 0] = rng.integers(1, 64, int(near.sum()))
+    pairs[-(n // 3):] = pairs[:n // 3]
+    dev = to_dev(pairs)
+    want = oracle.build_sketch(p, pairs)
+    with make_sketch(p) as sk:
+        sk.set_option(ddhf.SKETCH_OPT_SCATTER_PPT, 4)
+        sk.set_option(ddhf.SKETCH_OPT_BINNED_BLOCKS, 40)
+        for _ in range(2):
+            _, k = kernels(lambda: sk.update(dev))
+            say(f"{p} {n} pairs: {dict(k)}")
+            assert k["k_lin_scatter"] or k["k_bin_scatter"]
+            assert np.array_equal(sk.download(), want)
+
+
 @pytest.mark.parametrize("k,alpha,n,reset,written", [
     (14, 6, 24_575, "k_update_fresh", "k_update"), (14, 6, 24_576, "linear", "linear"),
     (16, 6, 24_576, "linear", "k_update"), (16, 6, 40_959, "linear", "k_update"),
